@@ -191,7 +191,8 @@ lts_status lts_set_induce_slices(lts_context *ctx, int32_t slices);
  * (1, 2, 4 or 8; 0 = the smallest that covers the table length plus a typical charge extent, and for 8 ticks the
  * loop that loads the next cell-tick block's window while computing the current one; an explicit 8 selects the
  * loop without that prefetch).  All choices give the same sums in the same order.  In LTS_REDUCE_SUMMED: 0 = one
- * wavefront per (pixel, 256-tick tile) with the table window staged in LDS (default), 8 = one wavefront per
+ * wavefront per (pixel, 768 ticks) on the FP16 matrix cores, every FP32 factor split into a pair of halves (default;
+ * error against FP64 no larger than the FP32 forms'), 8 = one wavefront per
  * (pixel, 512-tick tile) with register-resident table windows, 1, 2, 4 = the per-pair workgroup kernel over the
  * summed pieces; these agree to FP32 summation order. */
 lts_status lts_set_ticks_per_thread(lts_context *ctx, int32_t rt);

@@ -22,7 +22,8 @@ constexpr int kTileTicks = 512;      // ticks of one wavefront work unit of the 
 constexpr int kPieceMax = 248;       // maximum ticks of a summed charge column piece
 // Zero padding on each side of every table column.  The per-pair induction reads at most kNaMax + 16 values below
 // and kNaMax + 8 above the table span; the summed induction's tiles overhang a column's tick window by up to
-// kTileTicks - 1 ticks, so it reads at most kTileTicks + kPieceMax + 16 below and kTileTicks + kPieceMax above.
+// kTileTicks - 1 ticks, so it reads at most kTileTicks + kPieceMax + 16 below and kTileTicks + kPieceMax above (its
+// matrix form, in 256-tick tiles and 72-tick parts, less).
 constexpr int kPad = 792;
 static_assert(kPad % 8 == 0, "table columns keep 32-byte alignment");
 static_assert(kPad >= kNaMax + 16, "per-pair induction reads");

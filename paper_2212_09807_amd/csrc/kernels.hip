@@ -31,6 +31,10 @@ constexpr uint64_t kMask40 = (1ull << 40) - 1;
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
+__device__ __forceinline__ float lane_value(float v, int32_t l) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, v), l));
+}
+
 // FP64 per-event report accumulation, aggregated over the wavefront when all valid lanes share the event.
 // Must be reached by all 64 lanes of the wavefront.
 __device__ __forceinline__ void add_report(double *rep, int e, int k, double v, bool valid) {
@@ -2097,6 +2101,7 @@ __global__ __launch_bounds__(kWG) void k_sum_pieces(DevParams P, const SegInfo *
                 int64_t np, Lpad;
                 sum_interval_size(L, np, Lpad);
                 float *S = sw.S + so;
+                float top = 0.0f;                       // largest charge of the interval
                 for (int32_t a0c = 0; a0c < Lpad; a0c += 64) {
                     const int32_t aa = lo + a0c + lane, ch = min(lo + a0c + 63, hi);
                     float sum = 0.0f, cmp = 0.0f;
@@ -2127,8 +2132,14 @@ __global__ __launch_bounds__(kWG) void k_sum_pieces(DevParams P, const SegInfo *
                                 sum = t;
                             }
                     }
-                    if (a0c + lane < Lpad) S[a0c + lane] = sum - cmp;
+                    if (a0c + lane < Lpad) {
+                        S[a0c + lane] = sum - cmp;
+                        top = fmaxf(top, fabsf(sum - cmp));
+                    }
                 }
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+                const int32_t ex = __builtin_bit_cast(int32_t, top) >> 23;
                 for (int64_t k = lane; k < np; k += 64) {
                     SegInfo g = {};
                     g.u0 = u; g.nu = 1; g.v0 = v; g.nv = 1;
@@ -2139,7 +2150,7 @@ __global__ __launch_bounds__(kWG) void k_sum_pieces(DevParams P, const SegInfo *
                     g.event = e;
                     g.n_pairs = 1;
                     if (sw.piece_lists) sw.piece[pk + k] = g;
-                    sw.pdesc[pk + k] = PieceRef{g.a0, g.na, (uint32_t)(g.cell_off / kAC), 0};
+                    sw.pdesc[pk + k] = PieceRef{g.a0, g.na, (uint32_t)(g.cell_off / kAC), ex << kBinBits};
                 }
                 pk += np;
                 so += Lpad;
@@ -2236,7 +2247,7 @@ __global__ __launch_bounds__(kWG) void k_sum_lists_fill(DevParams P, int64_t n_s
                     }
                 if (sw.piece_lists) sw.list[q] = (int32_t)k;
                 PieceRef r = sw.pdesc[k];
-                r.bin = b;
+                r.bin |= b;
                 sw.rec[q] = r;
             }
         }
@@ -2307,7 +2318,8 @@ __global__ __launch_bounds__(kWG) void k_sum_merge(int64_t n_slots, SumWork sw) 
         if (in) r = sw.rec[c0 + lane];
         const int32_t end = r.a0 + r.na - 1;
         // runs: a new bin, or a first tick beyond the bin's spans so far (first ticks ascend within a bin) + the gap
-        const bool fb = lane == 0 || r.bin != __shfl_up(r.bin, 1);
+        const int32_t bin = r.bin & kBinMask;
+        const bool fb = lane == 0 || bin != __shfl_up(bin, 1);
         const int32_t mb = seg_scan_max(end, fb);
         const int32_t mprev = __shfl_up(mb, 1);
         bool st = fb || r.a0 > mprev + 1 + kMergeGap;
@@ -2326,6 +2338,9 @@ __global__ __launch_bounds__(kWG) void k_sum_merge(int64_t n_slots, SumWork sw) 
         const bool multi = st && nxt - lane > 1;
         const int32_t L = multi ? rhi - r.a0 + 1 : r.na;
         const int32_t Lp = multi ? (L + kAC - 1) / kAC * kAC : 0;
+        // bound of a merged run's charge: its members' largest exponent, raised by the bits of their number
+        const int32_t emax = __shfl(seg_scan_max((int32_t)((uint32_t)r.bin >> kBinBits), st), max(nxt - 1, 0));
+        const int32_t mexp = min(emax + 32 - __builtin_clz(max(nxt - lane, 2) - 1), 254);
         int64_t incl = Lp;                              // inclusive prefix of the merged-charge floats
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
@@ -2336,7 +2351,7 @@ __global__ __launch_bounds__(kWG) void k_sum_merge(int64_t n_slots, SumWork sw) 
             const int64_t moff = nm + incl - Lp;
             if (st) {
                 const int64_t g = ng + __builtin_popcountll(starts & ((1ull << lane) - 1ull));
-                sw.mrec[g] = multi ? PieceRef{r.a0, L, sw.nS8 + (uint32_t)(moff / kAC), r.bin} : r;
+                sw.mrec[g] = multi ? PieceRef{r.a0, L, sw.nS8 + (uint32_t)(moff / kAC), bin | mexp << kBinBits} : r;
             }
             uint64_t mm = __ballot(multi);
             while (mm) {                                // each merged run: its charge, lanes over its ticks
@@ -2397,6 +2412,30 @@ void launch_sum_merge(const SumWork &sw, int64_t n_slots, bool fill, hipStream_t
 // A record's summed charge: in the column pieces' buffer, or in the merged records' one.
 __device__ __forceinline__ const float *cell_ptr(const float *S, const float *Sm, uint32_t nS8, uint32_t cell8) {
     return cell8 < nS8 ? S + (int64_t)cell8 * kAC : Sm + (int64_t)(cell8 - nS8) * kAC;
+}
+
+// Charge that a pixel's records induce outside the readout, by one wavefront, added to the event's report.
+__device__ __forceinline__ void clipped_records(const DevParams &P, const float *S, const float *Sm, uint32_t nS8,
+                                                const double *prefix, const PieceRef *rec, int64_t pb, int64_t pe,
+                                                int32_t e, double *report) {
+    const int32_t NT = P.nticks, TR = P.t_r, lane = lane_id();
+    double clip = 0.0;
+    for (int64_t k = pb + lane; k < pe; k += 64) {
+        const PieceRef g = rec[k];
+        const int32_t wlo = g.a0 - (TR - 1), whi = g.a0 + g.na - 1;
+        if (wlo >= 0 && whi < NT) continue;
+        const double *pf = prefix + (int64_t)(g.bin & kBinMask) * (TR + 1);
+        const float *cv = cell_ptr(S, Sm, nS8, g.cell8);
+        for (int32_t a = 0; a < g.na; ++a) {
+            const int32_t aa = g.a0 + a;
+            const int32_t klo = min(max(TR - 1 - aa, 0), TR), khi = min(max(NT + TR - 1 - aa, 0), TR);
+            const double dropped = klo >= khi ? pf[TR] : pf[klo] + (pf[TR] - pf[khi]);
+            clip += (double)cv[a] * dropped;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) clip += __shfl_xor(clip, o);
+    if (lane == 0 && clip != 0.0) atomicAdd(&report[(int64_t)e * 5 + 3], clip);
 }
 
 constexpr int32_t kSumKahanEvery = 4;   // pieces summed in FP32 registers between compensated additions
@@ -2467,7 +2506,7 @@ __global__ __launch_bounds__(kWG) void k_induce_summed(DevParams P, const SegInf
             int64_t q = skip(pb);
             if (q < pe) {
                 auto colp = [&](const PieceRef &r) {
-                    return Rpad + (int64_t)r.bin * P.col_len + (nb - r.a0 + TR - 1 + kPad);
+                    return Rpad + (int64_t)(r.bin & kBinMask) * P.col_len + (nb - r.a0 + TR - 1 + kPad);
                 };
                 const PieceRef r0 = rec[q];
                 auto adv = [&](const float *&ncol, const float *&ncc, int32_t &nn) {
@@ -2525,7 +2564,7 @@ __global__ __launch_bounds__(kWG) void k_induce_summed(DevParams P, const SegInf
                 const PieceRef g = rec[k];
                 const int32_t wlo = g.a0 - (TR - 1), whi = g.a0 + g.na - 1;
                 if (wlo >= 0 && whi < NT) continue;
-                const double *pf = prefix + (int64_t)g.bin * (TR + 1);
+                const double *pf = prefix + (int64_t)(g.bin & kBinMask) * (TR + 1);
                 const float *cv = cell_ptr(S, Sm, nS8, g.cell8);
                 for (int32_t a = 0; a < g.na; ++a) {
                     const int32_t aa = g.a0 + a;
@@ -2541,47 +2580,138 @@ __global__ __launch_bounds__(kWG) void k_induce_summed(DevParams P, const SegInf
     }
 }
 
-// Summed induction in 256-tick work units (active pixel, tile of kTile4 ticks), one wavefront each: lane t owns
-// ticks t0 + 4t .. +3.  The pixel's records are scanned 64 at a time (a ballot of those whose tick window
-// [a0 - T_R + 1, a0 + na - 1] meets the tile); for each, the wavefront stages the table values the tile needs
-// (index t0 - a0 - nap + 1 .. t0 - a0 + 255 of the column, relative to its lag-0 entry) in its LDS slice with aligned
-// 16-byte copies, then streams the record's 8-tick charge blocks (uniform loads) against a 12-value window that moves
-// down 8 values per block (two aligned LDS reads per block).  Lanes whose ticks lie outside the record's window meet
-// the table's zero padding.  Products go to the lane's running sums with Kahan compensation after every 4 records
-// (records in list order: deterministic and batch-invariant).  The first tile of a pixel also accounts the charge
-// its records induce outside the readout.  Charge intervals start at any tick: the staged copy is loaded from the
-// 16-byte aligned column entry at or below its first value and written to LDS shifted down by the difference.
-constexpr int32_t kTile4 = 256;                         // ticks of one work unit: 64 lanes x 4
-constexpr int32_t kStage4 = kTile4 + kPieceMax + 8;     // staged table values per record and unit (at most)
+// ------------------------------------------------------------------------------------------ half-pair matrix form
+// Summed induction on the FP16 matrix cores.  Every FP32 factor is a pair of halves, x 2^k = h + l with h = half(x 2^k)
+// and l = half(x 2^k - h): 22 or more significant bits of x, and h h', h l', l h' are exact in the FP32 accumulator (the
+// dropped l l' is below 2^-22 of the product).  2^k puts the largest value of a table column (fixed when the table is
+// installed) below 2^15; for the charge, k is common to the 64 records of a chunk, the largest that keeps every one's
+// product with its column scale in range, so small values lose bits only below 2^-39 of the chunk's largest product.
+//
+// One wavefront per work unit (active pixel, kMmaTiles tiles of 256 ticks), taken from a counter.  A record's current on
+// a tile's ticks t0 + 16 j + i is D[i][j] = sum_w A[i][w] B[w][j] with A[i][w] = S[i - w + off] (the charge, a Toeplitz
+// matrix) and B[w][j] = R[16 j + w + c], w in [0, off + 16).  off is the smallest value >= L - 1 that makes c a multiple
+// of 8, so that a lane's 8 consecutive table values are one aligned 16-byte word; every w is covered 32 at a time by a
+// 16x16x32 instruction (lane l gives A[l % 16][8 (l / 16) ..] and B[8 (l / 16) ..][l % 16]).  The table words of a
+// record's window are staged in LDS (a tile reads each about 4 times), the charge as eight copies shifted by one value,
+// so that every lane's 8 consecutive (reversed) values are one aligned 16-byte word too; A then serves all tiles.
+// Tiles outside the record's window are skipped.  The products stay in the matrix accumulators over kMmaKahanEvery
+// records and are then added to the lane's sums with Kahan compensation, in list order (deterministic and
+// batch-invariant).
+//
+// The vector-ALU form of the same sums (256-tick units, 32 multiply-adds per lane against three LDS reads) took 37.5 ms
+// on a module event of 20,000 segments (13.6 million records, 1.37e12 products) and 36.2 ms on a spill tile of 64,000;
+// this one 16.7 and 16.8 ms, at an error against FP64 that is 0.7 to 0.95 of its (1.18e-7 against 1.33e-7 of the norm; a
+// compensated addition after every 4 parts instead of 2 would save 2 % and leave 0.93 to 0.98).
+// It runs at the card's power limit (2.07 GHz against 2.34 GHz), with the matrix cores busy 30 % and LDS about 75 % of
+// the time.  3 tiles per unit run 4 wavefronts per SIMD; 4 tiles (3 wavefronts) took 2 to 3 % longer, 2 tiles 10 % and
+// 1 tile 40 %: the charge is staged for fewer products.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
-// Block of 4 ticks x 8 charge ticks: tick r of the lane against charge tick q uses window value r - q + 7.
-__device__ __forceinline__ void block4(const float (&w)[12], const float (&c)[kAC], float (&acc)[4]) {
+constexpr int32_t kMmaSub = 256;                        // ticks of one tile
+constexpr int32_t kMmaTiles = 3;                        // tiles of a work unit
+constexpr int32_t kMmaUnit = kMmaTiles * kMmaSub;
+constexpr int32_t kMmaPart = 72;                        // charge ticks taken at a time (at most three steps of 32)
+constexpr int32_t kMmaLow = 24;                         // staged charge position of a part's last tick
+constexpr int32_t kMmaCopy = 144;                       // halves of one shifted copy (288 B: the copies' banks differ by 8)
+constexpr int32_t kMmaOct = kMmaTiles * 32 + 16;        // octets (8 table values, 16 bytes) of the longest window
+constexpr int32_t kMmaKahanEvery = 2;                   // parts summed in the accumulators between compensated additions
+static_assert(kPad >= kMmaSub + kMmaPart + 16 + 96, "summed matrix induction reads");
+
+struct alignas(16) MmaStage {                           // LDS of one wavefront
+    u32x4 r[2][kMmaOct];                                // [plane][octet] of the table window
+    uint32_t s[2][8][kMmaCopy / 2];                     // [plane][shift] of the reversed charge: copy k holds position m + k at m
+};
+
+// Planes of the response table: half pairs of column b scaled by 2^exps[b], in the layout of the FP32 columns.
+__global__ __launch_bounds__(kWG) void k_table_halves(const float *__restrict__ Rpad, int32_t col_len,
+                                                      _Float16 *__restrict__ hi, _Float16 *__restrict__ lo,
+                                                      int32_t *__restrict__ exps) {
+    __shared__ float red[kWG / 64];
+    const int64_t base = (int64_t)blockIdx.x * col_len;
+    float m = 0.0f;
+    for (int32_t k = threadIdx.x; k < col_len; k += kWG) m = fmaxf(m, fabsf(Rpad[base + k]));
 #pragma unroll
-    for (int q = 0; q < kAC; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = fmaf(c[q], w[r - q + 7], acc[r]);
-}
-__device__ __forceinline__ void window4(const float *p, float (&w)[12]) {
-    const float4 x = *(const float4 *)p, y = *(const float4 *)(p + 4), z = *(const float4 *)(p + 8);
-    w[0] = x.x; w[1] = x.y; w[2] = x.z; w[3] = x.w; w[4] = y.x; w[5] = y.y; w[6] = y.z; w[7] = y.w;
-    w[8] = z.x; w[9] = z.y; w[10] = z.z; w[11] = z.w;
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if (lane_id() == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    for (int i = 0; i < kWG / 64; ++i) m = fmaxf(m, red[i]);
+    const int32_t e = m > 0.0f ? 14 - ilogbf(m) : 0;
+    if (threadIdx.x == 0) exps[blockIdx.x] = e;
+    for (int32_t k = threadIdx.x; k < col_len; k += kWG) {
+        const float x = ldexpf(Rpad[base + k], e);
+        const _Float16 h = (_Float16)x;
+        hi[base + k] = h;
+        lo[base + k] = (_Float16)(x - (float)h);
+    }
 }
 
-__global__ __launch_bounds__(kWG) void k_induce_summed4(DevParams P, const float *__restrict__ S,
-                                                        const float *__restrict__ Sm, uint32_t nS8,
-                                                        const float *__restrict__ Rpad,
-                                                        const double *__restrict__ prefix,
-                                                        const int64_t *__restrict__ list_off,
-                                                        const PieceRef *__restrict__ rec,
-                                                        const int32_t *__restrict__ order,
-                                                        const int32_t *__restrict__ slot_gp, float *__restrict__ wave,
-                                                        DevHeader *H, double *report) {
-    __shared__ __align__(16) float stage_all[kWG / 64][4 + kStage4];
-    const int lane = threadIdx.x & 63;
-    float *stage = stage_all[threadIdx.x >> 6] + 4;     // 4 head floats take the unneeded values of a shifted copy
+void launch_table_halves(const float *Rpad, int32_t n_col, int32_t col_len, void *hi, void *lo, int32_t *exps,
+                         hipStream_t st) {
+    k_table_halves<<<(unsigned)n_col, kWG, 0, st>>>(Rpad, col_len, (_Float16 *)hi, (_Float16 *)lo, exps);
+}
+
+// Tiles T0 .. T1 of a staged part (kn steps of 32) into their accumulators; tiles in pairs: two independent chains, few
+// registers.
+template <int T0, int T1>
+__device__ __forceinline__ void mma_tiles(const u32x4 *rl, const u32x4 *sl, int32_t kn, floatx4 (&D)[kMmaTiles]) {
+    for (int32_t k = 0; k < kn; ++k) {
+        const half8 ah = __builtin_bit_cast(half8, sl[4 * k]), al = __builtin_bit_cast(half8, sl[4 * k + kMmaCopy]);
+#pragma unroll
+        for (int T = T0; T <= T1; T += 2) {
+            const u32x4 *r0 = rl + 32 * (T - T0) + 4 * k;
+            const half8 h0 = __builtin_bit_cast(half8, r0[0]), l0 = __builtin_bit_cast(half8, r0[kMmaOct]);
+            if (T < T1) {
+                const half8 h1 = __builtin_bit_cast(half8, r0[32]), l1 = __builtin_bit_cast(half8, r0[kMmaOct + 32]);
+                D[T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, h0, D[T], 0, 0, 0);
+                D[T + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, h1, D[T + 1], 0, 0, 0);
+                D[T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, h0, D[T], 0, 0, 0);
+                D[T + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, h1, D[T + 1], 0, 0, 0);
+                D[T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, l0, D[T], 0, 0, 0);
+                D[T + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, l1, D[T + 1], 0, 0, 0);
+            } else {
+                D[T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, h0, D[T], 0, 0, 0);
+                D[T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, h0, D[T], 0, 0, 0);
+                D[T] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, l0, D[T], 0, 0, 0);
+            }
+        }
+    }
+}
+// The tiles t0 .. t1 of a part (uniform), each range its own straight code (the whole unit first).
+template <int T0 = 0, int T1 = kMmaTiles - 1>
+__device__ __forceinline__ void mma_dispatch(const u32x4 *rl, const u32x4 *sl, int32_t kn, int32_t t0, int32_t t1,
+                                             floatx4 (&D)[kMmaTiles]) {
+    if (t0 == T0 && t1 == T1) return mma_tiles<T0, T1>(rl, sl, kn, D);
+    if constexpr (T1 > T0) mma_dispatch<T0, T1 - 1>(rl, sl, kn, t0, t1, D);
+    else if constexpr (T0 + 1 < kMmaTiles) mma_dispatch<T0 + 1, kMmaTiles - 1>(rl, sl, kn, t0, t1, D);
+}
+
+__global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const float *__restrict__ S,
+                                                              const float *__restrict__ Sm, uint32_t nS8,
+                                                              const u32x4 *__restrict__ Rh, const u32x4 *__restrict__ Rl,
+                                                              const int32_t *__restrict__ Rexp,
+                                                              const int64_t *__restrict__ list_off,
+                                                              const PieceRef *__restrict__ rec,
+                                                              const int32_t *__restrict__ order,
+                                                              float *__restrict__ wave, DevHeader *H) {
+    __shared__ MmaStage stage_all[kWG / 64];
+    MmaStage &st = stage_all[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
     const int32_t NT = P.nticks, TR = P.t_r;
-    const int32_t n_tiles = (NT + kTile4 - 1) / kTile4;
+    const int32_t n_tiles = (NT + kMmaUnit - 1) / kMmaUnit;
     const int64_t n_units = H->n_slots * n_tiles;
+    // staged charge: positions below kMmaLow - 1 stay zero
+    for (int32_t k = lane; k < 2 * 8 * kMmaCopy / 2; k += 64) st.s[0][0][k] = 0u;
+    const u32x4 *rl = st.r[0] + 2 * li + lg;             // this lane's octet of tile 0, step 0
+    // staging of the charge: lane k holds positions kMmaLow - 1 + k (and + 63 in the second round) and writes them with
+    // their upper neighbour, one word per copy of its position's parity
+    uint32_t *ws[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int32_t q = kMmaLow - 1 + 63 * r + lane;
+        ws[r] = &st.s[0][q & 1][(q - (q & 1)) / 2];
+    }
+    const int32_t pos0 = 15 - li + 8 * lg + kMmaLow;
     for (;;) {
         uint32_t got = 0;
         if (lane == 0) got = atomicAdd(&H->work[2], 1u);
@@ -2589,125 +2719,213 @@ __global__ __launch_bounds__(kWG) void k_induce_summed4(DevParams P, const float
         if (unit >= n_units) break;
         const int64_t ui = unit / n_tiles;
         const int64_t slot = order ? order[ui] : ui;                    // largest-first when an order is given
-        const int32_t t0 = (int32_t)(unit - ui * n_tiles) * kTile4, t1 = t0 + kTile4 - 1;
-        const int32_t gp = slot_gp[slot];
-        const int32_t e = gp / P.npx;
+        const int32_t t0 = (int32_t)(unit - ui * n_tiles) * kMmaUnit, t1 = min(t0 + kMmaUnit, NT) - 1;
         const int64_t pb = list_off[slot], pe = list_off[slot + 1];
-        float acc[4], sum[4], cmp[4];
+        float sum[4 * kMmaTiles], cmp[4 * kMmaTiles];
+        floatx4 D[kMmaTiles];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) { acc[r] = 0.0f; sum[r] = 0.0f; cmp[r] = 0.0f; }
-        int32_t pending = 0;
+        for (int T = 0; T < kMmaTiles; ++T) D[T] = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int r = 0; r < 4 * kMmaTiles; ++r) { sum[r] = 0.0f; cmp[r] = 0.0f; }
         for (int64_t c0 = pb; c0 < pe; c0 += 64) {
-            PieceRef rl{0, 0, 0, 0};
+            // 64 records at a time: each lane prepares one
+            PieceRef pr{0, 0, 0, 0};
             const bool in = c0 + lane < pe;
-            if (in) rl = rec[c0 + lane];
-            uint64_t mask = __ballot(in && rl.a0 + rl.na - 1 >= t0 && rl.a0 - (TR - 1) <= t1);
-            if (!mask) continue;
-            // record i of the chunk: its fields, and the lane's two staged float4s of it, loaded ahead
-            int32_t a0 = 0, nblk = 0, n4 = 0, dl = 0;
-            uint32_t c8 = 0;
-            float4 g0 = {0, 0, 0, 0}, g1 = {0, 0, 0, 0};
-            auto fetch = [&](int i) {
-                a0 = __builtin_amdgcn_readlane(rl.a0, i);
-                const int32_t na = __builtin_amdgcn_readlane(rl.na, i);
-                const int32_t bin = __builtin_amdgcn_readlane(rl.bin, i);
-                c8 = (uint32_t)__builtin_amdgcn_readlane((int)rl.cell8, i);
-                nblk = (na + kAC - 1) / kAC;
-                // the values staged are column entries idx0 .. idx0 + 255 + 8 nblk; they are loaded from the
-                // 16-byte aligned entry idx0 - dl below (table columns start 32-byte aligned)
-                const int32_t idx0 = t0 - a0 - nblk * kAC + TR + kPad;
-                dl = idx0 & 3;
-                n4 = (kTile4 + nblk * kAC + dl + 3) / 4;
-                const float *src = Rpad + (int64_t)bin * P.col_len + (idx0 - dl);
-                g0 = *(const float4 *)(src + 4 * lane);
-                if (lane + 64 < n4) g1 = *(const float4 *)(src + 4 * (lane + 64));
-            };
-            while (mask) {
-                const int i = __builtin_ctzll(mask);
-                mask &= mask - 1ull;
-                fetch(i);
-                // the previous record's window reads are done before the slice is overwritten
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                if (dl == 0) {
-                    *(float4 *)(stage + 4 * lane) = g0;
-                    if (lane + 64 < n4) *(float4 *)(stage + 4 * (lane + 64)) = g1;
-                } else {                                // dl entries down: lane 0's first ones land in the head
-                    float *d0 = stage + 4 * lane - dl;
-                    d0[0] = g0.x; d0[1] = g0.y; d0[2] = g0.z; d0[3] = g0.w;
-                    if (lane + 64 < n4) {
-                        float *d1 = d0 + 256;
-                        d1[0] = g1.x; d1[1] = g1.y; d1[2] = g1.z; d1[3] = g1.w;
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const int32_t nb_cur = nblk;
-                cfloat_ptr cc = uniform_cptr(cell_ptr(S, Sm, nS8, c8));
-                // 8-tick charge blocks against the 12-value window that moves down 8 per block (the latency of the
-                // window and charge loads is covered by the other wavefronts of the SIMD)
-                int32_t wb = 4 * lane + nb_cur * kAC - 8;
-                for (int32_t j = 0; j < nb_cur; ++j, wb -= 8) {
-                    float W[12], cv[kAC];
-                    window4(stage + wb, W);
+            if (in) pr = rec[c0 + lane];
+            const int32_t bin = pr.bin & kBinMask;
+            const bool meets = in && pr.a0 + pr.na - 1 >= t0 && pr.a0 - TR + 1 <= t1;
+            if (!__ballot(meets)) continue;
+            // the chunk's scale 2^N: charge x 2^(N - eb) below 2^15 for every record
+            const int32_t eb = meets ? Rexp[bin] : 0;
+            int32_t N = meets ? min(141 - (int32_t)((uint32_t)pr.bin >> kBinBits), 126) + eb : INT32_MAX;
 #pragma unroll
-                    for (int q = 0; q < kAC; ++q) cv[q] = cc[kAC * j + q];
-                    block4(W, cv, acc);
-                }
-                if (++pending == kSumKahanEvery) {
+            for (int o = 32; o > 0; o >>= 1) N = min(N, __shfl_xor(N, o));
+            N = min(max(__builtin_amdgcn_readfirstlane(N), -126), 126);
+            const float up = ldexpf(1.0f, N - eb), down = ldexpf(1.0f, -N);
+            int pending = 0;
+            auto flush = [&] {
+#pragma unroll
+                for (int T = 0; T < kMmaTiles; ++T) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const float y = acc[r] - cmp[r];
-                        const float t = sum[r] + y;
-                        cmp[r] = (t - sum[r]) - y;
-                        sum[r] = t;
-                        acc[r] = 0.0f;
+                        const float y = fmaf(D[T][r], down, -cmp[4 * T + r]);
+                        const float t = sum[4 * T + r] + y;
+                        cmp[4 * T + r] = (t - sum[4 * T + r]) - y;
+                        sum[4 * T + r] = t;
                     }
-                    pending = 0;
+                    D[T] = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
                 }
-            }
-        }
-        if (pending) {
+                pending = 0;
+            };
+            // records longer than kMmaPart ticks go in several rounds over the chunk
+            for (int32_t done = 0;; done += kMmaPart) {
+                const int32_t L = min(pr.na - done, kMmaPart), a0 = pr.a0 + done;
+                const int32_t lo = a0 - TR + 1 - t0, hi = a0 + L - 1 - t0;
+                uint64_t mask = __ballot(meets && L > 0 && hi >= 0 && lo <= t1 - t0);
+                const int32_t T0 = max(lo, 0) / kMmaSub, T1 = min(hi, t1 - t0) / kMmaSub;
+                const int32_t off = L - 1 + ((TR - a0 - L) & 7), kn = (off + 47) / 32;
+                // table bytes [v_at, v_end) of a plane are what the tiles read, charge bytes [v_q, v_q + 4 L)
+                const uint32_t v_at = (uint32_t)(bin * P.col_len + t0 + T0 * kMmaSub - a0 - off + TR - 1 + kPad) * 2u;
+                const uint32_t v_end = v_at + 16u * (uint32_t)(32 * (T1 - T0 + 1) + 4 * kn - 2);
+                const int32_t pack = 4 * L | kn << 9 | T0 << 11 | T1 << 13 | (off + 16 - L) << 15;
+                const uint64_t v_q = (uint64_t)(cell_ptr(S, Sm, nS8, pr.cell8) + done);
+                // a part in hand: its fields and the lane's words of it, loaded one part ahead
+                u32x4 gh[2], gl[2];
+                float x[2] = {0.0f, 0.0f}, xu = 0.0f;
+                int32_t qp = 0;
+                auto fetch = [&](int i) {
+                    qp = __builtin_amdgcn_readlane(pack, i);
+                    xu = lane_value(up, i);
+                    const int32_t o = __builtin_amdgcn_readlane((int)v_at, i), end = __builtin_amdgcn_readlane((int)v_end, i);
+                    // loads past the ends return zeros without touching memory
+                    const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc((void *)Rh, (short)0, end, kBufferWord3);
+                    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)Rl, (short)0, end, kBufferWord3);
+                    gh[0] = __builtin_amdgcn_raw_buffer_load_b128(rh, 16 * lane, o, 0);
+                    gl[0] = __builtin_amdgcn_raw_buffer_load_b128(rw, 16 * lane, o, 0);
+                    gh[1] = __builtin_amdgcn_raw_buffer_load_b128(rh, 16 * lane + 1024, o, 0);
+                    gl[1] = __builtin_amdgcn_raw_buffer_load_b128(rw, 16 * lane + 1024, o, 0);
+                    const int32_t l4 = qp & 511;
+                    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
+                        (void *)uniform_i64((int64_t)v_q, i), (short)0, l4, kBufferWord3);
+                    x[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rq, l4 - 4 * lane, 0, 0));
+                    if ((qp >> 9 & 3) > 2)
+                        x[1] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rq, l4 - 4 * lane - 252, 0, 0));
+                };
+                if (mask) fetch(__builtin_ctzll(mask));
+                while (mask) {
+                    mask &= mask - 1ull;
+                    const int32_t p = qp, pk = p >> 9 & 3, pT0 = p >> 11 & 3, pT1 = p >> 13 & 3;
+                    // the previous part's reads of the slice are done before it is overwritten
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    st.r[0][lane] = gh[0];
+                    st.r[1][lane] = gl[0];
+                    if (pT1 > pT0 && lane + 64 < kMmaOct) {
+                        st.r[0][lane + 64] = gh[1];
+                        st.r[1][lane + 64] = gl[1];
+                    }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float y = acc[r] - cmp[r];
-                const float t = sum[r] + y;
-                cmp[r] = (t - sum[r]) - y;
-                sum[r] = t;
+                    for (int r = 0; r < 2; ++r) {
+                        if (r == 1 && pk < 3) break;
+                        const float y = x[r] * xu;
+                        const _Float16 h = (_Float16)y, l = (_Float16)(y - (float)h);
+                        const uint32_t w = (uint32_t)__builtin_bit_cast(uint16_t, h) |
+                                           (uint32_t)__builtin_bit_cast(uint16_t, l) << 16;
+                        // lane + 1's values (DPP wave_shl:1, zero past lane 63: the next round writes that word again)
+                        const uint32_t v = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x130, 0xf, 0xf, true);
+                        const uint32_t wh = __builtin_amdgcn_perm(v, w, 0x05040100), wl = __builtin_amdgcn_perm(v, w, 0x07060302);
+                        if (r == 0 || lane < 40)            // (three steps read up to position 119)
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                ws[r][k * (kMmaCopy - 1)] = wh;
+                                ws[r][k * (kMmaCopy - 1) + 8 * kMmaCopy / 2] = wl;
+                            }
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    if (mask) fetch(__builtin_ctzll(mask));
+                    // A[i][8g + q] is at position 15 - i + 8g + q + (kMmaLow - (off + 16 - L))
+                    const int32_t pos = pos0 - (p >> 15);
+                    const u32x4 *sl = (const u32x4 *)&st.s[0][pos & 7][0] + (pos >> 3);
+                    mma_dispatch(rl, sl, pk, pT0, pT1, D);
+                    if (++pending == kMmaKahanEvery) flush();
+                }
+                if (!__ballot(meets && pr.na > done + kMmaPart)) break;
             }
+            if (pending) flush();
         }
         float *wrow = wave + slot * NT;
-        const int32_t nb = t0 + 4 * lane;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (nb + r < NT) wrow[nb + r] = sum[r] - cmp[r];
-        if (t0 == 0) {                                  // charge induced outside [0, NT) by the pixel's records
-            double clip = 0.0;
-            for (int64_t k = pb + lane; k < pe; k += 64) {
-                const PieceRef g = rec[k];
-                const int32_t wlo = g.a0 - (TR - 1), whi = g.a0 + g.na - 1;
-                if (wlo >= 0 && whi < NT) continue;
-                const double *pf = prefix + (int64_t)g.bin * (TR + 1);
-                const float *cv = cell_ptr(S, Sm, nS8, g.cell8);
-                for (int32_t a = 0; a < g.na; ++a) {
-                    const int32_t aa = g.a0 + a;
-                    const int32_t klo = min(max(TR - 1 - aa, 0), TR), khi = min(max(NT + TR - 1 - aa, 0), TR);
-                    const double dropped = klo >= khi ? pf[TR] : pf[klo] + (pf[TR] - pf[khi]);
-                    clip += (double)cv[a] * dropped;
-                }
-            }
+        for (int T = 0; T < kMmaTiles; ++T) {
+            const int32_t nb = t0 + kMmaSub * T + 16 * li + 4 * lg;
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) clip += __shfl_xor(clip, o);
-            if (lane == 0 && clip != 0.0) atomicAdd(&report[(int64_t)e * 5 + 3], clip);
+            for (int r = 0; r < 4; ++r)
+                if (nb + r < NT) wrow[nb + r] = sum[4 * T + r] - cmp[4 * T + r];
         }
     }
 }
 
-bool summed_tile256(int32_t rt, bool shift) { return rt == 0 && !shift; }
+// ------------------------------------------------------------------------------------------ charge outside the readout
+// The signed induction that falls outside [0, n_ticks), from FP64 prefix sums of the table columns.  Charge in column
+// (u, v) at tick a induces on every pixel that reaches the column, and only the sum over an event's pixels is reported, so
+// the pixels' prefix sums are added first: for a column whose reaching pixels all lie on the grid they depend only on its
+// offset within a pixel (a class of n_sub^2, summed when the table is installed); at the grid's edge the pixels are
+// walked.
+__global__ __launch_bounds__(kWG) void k_clip_classes(DevParams P, const double *__restrict__ prefix,
+                                                      double *__restrict__ cls) {
+    const int32_t c = blockIdx.x, ru = c / P.nsub, rv = c - ru * P.nsub, h = P.nsub / 2, n = P.t_r + 1;
+    auto first = [&](int32_t r, int32_t b) { return -b + ((r - h + b) % P.nsub + P.nsub) % P.nsub; };
+    for (int32_t k = threadIdx.x; k < n; k += kWG) {
+        double s = 0.0;
+        for (int32_t du = first(ru, P.bx); du < P.bx; du += P.nsub)
+            for (int32_t dv = first(rv, P.by); dv < P.by; dv += P.nsub)
+                s += prefix[(int64_t)(fold(du) * P.by + fold(dv)) * n + k];
+        cls[(int64_t)c * n + k] = s;
+    }
+}
+
+void launch_clip_classes(const DevParams &P, const double *prefix, double *cls, hipStream_t st) {
+    k_clip_classes<<<(unsigned)(P.nsub * P.nsub), kWG, 0, st>>>(P, prefix, cls);
+}
+
+// Dropped induction of unit charge in column (u, v) at tick a, summed over the pixels that reach the column.
+__device__ __forceinline__ double clip_weight(const DevParams &P, const double *__restrict__ prefix,
+                                              const double *__restrict__ cls, int32_t u, int32_t v, int32_t a) {
+    const int32_t T = P.t_r, h = P.nsub / 2, n = T + 1;
+    const int32_t klo = min(max(T - 1 - a, 0), T);                 // first kept table tick
+    const int32_t khi = min(max(P.nticks + T - 1 - a, 0), T);      // one past the last kept tick
+    if (klo == 0 && khi == T) return 0.0;
+    auto dropped = [&](const double *p) { return klo >= khi ? p[T] : p[klo] + (p[T] - p[khi]); };
+    const int32_t xa = ceil_div(u - h - P.bx + 1, P.nsub), xb = floor_div(u - h + P.bx, P.nsub);
+    const int32_t ya = ceil_div(v - h - P.by + 1, P.nsub), yb = floor_div(v - h + P.by, P.nsub);
+    if (cls && xa >= 0 && xb < P.nx && ya >= 0 && yb < P.ny) {
+        const int32_t ru = u - floor_div(u, P.nsub) * P.nsub, rv = v - floor_div(v, P.nsub) * P.nsub;
+        return dropped(cls + (int64_t)(ru * P.nsub + rv) * n);
+    }
+    double s = 0.0;
+    for (int32_t x = max(xa, 0); x <= min(xb, P.nx - 1); ++x)
+        for (int32_t y = max(ya, 0); y <= min(yb, P.ny - 1); ++y)
+            s += dropped(prefix + (int64_t)(fold(u - x * P.nsub - h) * P.by + fold(v - y * P.nsub - h)) * n);
+    return s;
+}
+
+// Summed mode: over the column pieces (a wavefront per column at a time).
+__global__ __launch_bounds__(kWG) void k_clip_columns(DevParams P, SumWork sw, const double *__restrict__ prefix,
+                                                      const double *__restrict__ cls, double *report) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t n_act = *sw.n_active, waves = gridDim.x * (kWG / 64);
+    double acc = 0.0;
+    int32_t ev = -1;
+    auto flush = [&] {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+        if (lane == 0 && acc != 0.0) atomicAdd(&report[(int64_t)ev * 5 + 3], acc);
+        acc = 0.0;
+    };
+    for (uint32_t ia = blockIdx.x * (kWG / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); ia < n_act;
+         ia += waves) {
+        const int64_t cc = __builtin_amdgcn_readfirstlane(sw.active[ia]);
+        const int32_t e = (int32_t)(cc / ((int64_t)sw.CU * sw.CV));
+        const int64_t r = cc - (int64_t)e * sw.CU * sw.CV;
+        const int32_t u = sw.UL + (int32_t)(r / sw.CV), v = sw.VL + (int32_t)(r % sw.CV);
+        if (e != ev && ev >= 0) flush();
+        ev = e;
+        for (int64_t k = sw.piece_off[cc]; k < sw.piece_off[cc + 1]; ++k) {
+            const PieceRef p = sw.pdesc[k];
+            if (p.a0 >= P.t_r - 1 && p.a0 + p.na <= P.nticks) continue;
+            const float *S = sw.S + (int64_t)p.cell8 * kAC;
+            for (int32_t i = lane; i < p.na; i += 64)
+                acc += (double)S[i] * clip_weight(P, prefix, cls, u, v, p.a0 + i);
+        }
+    }
+    if (ev >= 0) flush();
+}
+
+bool summed_matrix(int32_t rt, bool shift) { return rt == 0 && !shift; }
 int32_t summed_align_res(const DevParams &P, int32_t rt, bool shift) {
-    if (summed_tile256(rt, shift)) return -1;          // its staging copy realigns the table values itself
+    if (summed_matrix(rt, shift)) return -1;           // takes intervals at any tick
     return ((P.t_r - 1 + kPad) % 8 + 8) % 8;
 }
 
@@ -2757,11 +2975,12 @@ void launch_induce_summed(const DevParams &P, const Work &w, const SumWork &sw, 
         return;
     }
     if (n_slots <= 0) return;
-    if (summed_tile256(rt, shift)) {
-        const int64_t units = n_slots * ((P.nticks + kTile4 - 1) / kTile4);
-        const int64_t g = std::min<int64_t>((units + kWG / 64 - 1) / (kWG / 64), 256 * 8);
-        k_induce_summed4<<<(unsigned)g, kWG, 0, st>>>(P, sw.S, sw.Sm, sw.nS8, T.Rpad, T.prefix, sw.mlist_off, sw.mrec,
-                                                      order, w.slot_gp, wave, w.hdr, w.report);
+    if (summed_matrix(rt, shift)) {
+        k_clip_columns<<<256 * 4, kWG, 0, st>>>(P, sw, T.prefix, T.cls, w.report);
+        const int64_t units = n_slots * ((P.nticks + kMmaUnit - 1) / kMmaUnit);
+        const int64_t g = std::min<int64_t>((units + kWG / 64 - 1) / (kWG / 64), 256 * 4);
+        k_induce_summed_mma<<<(unsigned)g, kWG, 0, st>>>(P, sw.S, sw.Sm, sw.nS8, (const u32x4 *)T.hi, (const u32x4 *)T.lo,
+                                                         T.exps, sw.mlist_off, sw.mrec, order, wave, w.hdr);
         return;
     }
     const int64_t units = n_slots * ((P.nticks + kTileTicks - 1) / kTileTicks);
@@ -2791,9 +3010,6 @@ void launch_induce_summed(const DevParams &P, const Work &w, const SumWork &sw, 
 // segment of at most 64 ticks adds at most six roundings of its absolute sum, well inside the decision margin's
 // relative term.  (One thread per pixel walking the ticks in order was 4.4x slower: too few wavefronts, and a
 // dependent load per tick.)
-__device__ __forceinline__ float lane_value(float v, int32_t l) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int32_t, v), l));
-}
 
 __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *__restrict__ wave,
                                                      const int32_t *__restrict__ slot_gp,
@@ -3028,8 +3244,9 @@ void launch_work_stats(const DevParams &P, const SegInfo *si, int64_t n_seg, uns
 // Summed mode: a tick of a piece counts only if it holds charge (the ticks a piece adds for alignment, and the short
 // gaps between segments that a piece spans, hold exact zeros and are not algorithmic work).
 __global__ void k_work_stats_summed(DevParams P, int64_t n_slots, const int64_t *list_off, const PieceRef *rec,
-                                    const float *S, const int64_t *mlist_off, const PieceRef *mrec, int32_t tile,
+                                    const float *S, const int64_t *mlist_off, const PieceRef *mrec, bool matrix,
                                     unsigned long long *acc) {
+    const int32_t tile = matrix ? kMmaSub : kTileTicks;
     int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (slot >= n_slots) return;
     unsigned long long f = 0, cells = 0, issued = 0;
@@ -3047,14 +3264,21 @@ __global__ void k_work_stats_summed(DevParams P, int64_t n_slots, const int64_t 
         }
     }
     // products the summed kernel computes for the merged records, zeros included: every tile (of `tile` ticks) a
-    // record's window meets, all its ticks x every 8-tick charge block
+    // record's window meets, all its ticks x every 8-tick charge block (the matrix kernel: every 32-value step of a part)
     for (int64_t q = mlist_off[slot]; q < mlist_off[slot + 1]; ++q) {
         const PieceRef g = mrec[q];
         const int32_t t_lo = max(floor_div(g.a0 - P.t_r + 1, tile), 0);
         const int32_t t_hi = min(floor_div(g.a0 + g.na - 1, tile), n_tiles - 1);
-        if (t_hi >= t_lo)
-            issued += (unsigned long long)(t_hi - t_lo + 1) * (unsigned long long)((g.na + kAC - 1) / kAC) *
-                      (unsigned long long)(tile * kAC);
+        if (t_hi < t_lo) continue;
+        int32_t lags = (g.na + kAC - 1) / kAC * kAC;
+        if (matrix) {
+            lags = 0;
+            for (int32_t done = 0; done < g.na; done += kMmaPart) {
+                const int32_t L = min(g.na - done, kMmaPart);
+                lags += (L + 46 + ((P.t_r - g.a0 - done - L) & 7)) / 32 * 32;
+            }
+        }
+        issued += (unsigned long long)(t_hi - t_lo + 1) * (unsigned long long)lags * (unsigned long long)tile;
     }
     atomicAdd(&acc[0], (unsigned long long)(mlist_off[slot + 1] - mlist_off[slot]));
     atomicAdd(&acc[1], f);
@@ -3063,11 +3287,11 @@ __global__ void k_work_stats_summed(DevParams P, int64_t n_slots, const int64_t 
 }
 
 void launch_work_stats_summed(const DevParams &P, int64_t n_slots, const int64_t *list_off, const PieceRef *rec,
-                              const float *S, const int64_t *mlist_off, const PieceRef *mrec, bool tile256,
+                              const float *S, const int64_t *mlist_off, const PieceRef *mrec, bool matrix,
                               unsigned long long *acc, hipStream_t st) {
     if (n_slots > 0)
         k_work_stats_summed<<<(unsigned)((n_slots + kWG - 1) / kWG), kWG, 0, st>>>(
-            P, n_slots, list_off, rec, S, mlist_off, mrec, tile256 ? kTile4 : kTileTicks, acc);
+            P, n_slots, list_off, rec, S, mlist_off, mrec, matrix, acc);
 }
 
 // ================================================================================================= Philox test hook

@@ -46,6 +46,10 @@ constexpr int kOrderBuckets = 512;            // log-scale work buckets of the l
 struct Table {
     const float *Rpad = nullptr;             // [bx * by][col_len], zero-padded columns
     const double *prefix = nullptr;          // [bx * by][t_r + 1] FP64 prefix sums of each column
+    const void *hi = nullptr, *lo = nullptr; // [bx * by][col_len] half pairs of each column scaled by 2^exps[column]
+    const int32_t *exps = nullptr;           // [bx * by]
+    // prefix sums added over the pixels that reach a column, per offset within a pixel (or null)
+    const double *cls = nullptr;             // [n_sub * n_sub][t_r + 1]
 };
 
 // Device buffers of the summed (sum-then-convolve) induction: per event an absolute grid of sub-pixel columns
@@ -54,11 +58,13 @@ struct Table {
 // (no dependent loads): the piece's first tick and length, its summed charge at S + 8 * cell8 (at
 // Sm + 8 * (cell8 - nS8) for a merged record, cell8 >= nS8), and the folded table column that the pixel sees it
 // through.
+// The upper bits of `bin` hold the exponent (biased, as FP32 stores it) of a bound of the record's charge values.
 struct alignas(16) PieceRef {
     int32_t a0, na;
     uint32_t cell8;
     int32_t bin;
 };
+constexpr int32_t kBinBits = 16, kBinMask = (1 << kBinBits) - 1;   // at most 256 x 256 table columns
 
 // The fields of a segment that the column passes read for every (segment, column) entry, 32 bytes (the full record is
 // 176): a spill's array stays in the last-level cache.
@@ -95,9 +101,9 @@ struct SumWork {
     bool piece_lists = true;                 // write `piece` and `list` (read only by the lane-exchange kernel and the
                                              // per-pair kernels over the pieces)
 };
-// The summed induction kernel a tuning choice runs: the 256-tick LDS-staged one (automatic), the 512-tick register
+// The summed induction kernel a tuning choice runs: the matrix-core one (automatic), the 512-tick register
 // one (8 ticks per thread), or the per-pair kernels over the pieces; and the interval alignment each one wants.
-bool summed_tile256(int32_t rt, bool shift);
+bool summed_matrix(int32_t rt, bool shift);
 int32_t summed_align_res(const DevParams &P, int32_t rt, bool shift);
 constexpr int32_t kPieceTicks = kPieceMax;   // ticks per column piece (a multiple of kAC, <= kNaMax)
 static_assert(kPieceTicks % kAC == 0 && kPieceTicks <= kNaMax, "piece length");
@@ -114,6 +120,11 @@ const int32_t *launch_summed_order(const Work &w, const SumWork &sw, int64_t n_s
                                    hipStream_t st);
 void launch_induce_summed(const DevParams &P, const Work &w, const SumWork &sw, const Table &T, float *wave,
                           int64_t n_slots, int32_t rt, bool shift, const int32_t *order, hipStream_t st);
+
+void launch_table_halves(const float *Rpad, int32_t n_col, int32_t col_len, void *hi, void *lo, int32_t *exps,
+                         hipStream_t st);
+
+void launch_clip_classes(const DevParams &P, const double *prefix, double *cls, hipStream_t st);
 
 int64_t scan_tmp_needed(int64_t n);
 void scan_exclusive_i64(int64_t *data, int64_t n, int64_t *total_dst, void *tmp, hipStream_t st);
@@ -150,7 +161,7 @@ void launch_stage_quench_drift(const DevParams &P, const SegArrays &S, int64_t n
                                hipStream_t st);
 void launch_work_stats(const DevParams &P, const SegInfo *si, int64_t n_seg, unsigned long long *acc, hipStream_t st);
 void launch_work_stats_summed(const DevParams &P, int64_t n_slots, const int64_t *list_off, const PieceRef *rec,
-                              const float *S, const int64_t *mlist_off, const PieceRef *mrec, bool tile256,
+                              const float *S, const int64_t *mlist_off, const PieceRef *mrec, bool matrix,
                               unsigned long long *acc, hipStream_t st);
 void launch_philox(const uint32_t *ctr, uint32_t k0, uint32_t k1, uint32_t *out, int64_t n, hipStream_t st);
 

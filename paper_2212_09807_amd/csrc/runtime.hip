@@ -66,6 +66,8 @@ struct lts_context {
     DevParams P{};
     bool has_table = false;
     DevBuf Rpad, prefix;
+    DevBuf Rhalf, Rexp;              // the table's half pairs (high plane, then low) and their column scales
+    DevBuf Rclass;                   // the clip classes
     std::vector<float> table_host;   // kept to build server lanes
     int32_t t_r = 0, b_x = 0, b_y = 0;
     // scratch pool
@@ -244,8 +246,8 @@ constexpr lts_status kNotAdmitted = LTS_ERR_NOT_READY;
 std::vector<DevBuf *> pool_buffers(lts_context *c) {
     return {&c->ev_cnt, &c->mask, &c->col_seg_off, &c->col_cursor, &c->col_seg, &c->col_tmp, &c->piece_off,
             &c->s_off, &c->piece, &c->pdesc, &c->S, &c->list_off, &c->list, &c->rec, &c->mlist_off, &c->m_off,
-            &c->mrec, &c->Sm, &c->segc, &c->part, &c->Rpad, &c->prefix, &c->si, &c->cell_off, &c->pix_cnt, &c->cursor,
-            &c->pix_slot, &c->slot_gp, &c->slot_off, &c->pairs_u, &c->pairs, &c->cells, &c->pk_tick, &c->pk_adc,
+            &c->mrec, &c->Sm, &c->segc, &c->part, &c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Rclass,
+            &c->si, &c->cell_off, &c->pix_cnt, &c->cursor, &c->pix_slot, &c->slot_gp, &c->slot_off, &c->pairs_u, &c->pairs, &c->cells, &c->pk_tick, &c->pk_adc,
             &c->pk_flag, &c->pk_off, &c->hdr, &c->scan_tmp, &c->ev_off, &c->ev_ids, &c->report_tmp, &c->counts_tmp,
             &c->red_head, &c->red_start, &c->order};
 }
@@ -254,8 +256,9 @@ std::vector<DevBuf *> pool_buffers(lts_context *c) {
 // persist across calls); every buffer is grown again to the exact size the next call needs.  The caller makes sure
 // no queued work still uses them.
 void release_scratch(lts_context *c) {
+    const DevBuf *kept[] = {&c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Rclass, &c->mask};
     for (DevBuf *b : pool_buffers(c))
-        if (b != &c->Rpad && b != &c->prefix && b != &c->mask) free_buf(*b);
+        if (std::find(std::begin(kept), std::end(kept), b) == std::end(kept)) free_buf(*b);
 }
 
 // One buffer and the bytes a call needs in it.
@@ -379,6 +382,17 @@ lts_status check_segments(lts_context *c, const lts_segments *s) {
 
 SegArrays seg_arrays(const lts_segments *s) {
     return SegArrays{s->x0, s->y0, s->z0, s->t0, s->x1, s->y1, s->z1, s->t1, s->energy, s->dedx};
+}
+
+// Values of one half-pair plane: the columns, and what a wavefront's two loads of a window could reach past the last
+// one's end.
+size_t half_plane(int32_t b_x, int32_t b_y, int32_t col_len) { return (size_t)b_x * b_y * col_len + 2048; }
+
+Table table_of(lts_context *c) {
+    const size_t plane = half_plane(c->b_x, c->b_y, c->P.col_len);
+    Table T{as<float>(c->Rpad), as<double>(c->prefix), c->Rhalf.p, as<uint16_t>(c->Rhalf) + plane, as<int32_t>(c->Rexp)};
+    T.cls = as<double>(c->Rclass);
+    return T;
 }
 
 // Sizing half of the pipeline: quench / drift / rasterisation counts and scans; synchronises the stream and
@@ -563,7 +577,7 @@ lts_status run_summed(lts_context *c, const Work &w, const DevHeader &h, int64_t
     sw.mrec = as<PieceRef>(c->mrec);
     sw.Sm = as<float>(c->Sm);
     launch_sum_merge(sw, n_slots, true, st);
-    Table T{as<float>(c->Rpad), as<double>(c->prefix)};
+    Table T = table_of(c);
     const int32_t *order = launch_summed_order(w, sw, n_slots, c->ticks_per_thread, c->lane_exchange != 0, st);
     StageTimer tk(c, st, LTS_STAGE_INDUCE_KERNEL);
     launch_induce_summed(P, w, sw, T, wave, n_slots, c->ticks_per_thread, c->lane_exchange != 0, order, st);
@@ -707,7 +721,7 @@ lts_status run_pipeline(lts_context *c, int32_t n_ev, const uint64_t *event_ids,
     w.pk_off = as<int64_t>(c->pk_off);
     w.scan_tmp = c->scan_tmp.p;
     const DevParams &P = c->P;
-    Table T{as<float>(c->Rpad), as<double>(c->prefix)};
+    Table T = table_of(c);
     // The sequence from here to the packets has no host synchronisation in the per-pair and atomic modes, so it can
     // be captured and replayed as one HIP graph (zero fills are kernels, not memset nodes).
     const bool graph = c->use_graph && c->reduce_mode != LTS_REDUCE_SUMMED;
@@ -1035,10 +1049,30 @@ lts_status lts_set_response(lts_context *c, const float *R, int32_t t_r, int32_t
         }
     HIP_TRY(c, hipSetDevice(c->device));
     lts_status r;
+    c->has_table = false;                               // until every part of the new one is in place
     if ((r = ensure(c, c->Rpad, sizeof(float) * pad.size()))) return r;
     if ((r = ensure(c, c->prefix, sizeof(double) * pre.size()))) return r;
     HIP_TRY(c, hipMemcpy(c->Rpad.p, pad.data(), sizeof(float) * pad.size(), hipMemcpyHostToDevice));
     HIP_TRY(c, hipMemcpy(c->prefix.p, pre.data(), sizeof(double) * pre.size(), hipMemcpyHostToDevice));
+    const size_t plane = half_plane(b_x, b_y, col_len);
+    if ((r = ensure(c, c->Rhalf, 2 * sizeof(uint16_t) * plane))) return r;
+    if ((r = ensure(c, c->Rexp, sizeof(int32_t) * ncol))) return r;
+    launch_table_halves(as<float>(c->Rpad), (int32_t)ncol, col_len, c->Rhalf.p, as<uint16_t>(c->Rhalf) + plane,
+                        as<int32_t>(c->Rexp), nullptr);
+    DevParams tab = c->P;                               // (the context's own are set when nothing can fail any more)
+    tab.t_r = t_r;
+    tab.bx = b_x;
+    tab.by = b_y;
+    // clip classes up to 64 MB; finer sub-pixel grids walk the pixels of every column
+    const size_t cls = (size_t)tab.nsub * tab.nsub * (size_t)(t_r + 1) * sizeof(double);
+    if (cls <= (size_t)64 << 20) {
+        if ((r = ensure(c, c->Rclass, cls))) return r;
+        launch_clip_classes(tab, as<double>(c->prefix), as<double>(c->Rclass), nullptr);
+    } else {
+        free_buf(c->Rclass);
+    }
+    HIP_TRY(c, hipGetLastError());
+    HIP_TRY(c, hipStreamSynchronize(nullptr));
     c->table_host.assign(R, R + (size_t)t_r * b_x * b_y);
     c->t_r = t_r;
     c->b_x = b_x;
@@ -1278,7 +1312,7 @@ static lts_status stage_pairs(lts_context *c, uint64_t event_id, const lts_segme
         return fail(c, LTS_ERR_CAPACITY, "cap_pairs " + std::to_string(cap_pairs) + " < " + std::to_string(h.n_pairs));
     if (pair_segment || pair_pixel) launch_pair_list(c->P, w, h.n_slots, pair_segment, pair_pixel, st);
     if (pair_current) {
-        Table T{as<float>(c->Rpad), as<double>(c->prefix)};
+        Table T = table_of(c);
         launch_induce_pairs(c->P, w, T, h.n_slots, pair_current, st);
     }
     HIP_TRY(c, hipGetLastError());
@@ -1354,7 +1388,7 @@ lts_status lts_work_stats(lts_context *c, double out[6]) {
     if (c->last_mode == LTS_REDUCE_SUMMED) {
         launch_work_stats_summed(c->P, c->last_n_slots, as<int64_t>(c->list_off), as<PieceRef>(c->rec),
                                  as<float>(c->S), as<int64_t>(c->mlist_off), as<PieceRef>(c->mrec),
-                                 summed_tile256(c->last_rt, c->last_shift), as<unsigned long long>(c->counts_tmp),
+                                 summed_matrix(c->last_rt, c->last_shift), as<unsigned long long>(c->counts_tmp),
                                  nullptr);
         HIP_TRY(c, hipGetLastError());
         unsigned long long hs[4];

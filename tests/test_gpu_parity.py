@@ -958,3 +958,37 @@ def test_matrix_core_module_event_agrees_with_vector_path(lt, torch):
     e = per_pixel_errors(b["current"].astype(np.float64), a["current"].astype(np.float64))
     print(f"module event: matrix vs vector max e_p {e.max():.2e}, p99 {np.percentile(e, 99):.2e}")
     assert e.max() <= TOL_WAVE
+
+
+# ----------------------------------------------------------------------------------------------- tile edges
+
+def _edge_workload(n_ticks, t_r, b_x, b_y, n_sub):
+    """Charge at every residue of the start tick mod 8, single-tick to ~250-tick intervals (a drift-parallel track whose
+    columns hold several pieces and parts), charge values over four decades, and windows cut at both ends."""
+    w = W.config(1)
+    w.readout = dataclasses.replace(w.readout, n_x=6, n_y=5, n_ticks=n_ticks, n_sub=n_sub)
+    w.table = W.TableShape(t_r, b_x, b_y)
+    parts = []
+    n = 250
+    z = np.linspace(0.4, 4.4, n + 1)
+    r = np.stack([np.full(n + 1, 1.31), np.full(n + 1, 1.12), z], 1)
+    parts.append(W.make_segments(r[:-1], r[1:], np.full(n, 2.1 * 0.016)))
+    for k in range(9):
+        p = np.array([0.3 + 0.27 * k, 0.4 + 0.19 * k, 0.02 + 0.3 * k])
+        parts.append(W.make_segments(p, p + [0.01, 0.004, 0.002], 10.0 ** (-3 + 0.5 * k), t0=0.1 * k, t1=0.1 * k))
+    w.events, w.event_ids = [W.Segments.concat(parts)], [77]
+    return w
+
+
+# A tenth of the parity bar: half-pair products are within 3 x 2^-22 (7e-7) of their values, the cells within ~2e-6.
+TOL_EDGE = 1e-5
+
+
+@pytest.mark.parametrize("n_ticks,t_r,b_x,b_y,n_sub", [(1, 1, 1, 1, 2), (255, 37, 5, 3, 10), (256, 256, 9, 8, 4),
+                                                       (769, 200, 17, 10, 10), (1537, 1001, 20, 31, 10)])
+def test_summed_matrix_tile_edges(lt, orc, torch, n_ticks, t_r, b_x, b_y, n_sub):
+    """Summed induction on the matrix cores where its tiles, units, steps and parts end (ticks and table lengths around
+    256 and 768, intervals around 32, 72 and 248, reaches that are no multiple of anything)."""
+    h, r, e, _ = check_event(lt, orc, _edge_workload(n_ticks, t_r, b_x, b_y, n_sub), mode=2)
+    print(f"summed edges {n_ticks}/{t_r}/{b_x}x{b_y}/{n_sub}: pixels {len(r['pixels'])} max e_p {e.max():.2e}")
+    assert e.max() <= TOL_EDGE
