@@ -151,8 +151,11 @@ typedef struct lts_context lts_context;
 
 /* Reduction variant for the per-pixel sum over segments (Sec. 3.4):
  *   LTS_REDUCE_SORTED: pairs sorted pixel-major, one workgroup per pixel, Kahan-compensated FP32 accumulation in a
- *                      fixed segment order (deterministic, batch-invariant; default);
- *   LTS_REDUCE_ATOMIC: segment-major, per-pair currents added with FP32 atomics (order-dependent rounding);
+ *                      fixed segment order (deterministic, batch-invariant; default).  With the automatic tick tile
+ *                      a pixel's segments are taken in groups (up to 16 in ascending order, spanning up to 128 ticks)
+ *                      whose charge is summed per table column before the product with the table;
+ *   LTS_REDUCE_ATOMIC: segment-major, currents added with FP32 atomics (order-dependent rounding); with the automatic
+ *                      tick tile in groups of up to 8 consecutive segments;
  *   LTS_REDUCE_SUMMED: sum-then-convolve: eq. (current) is linear in the charge, so each sub-pixel column's charge
  *                      is first summed over all segments (fixed order, Kahan) and each pixel then convolves the summed
  *                      columns in its reach once; the same result without per-pair currents, with fewer
@@ -187,17 +190,19 @@ lts_status lts_set_channel_mask(lts_context *ctx, const uint8_t *mask, int64_t n
  * waveforms are added in a fixed order.  1 (default) = one workgroup per pixel. */
 lts_status lts_set_induce_slices(lts_context *ctx, int32_t slices);
 
-/* Induction tick tile: each of the 256 threads of a workgroup computes `rt` consecutive ticks of a pair's window
- * (1, 2, 4 or 8; 0 = the smallest that covers the table length plus a typical charge extent, and for 8 ticks the
- * loop that loads the next cell-tick block's window while computing the current one; an explicit 8 selects the
- * loop without that prefetch).  All choices give the same sums in the same order.  In LTS_REDUCE_SUMMED: 0 = one
- * wavefront per (pixel, 768 ticks) on the FP16 matrix cores, every FP32 factor split into a pair of halves (default;
- * error against FP64 no larger than the FP32 forms'), 8 = one wavefront per
- * (pixel, 512-tick tile) with register-resident table windows, 1, 2, 4 = the per-pair workgroup kernel over the
- * summed pieces; these agree to FP32 summation order. */
+/* Induction kernel.  0 (default): the FP16 matrix cores, every FP32 factor split into a pair of halves (error against
+ * FP64 no larger than the FP32 forms'): in the per-pair modes a workgroup per (pixel, group of segments), in
+ * LTS_REDUCE_SUMMED one wavefront per (pixel, 768 ticks).  1, 2, 4 or 8: the FP32 vector kernels.  Per pair, each of the
+ * 256 threads of a workgroup then computes that many consecutive ticks of a pair's window, with the same sums in the
+ * same order for each of the four; in LTS_REDUCE_SUMMED 8 = one wavefront per (pixel, 512-tick tile) with
+ * register-resident table windows, 1, 2, 4 = the per-pair workgroup kernel over the summed pieces.  All choices agree
+ * to FP32 summation order.  A pixel one of whose decisions (threshold, LSB edge, the margins that flag them) lies within
+ * twice the flags' margin gets its current in the vector kernels' order also with 0, so packets do not depend on the
+ * choice between 0 and the vector kernels of the per-pair modes.  With more than one induce slice, 0 = the smallest vector tile that covers the table length
+ * plus a typical charge extent. */
 lts_status lts_set_ticks_per_thread(lts_context *ctx, int32_t rt);
 
-/* Per-pair induction with 8-tick tiles: 1 = lanes share each table window by shifting it one lane per cell-tick
+/* Per-pair induction with explicit 8-tick tiles (lts_set_ticks_per_thread(8)): 1 = lanes share each table window by shifting it one lane per cell-tick
  * block (one coalesced load per column and lane); 0 (default, faster on gfx950) = every lane loads its own 15-value
  * window per block.
  * Both give the same sums in the same order.  A tuning option (Sec. 3.3.2 sets no kernel design). */

@@ -83,7 +83,9 @@ struct DevHeader {
     int64_t n_colseg;                       // sum over segments of nu * nv (bound for the summed induction)
     uint32_t work[4];                       // dynamic work counters of persistent kernels
     int32_t status;                         // ST_* bits
-    int32_t _pad[3];
+    uint32_t n_settle;                      // pixels with a decision too close to settle on the matrix cores' currents
+    uint32_t settle_work;                   // their dynamic work counter
+    int32_t _pad;
 };
 
 // ------------------------------------------------------------------------------------------------ helpers

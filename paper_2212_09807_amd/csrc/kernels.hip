@@ -12,12 +12,15 @@
 //   k_induce_*       Sec. 3.3.2 eq. (current): per (segment, pixel) pair and tick, the cells in the pixel's table
 //                    reach convolved in time with the field-response column of their mirror-folded bin; summed
 //                    over the pixel's segments (Sec. 3.4) either in a fixed order with Kahan compensation
-//                    (sorted variant) or with FP32 atomics (atomic variant).
+//                    (sorted variant) or with FP32 atomics (atomic variant).  k_induce_z*: as matrix products over
+//                    groups of a pixel's segments (default); k_induce_sorted / k_induce_atomic: on the vector units.
 //   k_sum_*          the same sum by linearity as sum-then-convolve: segments' charges summed per sub-pixel
 //                    column (column lists, sort, intervals, summed charges), per-pixel records by folded table
-//                    column, the mirror merge, then k_induce_summed4 / k_induce_summed over the records.
+//                    column, the mirror merge, then k_induce_summed_mma (default) / k_induce_summed over the records.
 //   k_electronics    Sec. 3.4: integrate, threshold (with discriminator noise), hold, digitise, reset, with
 //                    Philox4x32-10 noise; also the FP64 per-event sum of the currents.
+//   k_settle         the currents of pixels with a decision on the edge once more, in the vector kernels' order, and
+//                    k_electronics over them (after matrix-core sums only).
 //   k_compact        packets of all pixels into the caller's arrays.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -788,65 +791,6 @@ __device__ __forceinline__ void pair_block(const DevParams &P, const float *__re
     }
 }
 
-// pair_block<8> with the loads of later cell-tick blocks (each a 15-value table window and 8 cell values) issued
-// before the products of the current one, across column boundaries: the pair's blocks are walked as one sequence
-// (column-major, all columns of a pair have the same number of blocks) with three register buffers in turn.
-struct BlockCursor {
-    int32_t u, v, j;
-};
-
-__device__ __forceinline__ void pair_block_pf(const DevParams &P, const float *__restrict__ cc0, int32_t nv, int32_t nap,
-                                              int32_t u0, int32_t v0, int32_t a0, const float *__restrict__ Rpad,
-                                              int32_t ulo, int32_t uhi, int32_t vlo, int32_t vhi, int32_t uc,
-                                              int32_t vc, int32_t nb0, int32_t lane_off, float (&acc)[8]) {
-    // table offset of the window's first value for the workgroup's first thread (uniform) and this thread's offset
-    // from it (8 ticks per thread): every load is a uniform base plus a fixed 32-bit lane offset
-    const int32_t K0w = nb0 - a0 + P.t_r - 1 + kPad - (kAC - 1);
-    const int32_t nblk = nap / kAC;
-    const int32_t total = (uhi - ulo + 1) * (vhi - vlo + 1) * nblk;
-    BlockCursor f{ulo, vlo, 0};                         // next block to fetch
-    int32_t nf = 0;                                     // blocks fetched so far
-    // Loads are issued unconditionally (past the last block the last block is fetched again), so the number of
-    // loads in flight is the same on every path and the waits only cover the block about to be used.
-    auto fetch = [&](float (&w)[8 + kAC - 1], float (&cv)[kAC]) {
-        const int64_t cb = (int64_t)(fold(f.u - uc) * P.by + fold(f.v - vc)) * P.col_len + K0w - kAC * f.j;
-        gfloat_ptr base = (gfloat_ptr)(Rpad + cb);
-        cfloat_ptr cc = (cfloat_ptr)(cc0 + ((int64_t)(f.u - u0) * nv + (f.v - v0)) * nap + kAC * f.j);
-#pragma unroll
-        for (int m = 0; m < 8 + kAC - 1; ++m) w[m] = base[lane_off + m];
-#pragma unroll
-        for (int q = 0; q < kAC; ++q) cv[q] = cc[q];
-        if (++nf < total && ++f.j == nblk) {
-            f.j = 0;
-            if (++f.v > vhi) { f.v = vlo; ++f.u; }
-        }
-    };
-    auto block = [&](const float (&w)[8 + kAC - 1], const float (&cv)[kAC]) {
-#pragma unroll
-        for (int q = 0; q < kAC; ++q)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) acc[r] = fmaf(cv[q], w[r - q + kAC - 1], acc[r]);
-    };
-    // three register buffers in turn: the loads of block b + 2 are issued before the products of block b, so two
-    // blocks of products cover each load's latency
-    float wa[8 + kAC - 1], ca[kAC], wb[8 + kAC - 1], cb[kAC], wc[8 + kAC - 1], cx[kAC];
-    fetch(wa, ca);
-    fetch(wb, cb);
-    for (int32_t b = 0; b < total; b += 3) {
-        fetch(wc, cx);
-        __builtin_amdgcn_sched_barrier(0);
-        block(wa, ca);
-        if (b + 1 >= total) break;
-        fetch(wa, ca);
-        __builtin_amdgcn_sched_barrier(0);
-        block(wb, cb);
-        if (b + 2 >= total) break;
-        fetch(wb, cb);
-        __builtin_amdgcn_sched_barrier(0);
-        block(wc, cx);
-    }
-}
-
 // Value of lane - 1 of the wavefront (DPP wave_shr:1); lane 0 has no source lane and keeps `lane0`.
 __device__ __forceinline__ float shift_up_or(float v, float lane0) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, lane0),
@@ -1055,7 +999,7 @@ __device__ __forceinline__ double block_sum_double(double v, double *red) {
 
 // Sorted variant: one workgroup per active pixel (dynamic work queue); the pixel's segments in ascending id
 // order; per-pair FP32 sums in registers added into a Kahan-compensated FP32 accumulator in LDS.
-template <int RT, bool SHIFT, bool PREFETCH = false>
+template <int RT, bool SHIFT>
 __global__ __launch_bounds__(kWG) void k_induce_sorted(DevParams P, const SegInfo *__restrict__ si,
                                                        const float *__restrict__ cells, const float *__restrict__ Rpad,
                                                        const double *__restrict__ prefix,
@@ -1103,11 +1047,7 @@ __global__ __launch_bounds__(kWG) void k_induce_sorted(DevParams P, const SegInf
                 for (int r = 0; r < RT; ++r) acc[r] = 0.0f;
                 if constexpr (RT == 8 && SHIFT)
                     pair_block_ring(P, cc0, nv, nap, u0, v0, a0, Rpad, ulo, uhi, vlo, vhi, uc, vc, nb, nb <= hi, acc);
-                else if constexpr (RT == 8 && PREFETCH) {
-                    if (nb <= hi)
-                        pair_block_pf(P, cc0, nv, nap, u0, v0, a0, Rpad, ulo, uhi, vlo, vhi, uc, vc, nb0, tid * RT,
-                                      acc);
-                } else if (nb <= hi)
+                else if (nb <= hi)
                     pair_block<RT>(P, cc0, nv, nap, u0, v0, a0, Rpad, ulo, uhi, vlo, vhi, uc, vc, nb, acc);
 #pragma unroll
                 for (int r = 0; r < RT; ++r) {
@@ -1568,7 +1508,7 @@ void launch_induce_slices(const DevParams &P, const Work &w, const Table &T, flo
     }
 }
 
-template <int RT, bool SHIFT, bool PREFETCH = false>
+template <int RT, bool SHIFT>
 static void induce_rt(const DevParams &P, const Work &w, const Table &T, float *wave, int mode, int64_t n_slots,
                       hipStream_t st) {
     const int64_t cap = 2048;
@@ -1576,7 +1516,7 @@ static void induce_rt(const DevParams &P, const Work &w, const Table &T, float *
         int64_t g = n_slots < 1 ? 1 : (n_slots > cap ? cap : n_slots);
         size_t lds = (size_t)2 * P.nticks * sizeof(float);
         if (w.order && n_slots > 0) launch_slot_order(P, w, n_slots, st);
-        k_induce_sorted<RT, SHIFT, PREFETCH><<<(unsigned)g, kWG, lds, st>>>(P, w.si, w.cells, T.Rpad, T.prefix, w.slot_off, w.pairs,
+        k_induce_sorted<RT, SHIFT><<<(unsigned)g, kWG, lds, st>>>(P, w.si, w.cells, T.Rpad, T.prefix, w.slot_off, w.pairs,
                                                           w.slot_gp, n_slots > 0 ? w.order : nullptr, wave, w.hdr,
                                                           w.report);
     } else {
@@ -1603,7 +1543,6 @@ void launch_induce(const DevParams &P, const Work &w, const Table &T, float *wav
         case 4: induce_rt<4, false>(P, w, T, wave, mode, n_slots, st); break;
         default:
             if (shift) induce_rt<8, true>(P, w, T, wave, mode, n_slots, st);
-            else if (rt == 0) induce_rt<8, false, true>(P, w, T, wave, mode, n_slots, st);   // auto: prefetched
             else induce_rt<8, false>(P, w, T, wave, mode, n_slots, st);
             break;
     }
@@ -1629,65 +1568,11 @@ __global__ __launch_bounds__(kWG) void k_pair_list(DevParams P, const int64_t *_
     }
 }
 
-// Row q of `out` (n_ticks floats) receives pair q's current I_sp[n]: workgroup per active pixel, its pairs in
-// stored order; ticks outside the pair's reach in time are written as zero.
-template <int RT>
-__global__ __launch_bounds__(kWG) void k_induce_pairs(DevParams P, const SegInfo *__restrict__ si,
-                                                      const float *__restrict__ cells, const float *__restrict__ Rpad,
-                                                      const int64_t *__restrict__ slot_off,
-                                                      const int32_t *__restrict__ pairs,
-                                                      const int32_t *__restrict__ slot_gp, const DevHeader *H,
-                                                      float *__restrict__ out) {
-    const int NT = P.nticks;
-    const int tid = threadIdx.x;
-    for (int64_t slot = blockIdx.x; slot < H->n_slots; slot += gridDim.x) {
-        const int32_t gp = slot_gp[slot];
-        const int32_t p = gp - (gp / P.npx) * P.npx;
-        const int32_t ix = p % P.nx, iy = p / P.nx;
-        const int32_t uc = ix * P.nsub + P.nsub / 2, vc = iy * P.nsub + P.nsub / 2;
-        for (int64_t q = slot_off[slot]; q < slot_off[slot + 1]; ++q) {
-            const SegInfo &g = si[__builtin_amdgcn_readfirstlane(pairs[q])];
-            const int32_t u0 = g.u0, v0 = g.v0, a0 = g.a0, nv = g.nv, nap = g.na_pad, na = g.na;
-            const int32_t ulo = max(u0, uc - P.bx), uhi = min(u0 + g.nu - 1, uc + P.bx - 1);
-            const int32_t vlo = max(v0, vc - P.by), vhi = min(v0 + nv - 1, vc + P.by - 1);
-            const bool any = ulo <= uhi && vlo <= vhi;
-            const int32_t lo = any ? max(a0 - (P.t_r - 1), 0) : NT, hi = any ? min(a0 + na - 1, NT - 1) : -1;
-            float *row = out + q * NT;
-            for (int n = tid; n < NT; n += kWG)
-                if (n < lo || n > hi) row[n] = 0.0f;
-            const float *cc0 = cells + g.cell_off;
-            for (int32_t nb0 = lo; nb0 <= hi; nb0 += kWG * RT) {
-                const int32_t nb = nb0 + tid * RT;
-                if (nb > hi) continue;
-                float acc[RT];
-#pragma unroll
-                for (int r = 0; r < RT; ++r) acc[r] = 0.0f;
-                pair_block<RT>(P, cc0, nv, nap, u0, v0, a0, Rpad, ulo, uhi, vlo, vhi, uc, vc, nb, acc);
-#pragma unroll
-                for (int r = 0; r < RT; ++r)
-                    if (nb + r <= hi) row[nb + r] = acc[r];
-            }
-        }
-    }
-}
-
 void launch_pair_list(const DevParams &P, const Work &w, int64_t n_slots, int32_t *pair_seg, int32_t *pair_pix,
                       hipStream_t st) {
     if (n_slots <= 0) return;
     const unsigned g = (unsigned)std::min<int64_t>(n_slots, 65536);
     k_pair_list<<<g, kWG, 0, st>>>(P, w.slot_off, w.pairs, w.slot_gp, w.hdr, pair_seg, pair_pix);
-}
-
-void launch_induce_pairs(const DevParams &P, const Work &w, const Table &T, int64_t n_slots, float *out,
-                         hipStream_t st) {
-    if (n_slots <= 0) return;
-    const unsigned g = (unsigned)std::min<int64_t>(n_slots, 65536);
-    switch (pick_rt(P, 0)) {
-        case 1: k_induce_pairs<1><<<g, kWG, 0, st>>>(P, w.si, w.cells, T.Rpad, w.slot_off, w.pairs, w.slot_gp, w.hdr, out); break;
-        case 2: k_induce_pairs<2><<<g, kWG, 0, st>>>(P, w.si, w.cells, T.Rpad, w.slot_off, w.pairs, w.slot_gp, w.hdr, out); break;
-        case 4: k_induce_pairs<4><<<g, kWG, 0, st>>>(P, w.si, w.cells, T.Rpad, w.slot_off, w.pairs, w.slot_gp, w.hdr, out); break;
-        default: k_induce_pairs<8><<<g, kWG, 0, st>>>(P, w.si, w.cells, T.Rpad, w.slot_off, w.pairs, w.slot_gp, w.hdr, out); break;
-    }
 }
 
 // Per-pixel sum of pair waveforms grouped by pixel: head[q] = 1 where a run of equal pixel ids starts (q < n),
@@ -2847,6 +2732,524 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
     }
 }
 
+// ------------------------------------------------------------------------------------------ pixel products
+// Per-pixel induction of a group of segments on the FP16 matrix cores.  The group's charge is summed per table column
+// (the columns' mirror images folded onto them) and tick: C[bin][a].  With the bins as the contraction,
+// Z[a][tau] = sum_bin C[bin][a] R[bin][tau] is a matrix product with no padding but the rounding of ticks to 16, of
+// table ticks to 16 and of the bins to whole octets (8 consecutive j of one i), and the current is the sum along Z's
+// anti-diagonals, I[n] = sum_a Z[a][n - a + T_R - 1].  Both factors are half pairs as above; the table octets are laid
+// out so that 16 table ticks of an octet are 256 consecutive bytes (a 16x16x32 operand of four octets is four such
+// runs).  Anti-diagonals: lane (tau, g) holds rows a = 4g .. 4g + 3 of a tile, so row a moves up by a lanes within its 16
+// (DPP row shifts; what leaves the 16 belongs to the next tile), and the four groups are added by lane swaps once per
+// 16 output ticks.
+// A workgroup stages 32 ticks x 32 octets of C at a time, and each wavefront owns a range of output ticks (it also
+// computes the two table tiles below its range), so no sum is shared between wavefronts: the result depends only on
+// the segments' order.
+//   What bounds it: the table octets of every 32 x 32 stage come through L1 from L2 (all loads of a tile pair are issued
+// before its products; without that 14.6 instead of 9.1 ms), then the products.  Staging costs one load per charge value
+// and image, so a group saves work only where its segments share columns: 16 segments and 128 ticks (64 and 256 ticks
+// measured the same).  Two workgroups of four wavefronts a CU: three spill (1.34 -> 1.21 ms on the batch of 64 tracks,
+// but 9.1 -> 9.8 on the event).  Atomic units of 8 segments (4: 4.7 ms, 8: 3.06, 16: 3.3).
+//   Measured against the vector kernels (45 x 45 x 1950 table unless said): sorted, 3000 segments 91.3 -> 9.1 ms; atomic,
+// 800 segments 50 -> 3.06 ms; one track of 512 segments on 20 x 31 x 1001 1.106 -> 0.122 ms, 64 such tracks 9.2 -> 1.34.
+// Error against 64 bits (relative to the largest current): 1.4e-6 -> 1.3e-7, 2.2e-6 -> 1.7e-7 atomic.
+constexpr int32_t kZgSegs = 16;                         // segments of a group
+constexpr int32_t kZgSpan = 128;                        // ticks of a group's charge (unless one segment has more)
+constexpr int32_t kZgTicks = 32;                        // ticks and octets staged at a time
+constexpr int32_t kZgOct = 32;
+
+struct ZTable {                                         // half planes of the table by octets of bins
+    const u32x4 *hi, *lo;                               // [bx * njo][trq]: 8 halves
+    const int32_t *exps;                                // [bx * by] scale of a bin
+    const int32_t *emin;                                // [bx * njo] smallest scale at or beyond an octet in both indices
+    int32_t njo, trq;
+};
+
+struct ZSeg {                                           // a segment of the group, as the staging reads it
+    int64_t cells;
+    int32_t u0, nu, v0, nv, a0, na, nap, _pad;
+};
+
+// One mirror image of a segment's charge box in the pixel's folded bins: the charge of bin (i, j), i0 <= i <= i1 and
+// j0 <= j <= j1, at tick a of the box is at byte base + i si + j sj + 4 a of the segment's cells (`bytes` of them).
+struct ZJob {
+    int64_t cells;
+    int32_t bytes, base, si, sj, i0, i1, j0, j1, a0, na;
+};
+
+struct alignas(16) ZStage {
+    u32x4 c[2][2][kZgOct][16];                          // [plane][16 ticks][octet][tick]: 8 halves
+    ZSeg seg[kZgSegs];
+    ZJob job[4 * kZgSegs];
+    uint32_t at[kZgOct];                                // byte offset of an octet's table column
+};
+
+__global__ __launch_bounds__(kWG) void k_table_octets(const float *__restrict__ Rpad, int32_t col_len, int32_t t_r,
+                                                      int32_t by, int32_t njo, int32_t trq,
+                                                      const int32_t *__restrict__ exps, u32x4 *__restrict__ hi,
+                                                      u32x4 *__restrict__ lo) {
+    const int32_t o = blockIdx.x, i = o / njo, j0 = (o - i * njo) * 8;
+    for (int32_t t = threadIdx.x; t < trq; t += kWG) {
+        half8 h, l;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            float x = 0.0f;
+            if (j0 + q < by && t < t_r) {
+                const int32_t b = i * by + j0 + q;
+                x = ldexpf(Rpad[(int64_t)b * col_len + kPad + t], exps[b]);
+            }
+            h[q] = (_Float16)x;
+            l[q] = (_Float16)(x - (float)h[q]);
+        }
+        hi[(int64_t)o * trq + t] = __builtin_bit_cast(u32x4, h);
+        lo[(int64_t)o * trq + t] = __builtin_bit_cast(u32x4, l);
+    }
+}
+
+// emin[i][jo] = min over i' >= i, jo' >= jo of the bins' scales (one workgroup; the table has at most 256 x 32 octets).
+__global__ __launch_bounds__(kWG) void k_table_emin(const int32_t *__restrict__ exps, int32_t bx, int32_t by,
+                                                    int32_t njo, int32_t *emin) {
+    for (int32_t i = threadIdx.x; i < bx; i += kWG) {     // along j
+        int32_t m = INT32_MAX;
+        for (int32_t jo = njo - 1; jo >= 0; --jo) {
+            for (int32_t j = 8 * jo; j < min(8 * jo + 8, by); ++j) m = min(m, exps[i * by + j]);
+            emin[i * njo + jo] = m;
+        }
+    }
+    __syncthreads();
+    for (int32_t jo = threadIdx.x; jo < njo; jo += kWG) { // along i
+        int32_t m = INT32_MAX;
+        for (int32_t i = bx - 1; i >= 0; --i) {
+            m = min(m, emin[i * njo + jo]);
+            emin[i * njo + jo] = m;
+        }
+    }
+}
+
+void launch_table_octets(const float *Rpad, int32_t bx, int32_t by, int32_t t_r, int32_t col_len, int32_t trq,
+                         const int32_t *exps, void *hi, void *lo, int32_t *emin, hipStream_t st) {
+    const int32_t njo = (by + 7) / 8;
+    k_table_octets<<<(unsigned)(bx * njo), kWG, 0, st>>>(Rpad, col_len, t_r, by, njo, trq, exps, (u32x4 *)hi, (u32x4 *)lo);
+    k_table_emin<<<1, kWG, 0, st>>>(exps, bx, by, njo, emin);
+}
+
+template <int R>
+__device__ __forceinline__ float row_up(float x) {       // lane j of a row of 16 takes lane j - R's value, 0 below
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x110 + R, 0xf, 0xf, true));
+}
+template <int R>
+__device__ __forceinline__ float row_down(float x) {     // lane j of a row of 16 takes lane j + R's value, 0 above
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x100 + R, 0xf, 0xf, true));
+}
+// Sum over the four rows of 16 lanes, in every row: two copies of y exchange their halves, then their odd and even rows
+// (a wait of two states between a register's write and a swap of it).
+__device__ __forceinline__ float rows_sum(float y) {
+    float z = y;
+    asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(y), "+v"(z));
+    y += z;
+    z = y;
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(y), "+v"(z));
+    return y + z;
+}
+
+// Z tiles t and t + 1 of the staged octets (KN steps of four octets; steps past the staged ones meet zero charge).
+template <int KN, bool TWO>
+__device__ __forceinline__ void z_tiles(const ZStage &st, __amdgpu_buffer_rsrc_t rh, __amdgpu_buffer_rsrc_t rl,
+                                        uint32_t f0, uint32_t f1, int lj, int lg, floatx4 (&D)[2][2]) {
+    u32x4 h0[KN], l0[KN], h1[KN], l1[KN];
+#pragma unroll
+    for (int k = 0; k < KN; ++k) {                      // all loads first: they come from L2 or beyond
+        const uint32_t at = st.at[4 * k + lg] + 16u * (uint32_t)lj;
+        h0[k] = __builtin_amdgcn_raw_buffer_load_b128(rh, at, f0, 0);
+        l0[k] = __builtin_amdgcn_raw_buffer_load_b128(rl, at, f0, 0);
+        h1[k] = __builtin_amdgcn_raw_buffer_load_b128(rh, at, f1, 0);
+        l1[k] = __builtin_amdgcn_raw_buffer_load_b128(rl, at, f1, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < KN; ++k)
+#pragma unroll
+        for (int b = 0; b < (TWO ? 2 : 1); ++b) {
+            const half8 ah = __builtin_bit_cast(half8, st.c[0][b][4 * k + lg][lj]);
+            const half8 al = __builtin_bit_cast(half8, st.c[1][b][4 * k + lg][lj]);
+            const half8 p0 = __builtin_bit_cast(half8, h0[k]), p1 = __builtin_bit_cast(half8, h1[k]);
+            D[b][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, p0, D[b][0], 0, 0, 0);
+            D[b][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, p1, D[b][1], 0, 0, 0);
+            D[b][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, p0, D[b][0], 0, 0, 0);
+            D[b][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, p1, D[b][1], 0, 0, 0);
+            D[b][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(half8, l0[k]), D[b][0], 0, 0, 0);
+            D[b][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(half8, l1[k]), D[b][1], 0, 0, 0);
+        }
+}
+template <bool TWO>
+__device__ __forceinline__ void z_dispatch(int32_t nk, const ZStage &st, __amdgpu_buffer_rsrc_t rh,
+                                           __amdgpu_buffer_rsrc_t rl, uint32_t f0, uint32_t f1, int lj, int lg,
+                                           floatx4 (&D)[2][2]) {
+    if (nk <= 2) z_tiles<2, TWO>(st, rh, rl, f0, f1, lj, lg, D);
+    else if (nk <= 4) z_tiles<4, TWO>(st, rh, rl, f0, f1, lj, lg, D);
+    else if (nk <= 6) z_tiles<6, TWO>(st, rh, rl, f0, f1, lj, lg, D);
+    else z_tiles<8, TWO>(st, rh, rl, f0, f1, lj, lg, D);
+}
+
+// Adds the current of the group st.seg[0 .. n_seg) on the pixel with centre bins (uc, vc) through emit(n, value), n in
+// [0, n_ticks), called by 32 lanes at a time, never for the same n by two wavefronts between barriers.  `bound`: an upper
+// bound of the group's charge.  All threads of the workgroup call it; it starts and ends with a barrier.
+template <class Emit>
+__device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZStage &st, int32_t n_seg, int32_t A0,
+                                        int32_t A1, float bound, int32_t uc, int32_t vc,
+                                        const float *__restrict__ cells, Emit emit) {
+    const int tid = threadIdx.x, lane = tid & 63, lj = lane & 15, lg = lane >> 4;
+    const int32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t TR = P.t_r, NT = P.nticks, n_tau = Z.trq / 16;
+    const int32_t ebound = __builtin_bit_cast(int32_t, bound) >> 23;
+    const int32_t plane = P.bx * Z.njo * Z.trq * 16;    // bytes (at most 2^30)
+    const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc((void *)Z.hi, (short)0, plane, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc((void *)Z.lo, (short)0, plane, kBufferWord3);
+    __syncthreads();                                    // the group's segments are in place
+    for (int32_t ac = A0; ac <= A1; ac += kZgTicks) {
+        const int32_t n0 = ac - TR + 1;                 // tick of output 0
+        if (n0 >= NT || min(ac + kZgTicks - 1, A1) < 0) continue;
+        // the mirror images with charge in these ticks (lane = image of a segment; every wavefront finds the same, in
+        // the order segment, u side, v side), and the octets they span
+        ZJob jb{0, 0, 0, 0, 0, 0, -1, 0, -1, 0, 0};
+        int32_t alast = -1;
+        if (lane < 4 * n_seg) {
+            const ZSeg g = st.seg[lane >> 2];
+            const int32_t su = lane >> 1 & 1, sv = lane & 1;
+            // bins of the image: u = uc + i (or uc - 1 - i), 0 <= i < bx
+            jb.i0 = max(su ? uc - 1 - (g.u0 + g.nu - 1) : g.u0 - uc, 0);
+            jb.i1 = min(su ? uc - 1 - g.u0 : g.u0 + g.nu - 1 - uc, P.bx - 1);
+            jb.j0 = max(sv ? vc - 1 - (g.v0 + g.nv - 1) : g.v0 - vc, 0);
+            jb.j1 = min(sv ? vc - 1 - g.v0 : g.v0 + g.nv - 1 - vc, P.by - 1);
+            jb.cells = g.cells;
+            jb.bytes = g.nu * g.nv * g.nap * 4;
+            jb.si = (su ? -4 : 4) * g.nv * g.nap;
+            jb.sj = (sv ? -4 : 4) * g.nap;
+            jb.base = (((su ? uc - 1 : uc) - g.u0) * g.nv + ((sv ? vc - 1 : vc) - g.v0)) * g.nap * 4;
+            jb.a0 = g.a0;
+            jb.na = g.na;
+            if (!(g.a0 > ac + kZgTicks - 1 || g.a0 + g.na <= ac)) alast = min(g.a0 + g.na - 1 - ac, kZgTicks - 1);
+        }
+        const bool has = alast >= 0 && jb.i0 <= jb.i1 && jb.j0 <= jb.j1;
+        const uint64_t jobs = __ballot(has);
+        if (!jobs) continue;
+        const int32_t n_job = __builtin_popcountll(jobs);
+        int32_t i0 = has ? jb.i0 : INT32_MAX, i1 = has ? jb.i1 : -1, j0 = has ? jb.j0 : INT32_MAX, j1 = has ? jb.j1 : -1;
+        if (!has) alast = -1;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            i0 = min(i0, __shfl_xor(i0, o));
+            i1 = max(i1, __shfl_xor(i1, o));
+            j0 = min(j0, __shfl_xor(j0, o));
+            j1 = max(j1, __shfl_xor(j1, o));
+            alast = max(alast, __shfl_xor(alast, o));
+        }
+        i0 = __builtin_amdgcn_readfirstlane(i0);
+        i1 = __builtin_amdgcn_readfirstlane(i1);
+        j0 = __builtin_amdgcn_readfirstlane(j0);
+        j1 = __builtin_amdgcn_readfirstlane(j1);
+        alast = __builtin_amdgcn_readfirstlane(alast);
+        if (wv == 0 && has) st.job[__builtin_popcountll(jobs & ((1ull << lane) - 1ull))] = jb;
+        const int32_t jo0 = j0 / 8, nj = j1 / 8 - jo0 + 1, n_oct = (i1 - i0 + 1) * nj;
+        const bool two = alast >= 16;
+        const int32_t N = min(max(min(141 - ebound, 126) + Z.emin[i0 * Z.njo + jo0], -126), 126);
+        const float down = ldexpf(1.0f, -N);
+        // this wavefront's output tiles of 16 ticks
+        const int32_t m_first = max(-n0, 0) / 16, m_last = min(TR + alast - 1, NT - 1 - n0) / 16;
+        const int32_t per = (m_last - m_first + kWG / 64) / (kWG / 64);
+        const int32_t m_lo = m_first + wv * per, m_hi = min(m_lo + per, m_last + 1);
+        __syncthreads();                                // the images are in place
+        for (int32_t o0 = 0; o0 < n_oct; o0 += kZgOct) {
+            const int32_t no = min(kZgOct, n_oct - o0), nk = (no + 3) / 4, nq = nk <= 2 ? 8 : nk <= 4 ? 16 : nk <= 6 ? 24 : 32;
+            // stage: thread (tick, octet) sums its eight bins over the images, in order, four images' loads at a time
+            for (int32_t q = tid >> 5; q < nq; q += kWG / 32) {
+                const int32_t a = tid & 31, o = o0 + min(q, no - 1), ii = o / nj;
+                const int32_t i = i0 + ii, jo = jo0 + o - ii * nj, jb0 = jo * 8;
+                if (a == 0) st.at[q] = (uint32_t)((i * Z.njo + jo) * Z.trq) * 16u;
+                float c[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) c[k] = 0.0f;
+                // the images with a bin in one of the wavefront's two octets
+                bool near = false;
+                if (lane < n_job) {
+                    const ZJob &g = st.job[lane];
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        const int32_t iw = __builtin_amdgcn_readlane(i, 32 * w), jw = __builtin_amdgcn_readlane(jb0, 32 * w);
+                        near |= iw >= g.i0 && iw <= g.i1 && jw + 7 >= g.j0 && jw <= g.j1;
+                    }
+                }
+                uint64_t mask = __ballot(near);
+                while (mask) {
+                    uint32_t x[4][8];
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const bool any = mask != 0;
+                        const ZJob &g = st.job[any ? __builtin_ctzll(mask) : 0];
+                        mask &= mask - 1ull;
+                        const int32_t al = ac + a - g.a0;
+                        // bits of the octet's bins that are not in the image; their loads go past the box and return 0
+                        uint32_t out = ~0u;
+                        if (q < no && any && al >= 0 && al < g.na && i >= g.i0 && i <= g.i1)
+                            out = ~(~0u << min(max(g.j0 - jb0, 0), 8)) | ~0u << min(max(g.j1 - jb0 + 1, 0), 8);
+                        const int32_t at = g.base + i * g.si + jb0 * g.sj + 4 * al, sj = g.sj;
+                        const int64_t box = uniform_i64((int64_t)(cells + g.cells), 0);
+                        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+                            (void *)box, (short)0, __builtin_amdgcn_readfirstlane(g.bytes), kBufferWord3);
+#pragma unroll
+                        for (int k = 0; k < 8; ++k)
+                            x[w][k] = __builtin_amdgcn_raw_buffer_load_b32(
+                                rc, (uint32_t)(at + k * sj) | (uint32_t)((int32_t)(out << (31 - k)) >> 31), 0, 0);
+                    }
+#pragma unroll
+                    for (int w = 0; w < 4; ++w)
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) c[k] += __builtin_bit_cast(float, x[w][k]);
+                }
+                half8 h, l;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int32_t e = jb0 + k < P.by ? Z.exps[i * P.by + jb0 + k] : 0;
+                    const float y = ldexpf(c[k], N - e);
+                    h[k] = (_Float16)y;
+                    l[k] = (_Float16)(y - (float)h[k]);
+                }
+                st.c[0][a >> 4][q][a & 15] = __builtin_bit_cast(u32x4, h);
+                st.c[1][a >> 4][q][a & 15] = __builtin_bit_cast(u32x4, l);
+            }
+            __syncthreads();
+            if (m_lo < m_hi) {
+                float O[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                for (int32_t t = m_lo - 2; t < m_hi; t += 2) {
+                    const bool v0 = t >= 0 && t < n_tau, v1 = t + 1 >= 0 && t + 1 < n_tau;
+                    if (v0 || v1) {
+                        floatx4 D[2][2];
+#pragma unroll
+                        for (int b = 0; b < 2; ++b)
+#pragma unroll
+                            for (int y = 0; y < 2; ++y) D[b][y] = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
+                        const uint32_t f0 = (uint32_t)min(max(t, 0), n_tau - 1) * 256u;
+                        const uint32_t f1 = (uint32_t)min(max(t + 1, 0), n_tau - 1) * 256u;
+                        if (two) z_dispatch<true>(nk, st, rh, rl, f0, f1, lj, lg, D);
+                        else z_dispatch<false>(nk, st, rh, rl, f0, f1, lj, lg, D);
+                        // anti-diagonals: tile y of rows b goes to output tiles t + y + b (lo) and the next one (hi)
+#pragma unroll
+                        for (int b = 0; b < 2; ++b)
+#pragma unroll
+                            for (int y = 0; y < 2; ++y) {
+                                if ((b == 1 && !two) || !(y ? v1 : v0)) continue;
+                                const floatx4 d = D[b][y];
+                                const float lo = d[0] + row_up<1>(d[1]) + (row_up<2>(d[2]) + row_up<3>(d[3]));
+                                const float hi = row_down<15>(d[1]) + (row_down<14>(d[2]) + row_down<13>(d[3]));
+                                // row g moves up by 4 g more
+                                const float l4 = row_up<4>(lo), l8 = row_up<8>(lo), l12 = row_up<12>(lo);
+                                O[y + b] += lg == 0 ? lo : lg == 1 ? l4 : lg == 2 ? l8 : l12;
+                                const float s12 = row_down<12>(lo) + row_up<4>(hi), s8 = row_down<8>(lo) + row_up<8>(hi);
+                                const float s4 = row_down<4>(lo) + row_up<12>(hi);
+                                O[y + b + 1] += lg == 0 ? hi : lg == 1 ? s12 : lg == 2 ? s8 : s4;
+                            }
+                    }
+                    const float y0 = rows_sum(O[0]), y1 = rows_sum(O[1]);
+                    const int32_t m = t + (lg & 1), n = n0 + 16 * m + lj;
+                    if (lane < 32 && m >= m_lo && m < m_hi && n >= 0 && n < NT) emit(n, (lg ? y1 : y0) * down);
+                    O[0] = O[2];
+                    O[1] = O[3];
+                    O[2] = O[3] = 0.0f;
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// Loads the group that starts at list entry q of [q, end) into st.seg: the longest run of at most kZgSegs entries whose
+// ticks span at most kZgSpan (one entry at least).  id(k) is entry k's segment.  Every wavefront finds the same group;
+// the first one writes it.  Returns its length; [A0, A1] its ticks (A1 < A0: no charge), bound a bound of its charge.
+template <class Id>
+__device__ __forceinline__ int32_t z_load_group(const DevParams &P, const SegInfo *__restrict__ si, int64_t q, int64_t end,
+                                                int32_t uc, int32_t vc, Id id, ZStage &st, int32_t &A0, int32_t &A1,
+                                                float &bound) {
+    const int lane = lane_id();
+    const int32_t cnt = (int32_t)min<int64_t>(kZgSegs, end - q);
+    ZSeg z{0, 0, 0, 0, 0, INT32_MAX, 0, 0, 0};
+    int32_t lo = INT32_MAX, hi = INT32_MIN;
+    float qa = 0.0f;
+    if (lane < cnt) {
+        const SegInfo &g = si[id(q + lane)];
+        const bool any = max(g.u0, uc - P.bx) <= min(g.u0 + g.nu - 1, uc + P.bx - 1) &&
+                         max(g.v0, vc - P.by) <= min(g.v0 + g.nv - 1, vc + P.by - 1);
+        if (any && !(g.flags & (SEG_INVALID | SEG_TOO_LONG))) {
+            z = ZSeg{g.cell_off, g.u0, g.nu, g.v0, g.nv, g.a0, g.na, g.na_pad, 0};
+            lo = g.a0;
+            hi = g.a0 + g.na - 1;
+            qa = fabsf(g.q_a);
+        }
+    }
+#pragma unroll
+    for (int d = 1; d < kZgSegs; d <<= 1) {              // running span over the entries
+        const int32_t x = __shfl_up(lo, d), y = __shfl_up(hi, d);
+        const float b = __shfl_up(qa, d);
+        if (lane >= d) {
+            lo = min(lo, x);
+            hi = max(hi, y);
+            qa = fmaxf(qa, b);
+        }
+    }
+    const bool fits = lane < cnt && (lane == 0 || (int64_t)hi - lo < kZgSpan);
+    const int32_t n = __builtin_ctzll(~__ballot(fits));  // the entries that fit are a prefix
+    A0 = __builtin_amdgcn_readlane(lo, n - 1);
+    A1 = __builtin_amdgcn_readlane(hi, n - 1);
+    bound = lane_value(qa, n - 1) * (float)kZgSegs;
+    if (threadIdx.x < 64 && lane < n) st.seg[lane] = z;
+    return n;
+}
+
+// Sorted variant (automatic choice): one workgroup per active pixel, its segments in ascending id, group by group; the
+// groups' currents go into the pixel's waveform in LDS with Kahan compensation.
+__global__ __launch_bounds__(kWG, 2) void k_induce_z(DevParams P, ZTable Z, const SegInfo *__restrict__ si,
+                                                  const float *__restrict__ cells, const int64_t *__restrict__ slot_off,
+                                                  const int32_t *__restrict__ pairs, const int32_t *__restrict__ slot_gp,
+                                                  const int32_t *__restrict__ order, float *__restrict__ wave,
+                                                  DevHeader *H) {
+    extern __shared__ float sm[];
+    __shared__ ZStage st;
+    __shared__ int32_t s_slot;
+    const int NT = P.nticks, tid = threadIdx.x;
+    float *s_sum = sm, *s_cmp = sm + NT;
+    const int64_t n_slots = H->n_slots;
+    for (;;) {
+        if (tid == 0) s_slot = (int32_t)atomicAdd(&H->work[0], 1u);
+        __syncthreads();
+        const int32_t got = __builtin_amdgcn_readfirstlane(s_slot);
+        if (got >= n_slots) break;
+        const int64_t slot = order ? order[got] : got;
+        for (int n = tid; n < NT; n += kWG) { s_sum[n] = 0.0f; s_cmp[n] = 0.0f; }
+        const int32_t p = slot_gp[slot] % P.npx;
+        const int32_t uc = (p % P.nx) * P.nsub + P.nsub / 2, vc = (p / P.nx) * P.nsub + P.nsub / 2;
+        const int64_t pe = slot_off[slot + 1];
+        for (int64_t q = slot_off[slot]; q < pe;) {
+            int32_t A0, A1;
+            float bound;
+            const int32_t n = z_load_group(P, si, q, pe, uc, vc, [&](int64_t k) { return pairs[k]; }, st, A0, A1, bound);
+            z_group(P, Z, st, n, A0, A1, bound, uc, vc, cells, [&](int32_t t, float x) {
+                const float y = x - s_cmp[t], z = s_sum[t] + y;
+                s_cmp[t] = (z - s_sum[t]) - y;
+                s_sum[t] = z;
+            });
+            __syncthreads();                            // before the next group's segments
+            q += n;
+        }
+        float *wrow = wave + slot * NT;
+        for (int n = tid; n < NT; n += kWG) wrow[n] = s_sum[n] - s_cmp[n];
+        __syncthreads();
+    }
+}
+
+// Atomic variant (automatic choice): the same group products with FP32 atomics.  A work unit is a block of kZaSegs
+// consecutive segments and every 16th pixel row of their reach; runs of its segments of one event that lie close together
+// form the groups.
+constexpr int32_t kZaSegs = 8, kZaRows = 16;
+__global__ __launch_bounds__(kWG, 2) void k_induce_z_atomic(DevParams P, ZTable Z, const SegInfo *__restrict__ si,
+                                                         int64_t n_seg, const float *__restrict__ cells,
+                                                         const int32_t *__restrict__ pix_slot, float *wave,
+                                                         DevHeader *H) {
+    __shared__ ZStage st;
+    __shared__ int32_t s_unit;
+    const int NT = P.nticks, tid = threadIdx.x, lane = tid & 63;
+    const int64_t n_units = (n_seg + kZaSegs - 1) / kZaSegs * kZaRows;
+    for (;;) {
+        if (tid == 0) s_unit = (int32_t)atomicAdd(&H->work[1], 1u);
+        __syncthreads();
+        const int64_t unit = __builtin_amdgcn_readfirstlane(s_unit);
+        __syncthreads();
+        if (unit >= n_units) break;
+        const int64_t blk = unit / kZaRows, end = min(n_seg, (blk + 1) * kZaSegs);
+        const int32_t row = (int32_t)(unit - blk * kZaRows);
+        for (int64_t q = blk * kZaSegs; q < end;) {
+            // the group: entries q .. of one event whose ticks span at most kZgSpan and whose union of pixel rectangles is
+            // at most twice the largest one (every wavefront finds the same)
+            const int32_t cnt = (int32_t)(end - q);
+            ZSeg z{0, 0, 0, 0, 0, INT32_MAX, 0, 0, 0};
+            int32_t lo = INT32_MAX, hi = INT32_MIN, x0 = INT32_MAX, x1 = -1, y0 = INT32_MAX, y1 = -1, area = 0, ev = -1;
+            float qa = 0.0f;
+            if (lane < cnt) {
+                const SegInfo &g = si[q + lane];
+                ev = g.event;
+                if (g.n_pairs > 0) {
+                    z = ZSeg{g.cell_off, g.u0, g.nu, g.v0, g.nv, g.a0, g.na, g.na_pad, 0};
+                    lo = g.a0;
+                    hi = g.a0 + g.na - 1;
+                    x0 = g.ix0; x1 = g.ix1; y0 = g.iy0; y1 = g.iy1;
+                    area = g.n_pairs;
+                    qa = fabsf(g.q_a);
+                }
+            }
+            const bool same = ev == __builtin_amdgcn_readlane(ev, 0);
+#pragma unroll
+            for (int d = 1; d < kZaSegs; d <<= 1) {
+                const int32_t a = __shfl_up(lo, d), b = __shfl_up(hi, d), c = __shfl_up(x0, d), e = __shfl_up(x1, d);
+                const int32_t f = __shfl_up(y0, d), h = __shfl_up(y1, d), k = __shfl_up(area, d);
+                const float m = __shfl_up(qa, d);
+                if (lane >= d) {
+                    lo = min(lo, a); hi = max(hi, b); x0 = min(x0, c); x1 = max(x1, e); y0 = min(y0, f); y1 = max(y1, h);
+                    area = max(area, k);
+                    qa = fmaxf(qa, m);
+                }
+            }
+            const bool fits = lane < cnt && (lane == 0 || (same && (int64_t)hi - lo < kZgSpan &&
+                                                           (int64_t)(x1 - x0 + 1) * (y1 - y0 + 1) <= 2ll * area));
+            const uint64_t out = ~__ballot(fits);
+            const int32_t n = __builtin_ctzll(out);
+            const int32_t A0 = __builtin_amdgcn_readlane(lo, n - 1), A1 = __builtin_amdgcn_readlane(hi, n - 1);
+            const int32_t gx0 = __builtin_amdgcn_readlane(x0, n - 1), gx1 = __builtin_amdgcn_readlane(x1, n - 1);
+            const int32_t gy0 = __builtin_amdgcn_readlane(y0, n - 1), gy1 = __builtin_amdgcn_readlane(y1, n - 1);
+            const int32_t e = __builtin_amdgcn_readlane(ev, 0);
+            const float bound = lane_value(qa, n - 1) * (float)kZaSegs;
+            __syncthreads();                            // the previous group's segments are no longer read
+            if (tid < n) st.seg[tid] = z;
+            for (int32_t iy = gy0 + row; iy <= gy1; iy += kZaRows)
+                for (int32_t ix = gx0; ix <= gx1; ++ix) {
+                    const int32_t slot = __builtin_amdgcn_readfirstlane(pix_slot[(int64_t)e * P.npx + iy * P.nx + ix]);
+                    if (slot < 0) continue;
+                    float *wrow = wave + (int64_t)slot * NT;
+                    z_group(P, Z, st, n, A0, A1, bound, ix * P.nsub + P.nsub / 2, iy * P.nsub + P.nsub / 2, cells,
+                            [&](int32_t t, float x) {
+                                if (x != 0.0f) atomicAdd(&wrow[t], x);
+                            });
+                }
+            q += n;
+        }
+    }
+}
+
+// Materialised form: row q of `out` (n_ticks floats) receives pair q's current, one pair at a time.
+__global__ __launch_bounds__(kWG, 2) void k_induce_z_pairs(DevParams P, ZTable Z, const SegInfo *__restrict__ si,
+                                                        const float *__restrict__ cells,
+                                                        const int64_t *__restrict__ slot_off,
+                                                        const int32_t *__restrict__ pairs,
+                                                        const int32_t *__restrict__ slot_gp, const DevHeader *H,
+                                                        float *__restrict__ out) {
+    extern __shared__ float sm[];
+    __shared__ ZStage st;
+    const int NT = P.nticks, tid = threadIdx.x;
+    for (int n = tid; n < NT; n += kWG) sm[n] = 0.0f;
+    for (int64_t slot = blockIdx.x; slot < H->n_slots; slot += gridDim.x) {
+        const int32_t p = slot_gp[slot] % P.npx;
+        const int32_t uc = (p % P.nx) * P.nsub + P.nsub / 2, vc = (p / P.nx) * P.nsub + P.nsub / 2;
+        for (int64_t q = slot_off[slot]; q < slot_off[slot + 1]; ++q) {
+            int32_t A0, A1;
+            float bound;
+            z_load_group(P, si, q, q + 1, uc, vc, [&](int64_t k) { return pairs[k]; }, st, A0, A1, bound);
+            z_group(P, Z, st, 1, A0, A1, bound, uc, vc, cells, [&](int32_t t, float x) { sm[t] += x; });
+            __syncthreads();
+            float *row = out + q * NT;
+            for (int n = tid; n < NT; n += kWG) {
+                row[n] = sm[n];
+                sm[n] = 0.0f;
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------ charge outside the readout
 // The signed induction that falls outside [0, n_ticks), from FP64 prefix sums of the table columns.  Charge in column
 // (u, v) at tick a induces on every pixel that reaches the column, and only the sum over an event's pixels is reported, so
@@ -2891,6 +3294,28 @@ __device__ __forceinline__ double clip_weight(const DevParams &P, const double *
     return s;
 }
 
+// Per-pair modes: over the segments' charge cells (a workgroup per segment).
+__global__ __launch_bounds__(kWG) void k_clip_cells(DevParams P, const SegInfo *__restrict__ si, int64_t n_seg,
+                                                    const float *__restrict__ cells, const double *__restrict__ prefix,
+                                                    const double *__restrict__ cls, double *report) {
+    __shared__ double red[kWG / 64];
+    for (int64_t s = blockIdx.x; s < n_seg; s += gridDim.x) {
+        const SegInfo &g = si[s];
+        if (g.n_pairs == 0 || (g.a0 >= P.t_r - 1 && g.a0 + g.na <= P.nticks)) continue;
+        const int32_t na = g.na, nv = g.nv, nap = g.na_pad;
+        const float *c = cells + g.cell_off;
+        double acc = 0.0;
+        for (int32_t i = threadIdx.x; i < g.nu * nv * na; i += kWG) {
+            const int32_t col = i / na, a = i - col * na, u = col / nv;
+            const float q = c[(int64_t)col * nap + a];
+            if (q != 0.0f) acc += (double)q * clip_weight(P, prefix, cls, g.u0 + u, g.v0 + col - u * nv, g.a0 + a);
+        }
+        const double t = block_sum_double(acc, red);
+        if (threadIdx.x == 0 && t != 0.0) atomicAdd(&report[(int64_t)g.event * 5 + 3], t);
+        __syncthreads();
+    }
+}
+
 // Summed mode: over the column pieces (a wavefront per column at a time).
 __global__ __launch_bounds__(kWG) void k_clip_columns(DevParams P, SumWork sw, const double *__restrict__ prefix,
                                                       const double *__restrict__ cls, double *report) {
@@ -2921,6 +3346,45 @@ __global__ __launch_bounds__(kWG) void k_clip_columns(DevParams P, SumWork sw, c
         }
     }
     if (ev >= 0) flush();
+}
+
+static ZTable z_table(const Table &T) {
+    return ZTable{(const u32x4 *)T.zhi, (const u32x4 *)T.zlo, T.exps, T.zemin, T.njo, T.trq};
+}
+
+// The grid's dynamic LDS may exceed 64 KB with the static stage: the limit is raised once per device.
+hipError_t allow_z_lds() {
+    const int most = 2 * 8000 * (int)sizeof(float);
+    hipError_t e = hipFuncSetAttribute((const void *)k_induce_z, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)k_induce_z_pairs, hipFuncAttributeMaxDynamicSharedMemorySize, most / 2);
+    return e;
+}
+
+void launch_induce_z(const DevParams &P, const Work &w, const Table &T, float *wave, int mode, int64_t n_slots,
+                     hipStream_t st) {
+    const ZTable Z = z_table(T);
+    if (w.n_seg > 0) {
+        const int64_t g = std::min<int64_t>(w.n_seg, 8192);
+        k_clip_cells<<<(unsigned)g, kWG, 0, st>>>(P, w.si, w.n_seg, w.cells, T.prefix, T.cls, w.report);
+    }
+    if (mode == 0) {
+        if (n_slots <= 0) return;
+        if (w.order) launch_slot_order(P, w, n_slots, st);
+        k_induce_z<<<(unsigned)std::min<int64_t>(n_slots, 256 * 4), kWG, (size_t)2 * P.nticks * sizeof(float), st>>>(
+            P, Z, w.si, w.cells, w.slot_off, w.pairs, w.slot_gp, w.order, wave, w.hdr);
+    } else if (w.n_seg > 0) {
+        const int64_t units = (w.n_seg + kZaSegs - 1) / kZaSegs * kZaRows;
+        k_induce_z_atomic<<<(unsigned)std::min<int64_t>(units, 256 * 4), kWG, 0, st>>>(P, Z, w.si, w.n_seg, w.cells,
+                                                                                      w.pix_slot, wave, w.hdr);
+    }
+}
+
+void launch_induce_z_pairs(const DevParams &P, const Work &w, const Table &T, int64_t n_slots, float *out,
+                           hipStream_t st) {
+    if (n_slots <= 0) return;
+    k_induce_z_pairs<<<(unsigned)std::min<int64_t>(n_slots, 65536), kWG, (size_t)P.nticks * sizeof(float), st>>>(
+        P, z_table(T), w.si, w.cells, w.slot_off, w.pairs, w.slot_gp, w.hdr, out);
 }
 
 bool summed_matrix(int32_t rt, bool shift) { return rt == 0 && !shift; }
@@ -3011,19 +3475,26 @@ void launch_induce_summed(const DevParams &P, const Work &w, const SumWork &sw, 
 // relative term.  (One thread per pixel walking the ticks in order was 4.4x slower: too few wavefronts, and a
 // dependent load per tick.)
 
+
+// With `list` the pixels are the header's n_settle entries of it (a second pass over settled currents; the report's sum of
+// currents is the first pass's).  With `settle` a pixel one of whose decisions - a crossing, a code, or the margin that
+// flags them - lies within twice the margin is appended to it, and its dropped and surplus samples are left to that pass.
+template <bool SETTLE>
 __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *__restrict__ wave,
                                                      const int32_t *__restrict__ slot_gp,
                                                      const uint64_t *__restrict__ ev_ids, int32_t n_ev,
-                                                     const uint8_t *__restrict__ disabled, int64_t n_slots_arg,
+                                                     const uint8_t *__restrict__ disabled, int64_t n_slots,
                                                      int32_t *pk_tick, uint16_t *pk_adc, uint8_t *pk_flag,
                                                      int64_t *pk_cnt, DevHeader *H, double *report,
-                                                     int64_t *ev_cnt) {
-    const int64_t n_slots = n_slots_arg >= 0 ? n_slots_arg : H->n_slots;
+                                                     int64_t *ev_cnt, const int32_t *__restrict__ list,
+                                                     int32_t *settle) {
+    const int64_t n_rows = list ? (int64_t)H->n_settle : n_slots;
     const int32_t NT = P.nticks, RP = P.reset_period;
     const int lane = lane_id();
-    constexpr int kWaves = kWG / 64;
+    const int kWaves = blockDim.x / 64;
     const int32_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    for (int64_t slot = (int64_t)blockIdx.x * kWaves + wv; slot < n_slots; slot += (int64_t)gridDim.x * kWaves) {
+    for (int64_t row = (int64_t)blockIdx.x * kWaves + wv; row < n_rows; row += (int64_t)gridDim.x * kWaves) {
+        const int64_t slot = list ? __builtin_amdgcn_readfirstlane(list[row]) : row;
         const int32_t gp = __builtin_amdgcn_readfirstlane(slot_gp[slot]);
         if (!(gp >= 0 && gp < n_ev * P.npx)) {                   // ids outside the event grids are skipped
             if (lane == 0) pk_cnt[slot] = 0;
@@ -3037,7 +3508,7 @@ __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *_
         const float reset0 = P.sig_reset > 0.0f ? P.sig_reset * noise_normal(P, pid, kTickInitial, ev, STREAM_RESET)
                                                 : 0.0f;
         float Qb = reset0, Qbc = 0.0f, Ab = 0.0f;                     // carried charge (Kahan pair) and |charge|
-        bool pending = false, uncertain = false, done = off;
+        bool pending = false, uncertain = false, done = off, close = false;
         int32_t ns = 0, ready = 0, last = -(1 << 28), cnt = 0, dropped = 0, over = 0;
         const int64_t obase = slot * P.max_packets;
         double rs = 0.0;
@@ -3084,6 +3555,7 @@ __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *_
                     const float dist = (xq - fl) * P.q_lsb;
                     const float eps = P.eps_abs + P.eps_rel * (Av + fabsf(qs) + P.thr);
                     if (dist < eps || P.q_lsb - dist < eps) flag |= 1;
+                    if (SETTLE) close |= dist < 2.0f * eps || P.q_lsb - dist < 2.0f * eps;
                     if (cnt < P.max_packets) {
                         if (lane == 0) {
                             pk_tick[obase + cnt] = ns;
@@ -3121,15 +3593,18 @@ __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *_
                     eps = P.eps_abs + P.eps_rel * (Al + fabsf(Ql) + P.thr);
                 }
                 const uint64_t cross = __ballot(cmp && m >= 0.0f), near = __ballot(cmp && fabsf(m) < eps);
+                const uint64_t near2 = SETTLE ? __ballot(cmp && fabsf(m) < 2.0f * eps) : 0;
                 if (cross) {
                     const int32_t c = __ffsll((unsigned long long)cross) - 1;
                     if (near & ((2ull << c) - 1)) uncertain = true;    // lanes up to the crossing (c = 63: all)
+                    if (near2 & ((2ull << c) - 1)) close = true;
                     pending = true;
                     ns = max(n0 + c + P.hold, last + P.spacing);
                     if (ns >= NT) { ++dropped; done = true; break; }
                     continue;                                         // the sample may fall in this chunk
                 }
                 if (near) uncertain = true;
+                if (near2) close = true;
                 if (r < jn) {                                         // periodic reset at lane r
                     restart((uint32_t)(n0 + r));
                     s = r;
@@ -3147,7 +3622,11 @@ __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *_
             }
         }
         if (lane == 0) pk_cnt[slot] = off ? 0 : cnt;
-        add_report(report, e, 2, rs, true);
+        if (!list) add_report(report, e, 2, rs, true);
+        if (SETTLE && close) {
+            if (lane == 0) settle[atomicAdd(&H->n_settle, 1u)] = (int32_t)slot;
+            continue;
+        }
         if (lane == 0 && dropped) {
             atomicAdd((unsigned long long *)&H->dropped, (unsigned long long)dropped);
             if (ev_cnt) atomicAdd((unsigned long long *)&ev_cnt[2 * e], (unsigned long long)dropped);
@@ -3160,12 +3639,261 @@ __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *_
 }
 
 void launch_electronics(const DevParams &P, const float *wave, const int32_t *slot_gp, const uint64_t *event_ids,
-                        int64_t n_slots, const Work &w, hipStream_t st) {
+                        int64_t n_slots, const Work &w, int32_t *settle, hipStream_t st) {
     int64_t g = (n_slots + kWG / 64 - 1) / (kWG / 64);
     if (g < 1) g = 1;
     if (g > 65536) g = 65536;
-    k_electronics<<<(unsigned)g, kWG, 0, st>>>(P, wave, slot_gp, event_ids, w.n_ev, w.disabled, n_slots, w.pk_tick,
-                                               w.pk_adc, w.pk_flag, w.pk_off, w.hdr, w.report, w.ev_cnt);
+    auto *k = settle ? k_electronics<true> : k_electronics<false>;
+    k<<<(unsigned)g, kWG, 0, st>>>(P, wave, slot_gp, event_ids, w.n_ev, w.disabled, n_slots, w.pk_tick, w.pk_adc, w.pk_flag,
+                                   w.pk_off, w.hdr, w.report, w.ev_cnt, nullptr, settle);
+}
+
+// ================================================================================================= settled pixels
+// A packet's tick and code are decided by comparing a charge with a threshold or an LSB edge, and a charge that lies on
+// the edge to within rounding is decided by the order of the FP32 sum.  The vector kernels' order is the one packets are
+// stated in, so that they do not depend on which units summed the currents: a pixel with such a decision (about one in a
+// hundred) gets its currents again in that order, bit for bit, and passes the front end once more.
+//   Order: a pair's (a record's) products column by column, cell tick by cell tick, as one FP32 chain per output tick;
+// chains of a pair (of kSumKahanEvery records that meet a 256-tick tile) added with Kahan compensation in list order.
+//   A round is 16 chains of a (pixel, 256 ticks), one per wavefront (lane t: ticks 4 t .. + 3).  The few pixels of a call
+// are spread over the chip round by round: a workgroup computes a round's chains, waits until the round before has been
+// added, adds its own to the pixel's sum and compensation in memory and passes on.  Rounds are handed out in order, so a
+// round waits only on one that is already running.  Beyond the first kSettleSpread pixels there are enough to take a
+// pixel's rounds one after the other in one workgroup.  (One workgroup per pixel and 256 ticks throughout: 4.1 instead
+// of 0.65 ms for 4 pixels of 3000 dense segments, as 48 workgroups leave the chip idle; 1.1 instead of 0.74 ms for 14
+// pixels of a summed event of 20,000 segments, 3000 ticks.)
+constexpr int32_t kSettleWG = 1024, kSettleWaves = kSettleWG / 64, kSettleTile = 256;
+
+// Adds a sequence of (table column, cell column) products to the lane's 4 ticks, in pair_block's order.  next(col, cc, n)
+// gives the lane's lag-0 entry of the next table column, its cell column and that one's blocks of kAC ticks.  A block needs
+// 8 table values more than the one before (they are read as two 16-byte words, with the block's cells, while the block
+// before runs): the reads, not the products, bound the plain loop, which takes 11 words of 4 bytes.
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+template <class Next>
+__device__ __forceinline__ void chain4(Next next, float (&acc)[4]) {
+    const float *col;
+    cfloat_ptr cc;
+    int32_t n;
+    if (!next(col, cc, n)) return;
+    floatx4 t = *(const floatx4u *)col, a1 = *(const floatx4u *)(col - 4), a0 = *(const floatx4u *)(col - 8);
+    float c[kAC];
+#pragma unroll
+    for (int q = 0; q < kAC; ++q) c[q] = cc[q];
+    for (bool more = true; more;) {
+        floatx4 nt = a0, na1 = a1, na0 = a0;
+        if (--n > 0) {
+            col -= 8;
+            cc += kAC;
+        } else {
+            more = next(col, cc, n);
+            if (more) nt = *(const floatx4u *)col;
+        }
+        float nc[kAC];
+        if (more) {
+            na1 = *(const floatx4u *)(col - 4);
+            na0 = *(const floatx4u *)(col - 8);
+#pragma unroll
+            for (int q = 0; q < kAC; ++q) nc[q] = cc[q];
+        }
+        const float w[11] = {a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3], t[0], t[1], t[2], t[3]};
+#pragma unroll
+        for (int q = 0; q < kAC; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = fmaf(c[q], w[r - q + kAC - 1], acc[r]);
+        if (more) {
+            t = nt;
+            a1 = na1;
+            a0 = na0;
+#pragma unroll
+            for (int q = 0; q < kAC; ++q) c[q] = nc[q];
+        }
+    }
+}
+
+struct SettleLds {
+    float part[kSettleWaves][kSettleTile];
+    int32_t win[kSettleWaves][2];                       // ticks that a chain is added to
+    int32_t buf[kSettleWaves * kSumKahanEvery];         // summed form: the round's records
+    uint32_t unit;
+};
+
+// The chains of round r of pixel `slot`, ticks t0 .. t1, into L.part; returns how many wavefronts have one.
+template <bool SUMMED>
+__device__ __forceinline__ int32_t settle_chains(const DevParams &P, const Work &w, const SumWork &sw,
+                                                 const float *__restrict__ Rpad, SettleLds &L, int64_t slot, int32_t r,
+                                                 int32_t t0, int32_t t1) {
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int32_t TR = P.t_r, nb = t0 + 4 * lane;
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    int32_t lo = t0, hi = t1, n_chain;
+    if constexpr (SUMMED) {
+        // the records that meet the tile, number 64 r .. 64 r + 63 of them (every wavefront finds the same)
+        constexpr int32_t kEach = kSumKahanEvery, kRound = kSettleWaves * kEach;
+        static_assert(kRound == 64, "a round's records");
+        const int64_t pb = sw.mlist_off[slot], pe = sw.mlist_off[slot + 1];
+        int32_t seen = -64 * r, n = 0;                  // number of the next one, relative to the round
+        for (int64_t c0 = pb; c0 < pe && seen < kRound; c0 += 64) {
+            const int64_t k = c0 + lane;
+            bool in = k < pe;
+            if (in) {
+                const PieceRef g = sw.mrec[k];
+                in = g.a0 + g.na - 1 >= t0 && g.a0 - (TR - 1) <= t0 + kSettleTile - 1;
+            }
+            const uint64_t mask = __ballot(in);
+            const int32_t at = seen + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
+            if (wv == 0 && in && at >= 0 && at < kRound) L.buf[at] = (int32_t)(k - pb);
+            seen += __builtin_popcountll(mask);
+        }
+        n = min(max(seen, 0), kRound);
+        n_chain = (n + kEach - 1) / kEach;
+        __syncthreads();
+        int32_t j = wv * kEach;
+        const int32_t je = min(j + kEach, n);
+        chain4([&](const float *&col, cfloat_ptr &cc, int32_t &nblk) {
+            if (j >= je) return false;
+            const PieceRef g = sw.mrec[pb + __builtin_amdgcn_readfirstlane(L.buf[j++])];
+            cc = uniform_cptr(cell_ptr(sw.S, sw.Sm, sw.nS8, g.cell8));
+            col = Rpad + (int64_t)(g.bin & kBinMask) * P.col_len + nb - g.a0 + TR - 1 + kPad;
+            nblk = __builtin_amdgcn_readfirstlane((g.na + kAC - 1) / kAC);
+            return true;
+        }, acc);
+    } else {
+        const int64_t q = w.slot_off[slot] + (int64_t)r * kSettleWaves;
+        n_chain = (int32_t)min<int64_t>(kSettleWaves, w.slot_off[slot + 1] - q);
+        if (wv < n_chain) {
+            const int32_t p = w.slot_gp[slot] % P.npx;
+            const int32_t uc = (p % P.nx) * P.nsub + P.nsub / 2, vc = (p / P.nx) * P.nsub + P.nsub / 2;
+            const SegInfo &g = w.si[__builtin_amdgcn_readfirstlane(w.pairs[q + wv])];
+            lo = max(t0, g.a0 - (TR - 1));
+            hi = min(t1, g.a0 + g.na - 1);
+            const int32_t ulo = max(g.u0, uc - P.bx), uhi = min(g.u0 + g.nu - 1, uc + P.bx - 1);
+            const int32_t vlo = max(g.v0, vc - P.by), vhi = min(g.v0 + g.nv - 1, vc + P.by - 1);
+            if (ulo > uhi || vlo > vhi) hi = -1;
+            else if (nb <= hi && nb + 3 >= lo) {
+                const int32_t nblk = g.na_pad / kAC;
+                cfloat_ptr cells = uniform_cptr(w.cells + g.cell_off);
+                const float *row = Rpad + nb - g.a0 + TR - 1 + kPad;
+                int32_t u = ulo, v = vlo - 1;
+                chain4([&](const float *&col, cfloat_ptr &cc, int32_t &nn) {
+                    if (++v > vhi) {
+                        v = vlo;
+                        if (++u > uhi) return false;
+                    }
+                    cc = cells + ((int64_t)(u - g.u0) * g.nv + (v - g.v0)) * g.na_pad;
+                    col = row + (int64_t)(fold(u - uc) * P.by + fold(v - vc)) * P.col_len;
+                    nn = nblk;
+                    return true;
+                }, acc);
+            }
+        }
+    }
+    if (wv < n_chain) {
+        *(float4 *)&L.part[wv][4 * lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        if (lane == 0) {
+            L.win[wv][0] = lo;
+            L.win[wv][1] = hi;
+        }
+    }
+    return n_chain;
+}
+
+// Adds the round's chains to the sum of tick t.
+__device__ __forceinline__ void settle_add(const SettleLds &L, int32_t n_chain, int32_t t0, float &sum, float &cmp) {
+    const int32_t i = threadIdx.x, n = t0 + i;
+    for (int32_t j = 0; j < n_chain; ++j)
+        if (n >= L.win[j][0] && n <= L.win[j][1]) {
+            const float y = L.part[j][i] - cmp, t = sum + y;
+            cmp = (t - sum) - y;
+            sum = t;
+        }
+}
+
+// token[pixel of the list][tile]: rounds added so far (zero before the launch); comp: the compensations in between.
+template <bool SUMMED>
+__global__ __launch_bounds__(kSettleWG) void k_settle(DevParams P, Work w, SumWork sw, const float *__restrict__ Rpad,
+                                                      const int32_t *__restrict__ list, uint32_t *token, float *comp,
+                                                      float *wave) {
+    __shared__ __align__(16) SettleLds L;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int32_t NT = P.nticks, n_tiles = (NT + kSettleTile - 1) / kSettleTile;
+    const int32_t n_px = (int32_t)w.hdr->n_settle, n_spread = min(n_px, kSettleSpread);
+    if (n_px == 0) return;
+    auto rounds = [&](int64_t slot) {
+        const int64_t n = SUMMED ? sw.mlist_off[slot + 1] - sw.mlist_off[slot] : w.slot_off[slot + 1] - w.slot_off[slot];
+        const int32_t per = SUMMED ? 64 : kSettleWaves;
+        return max((int32_t)((n + per - 1) / per), 1);
+    };
+    // units: the spread pixels' (round, tile) pairs, lane i = pixel i of the list; then (pixel, tile) pairs
+    const int32_t mine = lane < n_spread ? rounds(list[lane]) * n_tiles : 0;
+    int32_t end = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t x = __shfl_up(end, d);
+        if (lane >= d) end += x;
+    }
+    const int32_t n_spread_units = __builtin_amdgcn_readlane(end, 63);
+    const int64_t n_units = n_spread_units + (int64_t)(n_px - n_spread) * n_tiles;
+    for (;;) {
+        if (tid == 0) L.unit = atomicAdd(&w.hdr->settle_work, 1u);
+        __syncthreads();
+        const uint32_t unit = __builtin_amdgcn_readfirstlane(L.unit);
+        __syncthreads();
+        if ((int64_t)unit >= n_units) break;
+        if ((int32_t)unit < n_spread_units) {
+            const int32_t i = __builtin_ctzll(__ballot(end > (int32_t)unit));
+            const int32_t k = (int32_t)unit - (__builtin_amdgcn_readlane(end, i) - __builtin_amdgcn_readlane(mine, i));
+            const int32_t r = k / n_tiles, tile = k - r * n_tiles, t0 = tile * kSettleTile;
+            const int64_t slot = __builtin_amdgcn_readfirstlane(list[i]);
+            const bool last = r + 1 == __builtin_amdgcn_readlane(mine, i) / n_tiles;
+            const int32_t n_chain = settle_chains<SUMMED>(P, w, sw, Rpad, L, slot, r, t0, min(t0 + kSettleTile, NT) - 1);
+            uint32_t *tk = &token[i * n_tiles + tile];
+            if (tid == 0)
+                while (__hip_atomic_load(tk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)r)
+                    __builtin_amdgcn_s_sleep(1);
+            __syncthreads();                            // the chains are in place, too
+            if (tid < kSettleTile && t0 + tid < NT) {
+                float *ps = &wave[slot * NT + t0 + tid], *pc = &comp[(int64_t)i * NT + t0 + tid];
+                float sum = 0.0f, cmp = 0.0f;
+                if (r > 0) {
+                    sum = __hip_atomic_load(ps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    cmp = __hip_atomic_load(pc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                settle_add(L, n_chain, t0, sum, cmp);
+                __hip_atomic_store(ps, last ? sum - cmp : sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(pc, cmp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            // sum and compensation are read and written past the caches, so their stores need only be complete before the
+            // token's (a release fence would write back the whole L2 in every round)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (tid == 0) __hip_atomic_store(tk, (uint32_t)r + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            const int64_t k = (int64_t)unit - n_spread_units;
+            const int64_t slot = __builtin_amdgcn_readfirstlane(list[n_spread + k / n_tiles]);
+            const int32_t t0 = (int32_t)(k % n_tiles) * kSettleTile, n_round = rounds(slot);
+            float sum = 0.0f, cmp = 0.0f;
+            for (int32_t r = 0; r < n_round; ++r) {
+                const int32_t n_chain = settle_chains<SUMMED>(P, w, sw, Rpad, L, slot, r, t0, min(t0 + kSettleTile, NT) - 1);
+                __syncthreads();
+                if (tid < kSettleTile) settle_add(L, n_chain, t0, sum, cmp);
+                __syncthreads();
+            }
+            if (tid < kSettleTile && t0 + tid < NT) wave[slot * NT + t0 + tid] = sum - cmp;
+        }
+        __syncthreads();                                // keeps thread 0's token and its next unit apart: without it the
+                                                        // other lanes of its wavefront are sent round the loop alone
+    }
+}
+
+void launch_settle(const DevParams &P, const Work &w, const SumWork &sw, const Table &T, float *wave,
+                   const int32_t *slot_gp, const uint64_t *event_ids, bool summed, int64_t n_slots, const int32_t *list,
+                   uint32_t *token, float *comp, hipStream_t st) {
+    if (n_slots <= 0) return;
+    auto *k = summed ? k_settle<true> : k_settle<false>;
+    k<<<256, kSettleWG, 0, st>>>(P, w, sw, T.Rpad, list, token, comp, wave);
+    k_electronics<false><<<(unsigned)std::min<int64_t>(n_slots, 256), 64, 0, st>>>(
+        P, wave, slot_gp, event_ids, w.n_ev, w.disabled, n_slots, w.pk_tick, w.pk_adc, w.pk_flag, w.pk_off, w.hdr, w.report,
+        w.ev_cnt, list, nullptr);
 }
 
 __global__ void k_compact(int32_t max_packets, int64_t n_slots, const int64_t *pk_off, const int32_t *slot_gp,

@@ -48,7 +48,11 @@ struct Table {
     const double *prefix = nullptr;          // [bx * by][t_r + 1] FP64 prefix sums of each column
     const void *hi = nullptr, *lo = nullptr; // [bx * by][col_len] half pairs of each column scaled by 2^exps[column]
     const int32_t *exps = nullptr;           // [bx * by]
-    // prefix sums added over the pixels that reach a column, per offset within a pixel (or null)
+    // the same half pairs by octets of bins (8 consecutive j): [bx * njo][trq] of 8 halves; smallest scale at or beyond an
+    // octet in both indices; prefix sums added over the pixels that reach a column, per offset within a pixel (or null)
+    const void *zhi = nullptr, *zlo = nullptr;
+    const int32_t *zemin = nullptr;
+    int32_t njo = 0, trq = 0;
     const double *cls = nullptr;             // [n_sub * n_sub][t_r + 1]
 };
 
@@ -124,7 +128,15 @@ void launch_induce_summed(const DevParams &P, const Work &w, const SumWork &sw, 
 void launch_table_halves(const float *Rpad, int32_t n_col, int32_t col_len, void *hi, void *lo, int32_t *exps,
                          hipStream_t st);
 
+void launch_table_octets(const float *Rpad, int32_t bx, int32_t by, int32_t t_r, int32_t col_len, int32_t trq,
+                         const int32_t *exps, void *hi, void *lo, int32_t *emin, hipStream_t st);
 void launch_clip_classes(const DevParams &P, const double *prefix, double *cls, hipStream_t st);
+hipError_t allow_z_lds();
+// the automatic per-pair induction (mode 0 sorted, 1 atomic) and its materialised form
+void launch_induce_z(const DevParams &P, const Work &w, const Table &T, float *wave, int mode, int64_t n_slots,
+                     hipStream_t st);
+void launch_induce_z_pairs(const DevParams &P, const Work &w, const Table &T, int64_t n_slots, float *out,
+                           hipStream_t st);
 
 int64_t scan_tmp_needed(int64_t n);
 void scan_exclusive_i64(int64_t *data, int64_t n, int64_t *total_dst, void *tmp, hipStream_t st);
@@ -145,15 +157,20 @@ void launch_induce_slices(const DevParams &P, const Work &w, const Table &T, flo
                           float *part, int64_t chunk, int32_t rt, hipStream_t st);
 void launch_pair_list(const DevParams &P, const Work &w, int64_t n_slots, int32_t *pair_seg, int32_t *pair_pix,
                       hipStream_t st);
-void launch_induce_pairs(const DevParams &P, const Work &w, const Table &T, int64_t n_slots, float *out,
-                         hipStream_t st);
 void launch_run_heads(const int32_t *pix, int64_t n, int64_t *head, DevHeader *H, hipStream_t st);
 void launch_run_starts(const int32_t *pix, int64_t n, const int64_t *idx, int64_t *start, int32_t *pixel_out,
                        int64_t cap, hipStream_t st);
 void launch_reduce_runs(const float *pair_current, const int64_t *start, int64_t n_runs, int32_t NT, float *current,
                         hipStream_t st);
 void launch_electronics(const DevParams &P, const float *wave, const int32_t *slot_gp, const uint64_t *event_ids,
-                        int64_t n_slots, const Work &w, hipStream_t st);
+                        int64_t n_slots, const Work &w, int32_t *settle, hipStream_t st);
+// the pixels listed by the front end (hdr->n_settle of them): currents in the vector kernels' order, packets once more.
+// token: kSettleSpread * settle_tiles(n_ticks) zeros; comp: kSettleSpread * n_ticks floats
+constexpr int32_t kSettleSpread = 64;
+inline int64_t settle_tiles(int32_t n_ticks) { return (n_ticks + 255) / 256; }
+void launch_settle(const DevParams &P, const Work &w, const SumWork &sw, const Table &T, float *wave,
+                   const int32_t *slot_gp, const uint64_t *event_ids, bool summed, int64_t n_slots, const int32_t *list,
+                   uint32_t *token, float *comp, hipStream_t st);
 void launch_compact_packets(const DevParams &P, const Work &w, int64_t n_slots, int32_t *pkt_pixel, int32_t *pkt_tick,
                             uint16_t *pkt_adc, uint8_t *pkt_flags, int64_t cap_packets, const int64_t *ev_pix_off,
                             int64_t *ev_pkt_off, int64_t *counts, hipStream_t st);

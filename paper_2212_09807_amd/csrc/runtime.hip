@@ -67,7 +67,7 @@ struct lts_context {
     bool has_table = false;
     DevBuf Rpad, prefix;
     DevBuf Rhalf, Rexp;              // the table's half pairs (high plane, then low) and their column scales
-    DevBuf Rclass;                   // the clip classes
+    DevBuf Roct, Remin, Rclass;      // the half pairs by octets of bins, the octets' smallest scales, the clip classes
     std::vector<float> table_host;   // kept to build server lanes
     int32_t t_r = 0, b_x = 0, b_y = 0;
     // scratch pool
@@ -246,7 +246,7 @@ constexpr lts_status kNotAdmitted = LTS_ERR_NOT_READY;
 std::vector<DevBuf *> pool_buffers(lts_context *c) {
     return {&c->ev_cnt, &c->mask, &c->col_seg_off, &c->col_cursor, &c->col_seg, &c->col_tmp, &c->piece_off,
             &c->s_off, &c->piece, &c->pdesc, &c->S, &c->list_off, &c->list, &c->rec, &c->mlist_off, &c->m_off,
-            &c->mrec, &c->Sm, &c->segc, &c->part, &c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Rclass,
+            &c->mrec, &c->Sm, &c->segc, &c->part, &c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Roct, &c->Remin, &c->Rclass,
             &c->si, &c->cell_off, &c->pix_cnt, &c->cursor, &c->pix_slot, &c->slot_gp, &c->slot_off, &c->pairs_u, &c->pairs, &c->cells, &c->pk_tick, &c->pk_adc,
             &c->pk_flag, &c->pk_off, &c->hdr, &c->scan_tmp, &c->ev_off, &c->ev_ids, &c->report_tmp, &c->counts_tmp,
             &c->red_head, &c->red_start, &c->order};
@@ -256,7 +256,7 @@ std::vector<DevBuf *> pool_buffers(lts_context *c) {
 // persist across calls); every buffer is grown again to the exact size the next call needs.  The caller makes sure
 // no queued work still uses them.
 void release_scratch(lts_context *c) {
-    const DevBuf *kept[] = {&c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Rclass, &c->mask};
+    const DevBuf *kept[] = {&c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Roct, &c->Remin, &c->Rclass, &c->mask};
     for (DevBuf *b : pool_buffers(c))
         if (std::find(std::begin(kept), std::end(kept), b) == std::end(kept)) free_buf(*b);
 }
@@ -391,6 +391,11 @@ size_t half_plane(int32_t b_x, int32_t b_y, int32_t col_len) { return (size_t)b_
 Table table_of(lts_context *c) {
     const size_t plane = half_plane(c->b_x, c->b_y, c->P.col_len);
     Table T{as<float>(c->Rpad), as<double>(c->prefix), c->Rhalf.p, as<uint16_t>(c->Rhalf) + plane, as<int32_t>(c->Rexp)};
+    T.njo = (c->b_y + 7) / 8;
+    T.trq = (c->t_r + 15) / 16 * 16;
+    T.zhi = c->Roct.p;
+    T.zlo = as<uint16_t>(c->Roct) + (size_t)c->b_x * T.njo * T.trq * 8;
+    T.zemin = as<int32_t>(c->Remin);
     T.cls = as<double>(c->Rclass);
     return T;
 }
@@ -493,13 +498,20 @@ void summed_needs(lts_context *c, const DevHeader &h, int64_t n_slots, int32_t n
     needs.push_back({&c->scan_tmp, sizeof(int64_t) * (size_t)scan_tmp_needed(std::max(nc1, n_slots + 1))});
 }
 
+// Whether the call's currents are summed on the FP16 matrix cores (the automatic kernels).
+bool matrix_sums(const lts_context *c) {
+    if (c->reduce_mode == LTS_REDUCE_SUMMED) return summed_matrix(c->ticks_per_thread, c->lane_exchange != 0);
+    return c->ticks_per_thread == 0 &&
+           (c->reduce_mode == LTS_REDUCE_ATOMIC || (c->induce_slices <= 1 && !c->matrix_cores));
+}
+
 // The buffers of summed_needs are grown by the caller.
 // cells_ready (may be null): recorded behind the charge cells on another stream; awaited before the column sums.
 lts_status run_summed(lts_context *c, const Work &w, const DevHeader &h, int64_t n_slots, float *wave, hipStream_t st,
-                      hipEvent_t cells_ready) {
+                      hipEvent_t cells_ready, SumWork &sw) {
     const DevParams &P = c->P;
     lts_status r;
-    SumWork sw = summed_grid(P, w.n_ev);
+    sw = summed_grid(P, w.n_ev);
     const int64_t nc1 = sw.n_cols + 1;
     if (sw.n_cols > (int64_t)INT32_MAX)
         return fail(c, LTS_ERR_INVALID_ARG, "summed induction: events x sub-pixel columns exceeds 2^31 - 1");
@@ -684,6 +696,11 @@ lts_status run_pipeline(lts_context *c, int32_t n_ev, const uint64_t *event_ids,
     const int64_t mp = c->P.max_packets;
     const bool summed = c->reduce_mode == LTS_REDUCE_SUMMED;
     const int64_t pair_cap = summed ? 1 : std::max<int64_t>(n_pairs, 1);   // the summed induction has no pair lists
+    // settled pixels: the list and the compensations in the order buffer (free after the induction), the tokens behind the
+    // packet counts (zeroed with them)
+    const bool settle = matrix_sums(c);
+    const int64_t n_token = settle ? kSettleSpread * settle_tiles(c->P.nticks) : 0;
+    const int64_t n_comp = settle ? (int64_t)kSettleSpread * c->P.nticks : 0;
     std::vector<Need> needs = {
         {&c->slot_gp, sizeof(int32_t) * (size_t)std::max<int64_t>(n_slots, 1)},
         {&c->slot_off, sizeof(int64_t) * (size_t)(n_slots + 1)},
@@ -693,9 +710,9 @@ lts_status run_pipeline(lts_context *c, int32_t n_ev, const uint64_t *event_ids,
         {&c->pk_tick, sizeof(int32_t) * (size_t)(n_slots * mp)},
         {&c->pk_adc, sizeof(uint16_t) * (size_t)(n_slots * mp)},
         {&c->pk_flag, sizeof(uint8_t) * (size_t)(n_slots * mp)},
-        {&c->pk_off, sizeof(int64_t) * (size_t)(n_slots + 1)},
+        {&c->pk_off, sizeof(int64_t) * (size_t)(n_slots + 1) + sizeof(uint32_t) * (size_t)n_token},
         {&c->scan_tmp, sizeof(int64_t) * (size_t)scan_tmp_needed(n_slots + 1)},
-        {&c->order, sizeof(int32_t) * (size_t)(2 * n_slots + 2 * kOrderBuckets)}};
+        {&c->order, sizeof(int32_t) * (size_t)(std::max<int64_t>(2 * n_slots + 2 * kOrderBuckets, n_slots + n_comp))}};
     if (c->reduce_mode == LTS_REDUCE_SUMMED) summed_needs(c, h, n_slots, n_ev, w.n_seg, needs);
     if (c->reduce_mode == LTS_REDUCE_SORTED && c->induce_slices > 1 && n_slots > 0) {
         const int64_t row_bytes = (int64_t)c->induce_slices * c->P.nticks * (int64_t)sizeof(float);
@@ -725,13 +742,14 @@ lts_status run_pipeline(lts_context *c, int32_t n_ev, const uint64_t *event_ids,
     // The sequence from here to the packets has no host synchronisation in the per-pair and atomic modes, so it can
     // be captured and replayed as one HIP graph (zero fills are kernels, not memset nodes).
     const bool graph = c->use_graph && c->reduce_mode != LTS_REDUCE_SUMMED;
+    SumWork sw;
     auto launch_all = [&](hipStream_t s) -> lts_status {
-        launch_zero(w.pk_off, (int64_t)sizeof(int64_t) * (n_slots + 1), s);
+        launch_zero(w.pk_off, (int64_t)sizeof(int64_t) * (n_slots + 1) + (int64_t)sizeof(uint32_t) * n_token, s);
         {
             StageTimer t(c, s, LTS_STAGE_RASTERIZE);
             launch_slots(P, w, out->pixel_id, out->event_pixel_offsets, s);
             launch_fill_pairs(P, w, s);
-            if (c->reduce_mode == LTS_REDUCE_SORTED) launch_sort_pairs(w, n_slots, s);
+            if (c->reduce_mode == LTS_REDUCE_SORTED || (settle && !summed)) launch_sort_pairs(w, n_slots, s);
         }
         // summed mode: the cells on the side stream, beside the column lists (forked after everything queued so far,
         // joined before the column sums and before anything this call leaves behind)
@@ -758,7 +776,7 @@ lts_status run_pipeline(lts_context *c, int32_t n_ev, const uint64_t *event_ids,
             lts_status r2;
             {
                 StageTimer t(c, s, LTS_STAGE_INDUCE);
-                r2 = run_summed(c, w, h, n_slots, out->current, s, cells_ready);
+                r2 = run_summed(c, w, h, n_slots, out->current, s, cells_ready, sw);
             }
             if (cells_ready) HIP_TRY(c, hipStreamWaitEvent(s, cells_ready, 0));   // also on an early return
             if (r2) return r2;
@@ -776,12 +794,18 @@ lts_status run_pipeline(lts_context *c, int32_t n_ev, const uint64_t *event_ids,
         } else {
             StageTimer t(c, s, LTS_STAGE_INDUCE);
             StageTimer tk(c, s, LTS_STAGE_INDUCE_KERNEL);
-            launch_induce(P, w, T, out->current, c->reduce_mode, n_slots, c->ticks_per_thread, c->lane_exchange != 0,
-                          s);
+            if (c->ticks_per_thread == 0)
+                launch_induce_z(P, w, T, out->current, c->reduce_mode, n_slots, s);
+            else
+                launch_induce(P, w, T, out->current, c->reduce_mode, n_slots, c->ticks_per_thread,
+                              c->lane_exchange != 0, s);
         }
         {
             StageTimer t(c, s, LTS_STAGE_ELECTRONICS);
-            launch_electronics(P, out->current, w.slot_gp, w.event_ids, n_slots, w, s);
+            launch_electronics(P, out->current, w.slot_gp, w.event_ids, n_slots, w, settle ? w.order : nullptr, s);
+            if (settle)
+                launch_settle(P, w, sw, T, out->current, w.slot_gp, w.event_ids, summed, n_slots, w.order,
+                              (uint32_t *)(w.pk_off + n_slots + 1), (float *)(w.order + n_slots), s);
             launch_compact_packets(P, w, n_slots, out->pkt_pixel, out->pkt_tick, out->pkt_adc, out->pkt_flags,
                                    out->cap_packets, out->event_pixel_offsets, out->event_packet_offsets, out->counts,
                                    s);
@@ -1059,6 +1083,12 @@ lts_status lts_set_response(lts_context *c, const float *R, int32_t t_r, int32_t
     if ((r = ensure(c, c->Rexp, sizeof(int32_t) * ncol))) return r;
     launch_table_halves(as<float>(c->Rpad), (int32_t)ncol, col_len, c->Rhalf.p, as<uint16_t>(c->Rhalf) + plane,
                         as<int32_t>(c->Rexp), nullptr);
+    const int32_t njo = (b_y + 7) / 8, trq = (t_r + 15) / 16 * 16;
+    const size_t oct = (size_t)b_x * njo * trq * 8;      // halves of one plane
+    if ((r = ensure(c, c->Roct, 2 * sizeof(uint16_t) * oct))) return r;
+    if ((r = ensure(c, c->Remin, sizeof(int32_t) * (size_t)b_x * njo))) return r;
+    launch_table_octets(as<float>(c->Rpad), b_x, b_y, t_r, col_len, trq, as<int32_t>(c->Rexp), c->Roct.p,
+                        as<uint16_t>(c->Roct) + oct, as<int32_t>(c->Remin), nullptr);
     DevParams tab = c->P;                               // (the context's own are set when nothing can fail any more)
     tab.t_r = t_r;
     tab.bx = b_x;
@@ -1071,6 +1101,7 @@ lts_status lts_set_response(lts_context *c, const float *R, int32_t t_r, int32_t
     } else {
         free_buf(c->Rclass);
     }
+    HIP_TRY(c, allow_z_lds());
     HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipStreamSynchronize(nullptr));
     c->table_host.assign(R, R + (size_t)t_r * b_x * b_y);
@@ -1202,7 +1233,7 @@ lts_status lts_stage_electronics(lts_context *c, uint64_t event_id, const int32_
     w.scan_tmp = c->scan_tmp.p;
     w.slot_gp = const_cast<int32_t *>(pixel_ids);
     w.disabled = c->has_mask ? as<uint8_t>(c->mask) : nullptr;
-    launch_electronics(c->P, current, pixel_ids, as<uint64_t>(c->ev_ids), n_pix, w, st);
+    launch_electronics(c->P, current, pixel_ids, as<uint64_t>(c->ev_ids), n_pix, w, nullptr, st);
     launch_compact_packets(c->P, w, n_pix, out->pkt_pixel, out->pkt_tick, out->pkt_adc, out->pkt_flags, out->cap_packets,
                            nullptr, nullptr, out->counts, st);
     HIP_TRY(c, hipGetLastError());
@@ -1251,7 +1282,7 @@ lts_status lts_stage_electronics_noalloc(lts_context *c, uint64_t event_id, cons
     launch_zero(w.report, sizeof(double) * 5, st);
     launch_zero(w.pk_off, 8 * (n_pix + 1), st);
     launch_store_u64((uint64_t *)(base + o_ev), event_id, st);
-    launch_electronics(c->P, current, pixel_ids, (const uint64_t *)(base + o_ev), n_pix, w, st);
+    launch_electronics(c->P, current, pixel_ids, (const uint64_t *)(base + o_ev), n_pix, w, nullptr, st);
     launch_compact_packets(c->P, w, n_pix, out->pkt_pixel, out->pkt_tick, out->pkt_adc, out->pkt_flags, out->cap_packets,
                            nullptr, nullptr, out->counts, st);
     HIP_TRY(c, hipGetLastError());
@@ -1313,7 +1344,7 @@ static lts_status stage_pairs(lts_context *c, uint64_t event_id, const lts_segme
     if (pair_segment || pair_pixel) launch_pair_list(c->P, w, h.n_slots, pair_segment, pair_pixel, st);
     if (pair_current) {
         Table T = table_of(c);
-        launch_induce_pairs(c->P, w, T, h.n_slots, pair_current, st);
+        launch_induce_z_pairs(c->P, w, T, h.n_slots, pair_current, st);
     }
     HIP_TRY(c, hipGetLastError());
     return LTS_OK;

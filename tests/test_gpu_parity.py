@@ -992,3 +992,43 @@ def test_summed_matrix_tile_edges(lt, orc, torch, n_ticks, t_r, b_x, b_y, n_sub)
     h, r, e, _ = check_event(lt, orc, _edge_workload(n_ticks, t_r, b_x, b_y, n_sub), mode=2)
     print(f"summed edges {n_ticks}/{t_r}/{b_x}x{b_y}/{n_sub}: pixels {len(r['pixels'])} max e_p {e.max():.2e}")
     assert e.max() <= TOL_EDGE
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n_ticks,t_r,b_x,b_y,n_sub", [(1, 1, 1, 1, 2), (130, 17, 2, 9, 4), (255, 37, 5, 3, 10),
+                                                       (256, 256, 9, 8, 4), (1537, 1001, 20, 31, 10)])
+def test_group_product_edges(lt, orc, torch, mode, n_ticks, t_r, b_x, b_y, n_sub):
+    """Per-pair induction as group products where groups, octets, stages and tiles end (more than 16 segments of a pixel,
+    groups cut by their span, reaches of 1 to 4 octets, tables and windows around 16 and 32 ticks); pair by pair, the
+    materialised form adds up to the same."""
+    w = _edge_workload(n_ticks, t_r, b_x, b_y, n_sub)
+    h, r, e, _ = check_event(lt, orc, w, mode=mode)
+    assert e.max() <= TOL_EDGE
+    if mode == 0:
+        segs = lt.to_device(w.events[0])
+        c = lt.Context.from_workload(w)
+        _, pix, cur = c.stage_induce(segs, w.event_ids[0])
+        ids, red = c.stage_reduce(pix, cur)
+        red, ids = red.cpu().numpy().astype(np.float64), ids.cpu().numpy()
+        row = {int(p): k for k, p in enumerate(h["pixel_id"])}
+        full = np.asarray(h["current"], np.float64)
+        diff = max(np.abs(red[k] - full[row[int(p)]]).max() for k, p in enumerate(ids))
+        assert diff <= 2 * TOL_EDGE * np.abs(full).max()
+        c.close()
+
+
+@pytest.mark.parametrize("cfg,ev", [(1, 0), (1, 1), (3, 0)])
+def test_packets_do_not_depend_on_the_summing_units(lt, torch, cfg, ev):
+    """Decisions that rounding could turn are settled in the vector kernels' summation order: the matrix-core forms give
+    the same packets and flags, and a pixel with a flagged packet has the vector kernels' current bit for bit."""
+    w = W.make_workload(cfg, n_events=2)
+    _, a = run_gpu(lt, w, ev, 0, rt=0)
+    _, b = run_gpu(lt, w, ev, 0, rt=4)
+    for k in ("pixel_id", "pkt_pixel", "pkt_tick", "pkt_adc", "pkt_flags"):
+        assert np.array_equal(a[k], b[k])
+    flagged = np.unique(a["pkt_pixel"][(a["pkt_flags"] & 3) != 0])
+    rows = np.searchsorted(a["pixel_id"], flagged)
+    assert np.array_equal(a["current"][rows], b["current"][rows])
+    _, c = run_gpu(lt, w, ev, 1, rt=0)
+    assert len(c["pkt_adc"]) == len(a["pkt_adc"])
+    print(f"config {cfg} event {ev}: {len(a['pkt_adc'])} packets, {len(flagged)} flagged pixels")
