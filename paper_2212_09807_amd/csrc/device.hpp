@@ -141,8 +141,8 @@ __device__ __forceinline__ void point_local(const SegInfo &g, const DevParams &P
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        uint32_t hi0 = __umulhi(0xD2511F53u, c.x), lo0 = 0xD2511F53u * c.x;
-        uint32_t hi1 = __umulhi(0xCD9E8D57u, c.z), lo1 = 0xCD9E8D57u * c.z;
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c.x, p1 = (uint64_t)0xCD9E8D57u * c.z;
+        const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0, hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
         c = make_uint4(hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0);
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
@@ -151,14 +151,28 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
 }
 
 // Standard normal for (pixel, tick, event, stream): Box-Muller on the first two words.  Counter layout:
-// (pixel id, tick, event id low word, (event id high word << 4) | stream).
+// (pixel id, tick, event id low word, (event id high word << 4) | stream).  The key is taken as unknown at each call: else
+// the compiler keeps the 20 bumped keys in registers across a caller's loop.
+__device__ __forceinline__ void noise_words(const DevParams &P, uint32_t pixel, uint32_t tick, uint64_t event,
+                                            uint32_t stream, float &u0, float &u1) {
+    uint4 c = make_uint4(pixel, tick, (uint32_t)event, (uint32_t)((event >> 32) << 4) | (stream & 15u));
+    uint32_t k0 = P.key0, k1 = P.key1;
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    uint4 x = philox4x32_10(c, k0, k1);
+    u0 = fmaf((float)x.x, 0x1p-32f, 0x1p-33f);
+    u1 = fmaf((float)x.y, 0x1p-32f, 0x1p-33f);
+}
+__device__ __forceinline__ float box_muller(float u0, float u1) { return sqrtf(-2.0f * logf(u0)) * cospif(2.0f * u1); }
 __device__ __forceinline__ float noise_normal(const DevParams &P, uint32_t pixel, uint32_t tick, uint64_t event,
                                               uint32_t stream) {
-    uint4 c = make_uint4(pixel, tick, (uint32_t)event, (uint32_t)((event >> 32) << 4) | (stream & 15u));
-    uint4 x = philox4x32_10(c, P.key0, P.key1);
-    float u0 = fmaf((float)x.x, 0x1p-32f, 0x1p-33f);
-    float u1 = fmaf((float)x.y, 0x1p-32f, 0x1p-33f);
-    return sqrtf(-2.0f * logf(u0)) * cospif(2.0f * u1);
+    float u0, u1;
+    noise_words(P, pixel, tick, event, stream, u0, u1);
+    return box_muller(u0, u1);
+}
+// Whether the normal of u0 surely lies below z: its radius sqrt(-2 ln u0) does (z^2 / 2 > -ln u0 by 1e-3, far more than
+// the rounding of either).  One exponential instead of the logarithm, root and cosine.
+__device__ __forceinline__ bool normal_below(float u0, float z) {
+    return z > 0.0f && u0 > 1.001f * __builtin_amdgcn_exp2f(-0.72134752f * z * z);
 }
 
 // Drift of sample point mu at its own drift time (per-point mode): charge Q_R / N * exp(-t / tau) and the

@@ -570,6 +570,7 @@ __device__ void mc_cells(const DevParams &P, const SegInfo &g, uint32_t seg, uin
 // 2 x 2 blocks of tiles in turn, so every A value serves two tiles and every B value two; out-of-box rows, ticks and
 // points contribute zeros and are not written.  `first` writes the pass's sums, otherwise they are added.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ void cells_mfma(const float *fx, const float *fy, const float *ft, int32_t nu, int32_t nv,
                                            int32_t nap, int32_t np, float q, bool first, float *out) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -3475,6 +3476,31 @@ void launch_induce_summed(const DevParams &P, const Work &w, const SumWork &sw, 
 // relative term.  (One thread per pixel walking the ticks in order was 4.4x slower: too few wavefronts, and a
 // dependent load per tick.)
 
+// Most chunks have no event: no sample is due, no reset falls into them, and the carried charge plus the sum of the
+// chunk's magnitudes stays below the threshold by more than the margins and any noise draw, or at least the 64 draws of
+// the chunk.  Such a chunk needs only the two totals its last lane's prefix sums would hold, which the same tree of
+// additions gives without a scan: every lane loads 4 ticks, 64 lanes four chunks, and a row of 16 lanes adds up a chunk.
+// What bounds the kernel is its instructions, about 250 for a scanned chunk, 100 for one settled by its draws, 30 for one
+// that needs none (15,000 pixels x 3000 ticks with 4 pulses and noise: 239 us, every chunk scanned 318; 250 pixels of a
+// track 19 us, scanned 46).
+
+// Value of the lane whose number is at / 4 (mod 64).
+__device__ __forceinline__ float lane_from(int at, float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(at, __builtin_bit_cast(int, x)));
+}
+
+// Sum over the lane's row of 16, in every lane, paired as a prefix sum over its ticks pairs them.
+__device__ __forceinline__ float row_tree(float x) {
+    auto add = [&](auto c) {
+        x += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(c)::value, 0xf, 0xf,
+                                                                true));
+    };
+    add(std::integral_constant<int, 0xB1>());            // lane ^ 1, lane ^ 2 (quads), the other quad, the other eight
+    add(std::integral_constant<int, 0x4E>());
+    add(std::integral_constant<int, 0x141>());
+    add(std::integral_constant<int, 0x140>());
+    return x;
+}
 
 // With `list` the pixels are the header's n_settle entries of it (a second pass over settled currents; the report's sum of
 // currents is the first pass's).  With `settle` a pixel one of whose decisions - a crossing, a code, or the margin that
@@ -3505,26 +3531,74 @@ __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *_
         const bool off = disabled && disabled[pid];                   // disabled channel: no packets
         const uint64_t ev = ev_ids[e];
         const float *w = wave + slot * NT;
+        const float disc_inv = P.sig_disc > 0.0f ? 1.0f / P.sig_disc : 0.0f;
         const float reset0 = P.sig_reset > 0.0f ? P.sig_reset * noise_normal(P, pid, kTickInitial, ev, STREAM_RESET)
                                                 : 0.0f;
         float Qb = reset0, Qbc = 0.0f, Ab = 0.0f;                     // carried charge (Kahan pair) and |charge|
         bool pending = false, uncertain = false, done = off, close = false;
         int32_t ns = 0, ready = 0, last = -(1 << 28), cnt = 0, dropped = 0, over = 0;
         const int64_t obase = slot * P.max_packets;
+        auto carry = [&](float q, float a) {                          // a segment's charge into the next chunk
+            const float y = q - Qbc, t = Qb + y;
+            Qbc = (t - Qb) - y;
+            Qb = t;
+            Ab += a;
+        };
         double rs = 0.0;
+        // four chunks at a time, lane l with ticks 4 l .. + 3 of them: row k of 16 lanes holds chunk k
+        auto load = [&](int32_t g0) {
+            floatx4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+            const int32_t n = g0 + 4 * lane;
+            if (n + 3 < NT) return (floatx4)(*(const floatx4u *)(w + n));
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (n + k < NT) v[k] = w[n + k];
+            return v;
+        };
+        floatx4 ahead = load(0);
+        float tot = 0.0f, mag = 0.0f;
+        int32_t reset = RP;                                           // the next periodic reset at or after the chunk
         for (int32_t n0 = 0; n0 < NT; n0 += 64) {
+            if ((n0 & 255) == 0) {
+                const floatx4 v = ahead;
+                ahead = load(n0 + 256);
+                rs += ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]);
+                tot = row_tree((v[0] + v[1]) + (v[2] + v[3]));
+                mag = row_tree((fabsf(v[0]) + fabsf(v[1])) + (fabsf(v[2]) + fabsf(v[3])));
+            }
+            if (done) continue;
+            const float ct = lane_value(tot, (n0 & 255) / 4), ca = lane_value(mag, (n0 & 255) / 4);
+            while (RP > 0 && reset < n0) reset += RP;
+            bool idle;                                                // no sample, reset or close comparison in the chunk
+            if (pending) {
+                idle = ns - n0 >= 64;
+            } else {
+                const float q0 = Qb - Qbc;
+                const float most = P.eps_abs + P.eps_rel * ((Ab + ca) + (fabsf(q0) + ca) + P.thr);
+                const float room = (P.thr - (q0 + 1.00001f * ca)) - 2.5f * most;     // to the threshold, at least
+                const bool no_reset = RP <= 0 || reset - n0 >= 64;
+                idle = no_reset && (ready - n0 >= 64 || room > kNormalBound * P.sig_disc);
+                if (!idle && no_reset && room * disc_inv > 3.25f) {   // few chunks have a draw that far out
+                    float u0, u1;
+                    noise_words(P, pid, (uint32_t)(n0 + lane), ev, STREAM_DISC, u0, u1);
+                    idle = !__ballot(!normal_below(u0, room * disc_inv));
+                }
+            }
+            if (idle) {
+                carry(ct, ca);
+                continue;
+            }
             const int32_t n = n0 + lane;
             const float x = n < NT ? w[n] : 0.0f;
-            rs += (double)x;
-            if (done) continue;
             float sx, sa;                                             // prefix sums over lanes s..lane
             auto scan = [&](int32_t s) {
                 sx = lane >= s ? x : 0.0f;
                 sa = fabsf(sx);
 #pragma unroll
                 for (int d = 1; d < 64; d <<= 1) {
-                    const float yx = __shfl_up(sx, d), ya = __shfl_up(sa, d);
-                    if (lane >= d) { sx += yx; sa += ya; }
+                    const float yx = lane_from(4 * lane + 256 - 4 * d, sx), ya = lane_from(4 * lane + 256 - 4 * d, sa);
+                    sx += lane >= d ? yx : 0.0f;
+                    sa += lane >= d ? ya : 0.0f;
                 }
             };
             auto restart = [&](uint32_t tick) {                       // integrator reset
@@ -3587,10 +3661,13 @@ __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *_
                 float m = 0.0f, eps = 0.0f;
                 if (cmp) {
                     float disc = 0.0f;
-                    if (P.sig_disc > 0.0f && Ql + kNormalBound * P.sig_disc >= P.thr)
-                        disc = P.sig_disc * noise_normal(P, pid, (uint32_t)n, ev, STREAM_DISC);
-                    m = (Ql + disc) - P.thr;
                     eps = P.eps_abs + P.eps_rel * (Al + fabsf(Ql) + P.thr);
+                    if (P.sig_disc > 0.0f && Ql + kNormalBound * P.sig_disc >= P.thr) {
+                        float u0, u1;
+                        noise_words(P, pid, (uint32_t)n, ev, STREAM_DISC, u0, u1);
+                        if (!normal_below(u0, ((P.thr - Ql) - 2.5f * eps) * disc_inv)) disc = P.sig_disc * box_muller(u0, u1);
+                    }
+                    m = (Ql + disc) - P.thr;
                 }
                 const uint64_t cross = __ballot(cmp && m >= 0.0f), near = __ballot(cmp && fabsf(m) < eps);
                 const uint64_t near2 = SETTLE ? __ballot(cmp && fabsf(m) < 2.0f * eps) : 0;
@@ -3614,12 +3691,7 @@ __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *_
                 }
                 break;
             }
-            if (!done && s < jn) {                                    // carry the segment's charge into the next chunk
-                const float y = lane_value(sx, jn - 1) - Qbc, t = Qb + y;
-                Qbc = (t - Qb) - y;
-                Qb = t;
-                Ab += lane_value(sa, jn - 1);
-            }
+            if (!done && s < jn) carry(lane_value(sx, jn - 1), lane_value(sa, jn - 1));
         }
         if (lane == 0) pk_cnt[slot] = off ? 0 : cnt;
         if (!list) add_report(report, e, 2, rs, true);
@@ -3668,7 +3740,6 @@ constexpr int32_t kSettleWG = 1024, kSettleWaves = kSettleWG / 64, kSettleTile =
 // gives the lane's lag-0 entry of the next table column, its cell column and that one's blocks of kAC ticks.  A block needs
 // 8 table values more than the one before (they are read as two 16-byte words, with the block's cells, while the block
 // before runs): the reads, not the products, bound the plain loop, which takes 11 words of 4 bytes.
-typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 template <class Next>
 __device__ __forceinline__ void chain4(Next next, float (&acc)[4]) {
     const float *col;

@@ -604,6 +604,32 @@ def test_electronics_walk_edges_vs_oracle(lt, orc, torch, period, hold, spacing)
         assert len(np.unique(h["pkt_pixel"])) == len(h["pkt_pixel"])
 
 
+@pytest.mark.parametrize("n_ticks,period", [(1, 0), (63, 0), (64, 50), (65, 0), (255, 0), (257, 64), (1000, 0), (1000, 300)])
+def test_electronics_idle_chunks_vs_oracle(lt, orc, torch, n_ticks, period):
+    """Charges that hold still 0.2 to 8 noise widths below the threshold: chunks that need no draw, that their draws
+    settle, and that have a crossing, in windows that end within a chunk, a group of four and a loaded word."""
+    w = W.config(5)
+    w.electronics.reset_period = period
+    w.readout = W.Readout(n_x=32, n_y=32, n_ticks=n_ticks)
+    el = w.electronics
+    rng = np.random.default_rng(n_ticks + period)
+    n = 256
+    cur = rng.normal(0.0, 0.01, (n, n_ticks)) * el.sigma_disc
+    cur[:, 0] += el.threshold - el.sigma_disc * np.linspace(0.2, 8.0, n)
+    cur[::3, n_ticks // 2] += 3.0 * el.sigma_disc
+    cur[::5, n_ticks - 1] -= 2.0 * el.threshold
+    cur32 = cur.astype(np.float32)
+    pix = np.arange(n, dtype=np.int32)
+    ctx = lt.Context.from_workload(w)
+    h = ctx.stage_electronics(9, torch.tensor(pix, device="cuda"), torch.tensor(cur32, device="cuda")).host()
+    pk, st, uf = orc.electronics(el, w.readout, 9, pix, cur32.astype(np.float64), EPS_REL, EPS_ABS, with_uncertain=True)
+    cmp_, flg, bad = compare_packets(h, pix, pk, uf)
+    print(f"idle chunks {n_ticks} {period}: compared {cmp_} flagged {flg} dropped {h['counts'][2]} / {st[0]}")
+    assert not bad, bad[:3]
+    assert abs(int(h["counts"][2]) - int(st[0])) <= int((uf < n_ticks).sum())
+    assert float(h["report"][0][2]) == pytest.approx(float(cur32.astype(np.float64).sum()), rel=1e-12)
+
+
 # ----------------------------------------------------------------------------------------------- batching
 
 @pytest.mark.parametrize("mode", [0, 2])
