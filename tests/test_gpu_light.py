@@ -83,6 +83,27 @@ def test_light_ragged_and_degenerate_shapes(lt, OL, torch):
     check(lt, OL, torch, lp2, ipe, W.light_response(n_resp=77), W.light_noise_amplitudes(n_freq=300, sigma=1.0), 100)
 
 
+@pytest.mark.parametrize("taps,n_ticks", [(511, 1600), (512, 512), (512, 1537), (513, 2053), (1000, 5001), (8193, 17000),
+                                          (9000, 30011)])
+def test_light_decay_blocks(lt, OL, torch, taps, n_ticks):
+    """The scintillation sum by recursions where its blocks, wavefronts and passes end, and the direct sum below it; light
+    at both edges of a window of taps, dark ticks exactly zero."""
+    lp = dataclasses.replace(W.Light(), n_det=2, n_ticks=n_ticks, group=1, max_trig=0, trunc=(taps - 0.5) / 1600.0)
+    assert OL.taps(lp) == taps
+    rng = np.random.default_rng(taps + n_ticks)
+    ipe = np.zeros((2, n_ticks), np.float32)
+    ipe[0] = rng.uniform(0.0, 0.05, n_ticks)
+    ipe[1, [0, n_ticks // 3, min(taps, n_ticks - 1), n_ticks - 1]] = (200.0, 3.0, 40.0, 1.0)
+    check(lt, OL, torch, lp, ipe, W.light_response(n_resp=9), np.zeros(0, np.float32), 3)
+    one = np.zeros((2, n_ticks), np.float32)
+    one[:, n_ticks // 4] = 1.0
+    sim = lt.LightSim(lp, W.light_response(n_resp=9), np.zeros(0, np.float32))
+    mu = sim.simulate(torch.from_numpy(one).cuda(), 1, keep_mu=True)["mu"].cpu().numpy()
+    t = np.arange(n_ticks)
+    assert np.array_equal(mu[0] > 0, (t >= n_ticks // 4) & (t < n_ticks // 4 + taps))
+    sim.close()
+
+
 def test_light_invalid_parameters(lt, torch):
     lp = W.Light()
     r, a = W.light_response(), W.light_noise_amplitudes()
