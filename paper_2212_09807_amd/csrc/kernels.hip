@@ -2238,35 +2238,7 @@ __global__ __launch_bounds__(kWG) void k_sum_merge(int64_t n_slots, SumWork sw) 
             if (st) {
                 const int64_t g = ng + __builtin_popcountll(starts & ((1ull << lane) - 1ull));
                 sw.mrec[g] = multi ? PieceRef{r.a0, L, sw.nS8 + (uint32_t)(moff / kAC), bin | mexp << kBinBits} : r;
-            }
-            uint64_t mm = __ballot(multi);
-            while (mm) {                                // each merged run: its charge, lanes over its ticks
-                const int i = __builtin_ctzll(mm);
-                mm &= mm - 1ull;
-                const int32_t lo = __builtin_amdgcn_readlane(r.a0, i);
-                const int32_t ke = __builtin_amdgcn_readlane(nxt, i);
-                const int32_t lp = __builtin_amdgcn_readlane(Lp, i);
-                const int64_t off = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(moff >> 32), i) << 32) |
-                                              (uint32_t)__builtin_amdgcn_readlane((int)moff, i));
-                for (int32_t t0 = 0; t0 < lp; t0 += 64) {
-                    float v = 0.0f;
-                    for (int32_t k0 = i; k0 < ke; k0 += 4) {  // members in list order, four loads in flight
-                        float x[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            x[q] = 0.0f;
-                            const int32_t k = min(k0 + q, 63);
-                            const int32_t ma = __builtin_amdgcn_readlane(r.a0, k);
-                            const int32_t mn = __builtin_amdgcn_readlane(r.na, k);
-                            const uint32_t mc = (uint32_t)__builtin_amdgcn_readlane((int)r.cell8, k);
-                            const int32_t o = lo + t0 + lane - ma;
-                            if (k0 + q < ke && o >= 0 && o < mn) x[q] = sw.S[(int64_t)mc * kAC + o];
-                        }
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) v += x[q];  // adding an exact zero leaves v unchanged
-                    }
-                    if (t0 + lane < lp) sw.Sm[off + t0 + lane] = v;
-                }
+                sw.mstart[g] = c0 + lane;
             }
         }
         ng += __builtin_popcountll(starts);
@@ -2276,13 +2248,59 @@ __global__ __launch_bounds__(kWG) void k_sum_merge(int64_t n_slots, SumWork sw) 
         sw.mlist_off[slot] = ng;
         sw.m_off[slot] = nm;
     }
+    if (FILL && lane == 0 && slot == n_slots - 1) sw.mstart[ng] = pe;
 }
 
-void launch_sum_merge(const SumWork &sw, int64_t n_slots, bool fill, hipStream_t st) {
+// The merged records' charges, members in list order: 8 lanes a record, over its ticks.  A pixel's runs are independent of
+// each other, so they are spread over the chip by record (in the pass above, a wavefront per pixel, the pixels with the
+// longest lists kept it running).  A 20,000-segment event has 13.5 million records of some 30 ticks, whose charges (1.6 GB)
+// are what bounds it: the pass and this kernel take 245 + 636 us instead of 1424, for a 500-segment event 37 + 18 instead of
+// 345 (16 lanes x 4 ticks a record: 848, 4 x 8: 740).
+constexpr int32_t kMergeLanes = 8, kMergeTicks = 8;   // ticks a lane at a time
+__global__ __launch_bounds__(kWG) void k_sum_merged(int64_t n_rec, SumWork sw) {
+    const int lane = threadIdx.x % kMergeLanes;
+    const int64_t g = (int64_t)blockIdx.x * (kWG / kMergeLanes) + threadIdx.x / kMergeLanes;
+    if (g >= n_rec) return;
+    const PieceRef m = sw.mrec[g];
+    if (m.cell8 < sw.nS8) return;                       // a single piece
+    const PieceRef *rec = sw.rec + sw.mstart[g];
+    const int32_t n_mem = (int32_t)(sw.mstart[g + 1] - sw.mstart[g]), lp = (m.na + kAC - 1) / kAC * kAC;
+    float *out = sw.Sm + (int64_t)(m.cell8 - sw.nS8) * kAC;
+    for (int32_t t0 = lane; t0 < lp; t0 += kMergeLanes * kMergeTicks) {
+        float v[kMergeTicks];
+#pragma unroll
+        for (int i = 0; i < kMergeTicks; ++i) v[i] = 0.0f;
+        for (int32_t k = 0; k < n_mem; k += 2) {         // two members' loads in flight
+            const PieceRef r0 = rec[k], r1 = rec[min(k + 1, n_mem - 1)];
+            const uint32_t o0 = (uint32_t)(m.a0 + t0 - r0.a0), n0 = (uint32_t)r0.na;
+            const uint32_t o1 = (uint32_t)(m.a0 + t0 - r1.a0), n1 = k + 1 < n_mem ? (uint32_t)r1.na : 0u;
+            const float *c0 = sw.S + (int64_t)r0.cell8 * kAC, *c1 = sw.S + (int64_t)r1.cell8 * kAC;
+            float x0[kMergeTicks], x1[kMergeTicks];
+#pragma unroll
+            for (int i = 0; i < kMergeTicks; ++i) {
+                const uint32_t d = (uint32_t)(kMergeLanes * i);
+                x0[i] = o0 + d < n0 ? c0[o0 + d] : 0.0f;
+                x1[i] = o1 + d < n1 ? c1[o1 + d] : 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < kMergeTicks; ++i) v[i] = (v[i] + x0[i]) + x1[i];   // an exact zero leaves v unchanged
+        }
+#pragma unroll
+        for (int i = 0; i < kMergeTicks; ++i)
+            if (t0 + kMergeLanes * i < lp) out[t0 + kMergeLanes * i] = v[i];
+    }
+}
+
+void launch_sum_merge(const SumWork &sw, int64_t n_slots, int64_t n_rec, hipStream_t st) {
     if (n_slots <= 0) return;
     const unsigned g = (unsigned)((n_slots + kWG / 64 - 1) / (kWG / 64));
-    if (fill) k_sum_merge<true><<<g, kWG, 0, st>>>(n_slots, sw);
-    else k_sum_merge<false><<<g, kWG, 0, st>>>(n_slots, sw);
+    if (n_rec < 0) {
+        k_sum_merge<false><<<g, kWG, 0, st>>>(n_slots, sw);
+        return;
+    }
+    k_sum_merge<true><<<g, kWG, 0, st>>>(n_slots, sw);
+    constexpr int64_t per = kWG / kMergeLanes;
+    if (n_rec > 0) k_sum_merged<<<(unsigned)((n_rec + per - 1) / per), kWG, 0, st>>>(n_rec, sw);
 }
 
 // Summed induction, one wavefront per work unit (active pixel, tile of kTileTicks ticks): lane t owns ticks

@@ -99,6 +99,7 @@ struct SumWork {
     int64_t *mlist_off = nullptr;            // [n_slots + 1] records per active pixel after the mirror merge, offsets
     int64_t *m_off = nullptr;                // [n_slots + 1] merged charge floats per active pixel, then offsets
     PieceRef *mrec = nullptr;                // [n_mlist] the merged records
+    int64_t *mstart = nullptr;               // [n_mlist + 1] first list entry of each merged record
     float *Sm = nullptr;                     // [n_m] charges of the merged records (padded to kAC)
     uint32_t nS8 = 0;                        // S floats / kAC: cell8 at or above it points into Sm
     int32_t align_res = 0;                   // first tick of every column interval, mod 8 (set by the kernel choice)
@@ -118,7 +119,8 @@ void launch_sum_pieces(const DevParams &P, const Work &w, const SumWork &sw, hip
 void launch_sum_lists_count(const DevParams &P, const Work &w, const SumWork &sw, int64_t n_slots, hipStream_t st);
 void launch_sum_lists_fill(const DevParams &P, const Work &w, const SumWork &sw, int64_t n_slots, int64_t n_list,
                            hipStream_t st);                                                    // + records
-void launch_sum_merge(const SumWork &sw, int64_t n_slots, bool fill, hipStream_t st);          // mirror merge
+// mirror merge: counts (n_rec < 0), or the n_rec records and their charges
+void launch_sum_merge(const SumWork &sw, int64_t n_slots, int64_t n_rec, hipStream_t st);
 // largest-first pixel order of the summed induction (null when the chosen kernel takes pixels in slot order)
 const int32_t *launch_summed_order(const Work &w, const SumWork &sw, int64_t n_slots, int32_t rt, bool shift,
                                    hipStream_t st);

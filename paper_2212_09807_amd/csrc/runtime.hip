@@ -574,7 +574,7 @@ lts_status run_summed(lts_context *c, const Work &w, const DevHeader &h, int64_t
     launch_sum_lists_fill(P, w, sw, n_slots, tot[0], st);
     // mirror merge: sizes of the merged records and charges, then the records
     sw.nS8 = (uint32_t)(tot[2] / kAC);
-    launch_sum_merge(sw, n_slots, false, st);
+    launch_sum_merge(sw, n_slots, -1, st);
     scan_exclusive_i64(sw.mlist_off, n_slots + 1, nullptr, tmp, st);
     scan_exclusive_i64(sw.m_off, n_slots + 1, nullptr, tmp, st);
     int64_t mt[2] = {0, 0};
@@ -583,12 +583,13 @@ lts_status run_summed(lts_context *c, const Work &w, const DevHeader &h, int64_t
     HIP_TRY(c, hipStreamSynchronize(st));
     if (tot[2] / kAC + mt[1] / kAC >= (int64_t)UINT32_MAX)
         return fail(c, LTS_ERR_CAPACITY, "summed induction: too many summed charge values for one call");
-    if ((r = grow(c, h, {{&c->mrec, sizeof(PieceRef) * (size_t)std::max<int64_t>(mt[0], 1)},
+    if ((r = grow(c, h, {{&c->mrec, sizeof(PieceRef) * (size_t)mt[0] + sizeof(int64_t) * (size_t)(mt[0] + 1)},
                          {&c->Sm, sizeof(float) * (size_t)(mt[1] + kCellSlack)}})))
         return r;
     sw.mrec = as<PieceRef>(c->mrec);
+    sw.mstart = (int64_t *)(sw.mrec + mt[0]);
     sw.Sm = as<float>(c->Sm);
-    launch_sum_merge(sw, n_slots, true, st);
+    launch_sum_merge(sw, n_slots, mt[0], st);
     Table T = table_of(c);
     const int32_t *order = launch_summed_order(w, sw, n_slots, c->ticks_per_thread, c->lane_exchange != 0, st);
     StageTimer tk(c, st, LTS_STAGE_INDUCE_KERNEL);
