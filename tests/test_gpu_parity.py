@@ -650,6 +650,36 @@ def test_batch_equals_single_events(lt, torch, mode):
         np.testing.assert_allclose(b["report"][e], s["report"][0], rtol=1e-12, atol=1e-9)
 
 
+@pytest.mark.parametrize("n,per_point", [(1, 0), (255, 1), (256, 0)])
+def test_cells_are_the_same_in_any_workgroup(lt, torch, n, per_point):
+    """Charge cells by 1024 threads a segment (few segments) and by 256 (the same events five times in a batch): the same
+    currents bit for bit."""
+    w = W.make_workload(1, n_events=1)
+    w.physics.per_point = per_point
+    e = w.events[0]
+    part = dataclasses.replace(e, **{f.name: getattr(e, f.name)[:n] for f in dataclasses.fields(e)
+                                     if isinstance(getattr(e, f.name), np.ndarray)})
+    ctx = lt.Context.from_workload(w)
+    one = ctx.simulate(lt.to_device(part), event_id=3).host()
+    k = 5 if n > 1 else 300
+    b = ctx.simulate_batch(lt.to_device(W.Segments.concat([part] * k)), np.arange(k + 1) * part.n, [3] * k).host()
+    po = b["event_pixel_offsets"]
+    for i in (0, k - 1):
+        assert np.array_equal(b["pixel_id"][po[i]:po[i + 1]], one["pixel_id"])
+        assert np.array_equal(b["current"][po[i]:po[i + 1]], one["current"])
+
+
+@pytest.mark.parametrize("n,draws", [(1, 471), (1, 472), (6, 2)])
+def test_draw_counts_in_any_width(lt, orc, torch, n, draws):
+    """Hits of 139 points x 471 draws fit in 16 bits (two cells a word), of 472 draws they need not."""
+    w = W.make_workload(1, n_events=1)
+    w.physics.mc_draws = draws
+    e = w.events[0]
+    w.events[0] = dataclasses.replace(e, **{f.name: getattr(e, f.name)[:n] for f in dataclasses.fields(e)
+                                            if isinstance(getattr(e, f.name), np.ndarray)})
+    check_event(lt, orc, w, mode=0)
+
+
 def test_graph_replay_equals_direct_launches(lt, torch):
     """Calls replayed as HIP graphs (updated in place between events of different sizes, re-instantiated when the
     launch structure changes) give the same results as direct launches, with the program's own GPU work and
