@@ -86,6 +86,7 @@ struct DevHeader {
     uint32_t n_settle;                      // pixels with a decision too close to settle on the matrix cores' currents
     uint32_t settle_work;                   // their dynamic work counter
     int32_t _pad;
+    int64_t sum_sizes[2];                   // sizes the summed induction reads back on the way
 };
 
 // ------------------------------------------------------------------------------------------------ helpers

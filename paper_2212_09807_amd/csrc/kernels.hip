@@ -66,96 +66,145 @@ __device__ __forceinline__ int find_event(const int64_t *off, int n_ev, int64_t 
 }
 
 // ================================================================================================= scans
-// Exclusive scan of int64 / uint64 arrays: per-tile reduce, scan of tile sums (one workgroup), per-tile scan.
+// Exclusive scans of one or two 64-bit arrays of the same length or not (blockIdx.y); an array's last element is taken as 0,
+// so that it receives the total, which also goes to `total` (and its upper part to `total_hi`, for the pixel counts).  With
+// `mark` every count > 0 gets a one in the bits above 40, so one scan yields pair offsets and slot indices.  Short arrays
+// take one workgroup and one launch each, or together (a launch costs more than their scan); longer ones a reduction per
+// tile, a scan of the tiles' sums and a scan per tile.
 constexpr int kScanPT = 8;
 constexpr int kScanTile = kWG * kScanPT;
+constexpr int kScanOneWG = 1024;
+constexpr int64_t kScanOne = 16384;                     // elements of an array that one workgroup takes: two passes
 
-template <typename T>
-__device__ __forceinline__ T block_exclusive(T v, T *lds, T &total) {
+struct ScanJob {
+    uint64_t *data;
+    int64_t n;
+    int64_t *total, *total_hi;
+    bool mark;
+    __device__ __forceinline__ uint64_t at(int64_t i) const {
+        const uint64_t v = i < n - 1 ? data[i] : 0;
+        return mark && v ? v | (1ull << 40) : v;
+    }
+    __device__ __forceinline__ void put(int64_t i, uint64_t v) const {
+        data[i] = v;
+        if (i == n - 1 && total) {
+            *total = (int64_t)(total_hi ? v & kMask40 : v);
+            if (total_hi) *total_hi = (int64_t)(v >> 40);
+        }
+    }
+};
+struct ScanJobs {
+    ScanJob job[2];
+};
+
+template <int WG>
+__device__ __forceinline__ uint64_t block_exclusive(uint64_t v, uint64_t *lds, uint64_t &total) {
     // wavefront inclusive scan
     const int lane = lane_id(), wv = threadIdx.x >> 6;
-    T x = v;
+    uint64_t x = v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        T y = __shfl_up(x, o);
+        const uint64_t y = __shfl_up(x, o);
         if (lane >= o) x += y;
     }
     if (lane == 63) lds[wv] = x;
     __syncthreads();
     if (threadIdx.x == 0) {
-        T run = 0;
-        for (int i = 0; i < kWG / 64; ++i) { T t = lds[i]; lds[i] = run; run += t; }
-        lds[kWG / 64] = run;
+        uint64_t run = 0;
+        for (int i = 0; i < WG / 64; ++i) { const uint64_t t = lds[i]; lds[i] = run; run += t; }
+        lds[WG / 64] = run;
     }
     __syncthreads();
-    T res = x - v + lds[wv];
-    total = lds[kWG / 64];
+    const uint64_t res = x - v + lds[wv];
+    total = lds[WG / 64];
     __syncthreads();
     return res;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kWG) void k_scan_reduce(const T *data, int64_t n, T *part) {
-    __shared__ T lds[kWG / 64 + 1];
-    int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPT;
-    T s = 0;
+__global__ __launch_bounds__(kScanOneWG) void k_scan_one(ScanJobs jobs) {
+    __shared__ uint64_t lds[kScanOneWG / 64 + 1];
+    const ScanJob j = jobs.job[blockIdx.y];
+    uint64_t carry = 0;
+    for (int64_t b0 = 0; b0 < j.n; b0 += kScanOneWG * kScanPT) {
+        const int64_t base = b0 + (int64_t)threadIdx.x * kScanPT;
+        uint64_t v[kScanPT], s = 0, tot;
 #pragma unroll
-    for (int i = 0; i < kScanPT; ++i)
-        if (base + i < n) s += data[base + i];
-    T tot;
-    block_exclusive<T>(s, lds, tot);
-    if (threadIdx.x == 0) part[blockIdx.x] = tot;
+        for (int i = 0; i < kScanPT; ++i) {
+            v[i] = j.at(base + i);
+            s += v[i];
+        }
+        uint64_t run = block_exclusive<kScanOneWG>(s, lds, tot) + carry;
+        carry += tot;
+#pragma unroll
+        for (int i = 0; i < kScanPT; ++i)
+            if (base + i < j.n) { j.put(base + i, run); run += v[i]; }
+    }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kWG) void k_scan_partials(T *part, int64_t nb) {
-    __shared__ T lds[kWG / 64 + 1];
-    T carry = 0;
+__global__ __launch_bounds__(kWG) void k_scan_reduce(ScanJobs jobs, uint64_t *part, int64_t stride) {
+    __shared__ uint64_t lds[kWG / 64 + 1];
+    const ScanJob j = jobs.job[blockIdx.y];
+    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPT;
+    uint64_t s = 0, tot;
+#pragma unroll
+    for (int i = 0; i < kScanPT; ++i) s += j.at(base + i);
+    block_exclusive<kWG>(s, lds, tot);
+    if (threadIdx.x == 0) part[blockIdx.y * stride + blockIdx.x] = tot;
+}
+
+__global__ __launch_bounds__(kWG) void k_scan_partials(uint64_t *part, int64_t stride, int64_t nb) {
+    __shared__ uint64_t lds[kWG / 64 + 1];
+    part += blockIdx.y * stride;
+    uint64_t carry = 0;
     for (int64_t b0 = 0; b0 < nb; b0 += kWG) {
-        int64_t i = b0 + threadIdx.x;
-        T v = i < nb ? part[i] : 0;
-        T tot;
-        T ex = block_exclusive<T>(v, lds, tot);
+        const int64_t i = b0 + threadIdx.x;
+        const uint64_t v = i < nb ? part[i] : 0;
+        uint64_t tot;
+        const uint64_t ex = block_exclusive<kWG>(v, lds, tot);
         if (i < nb) part[i] = ex + carry;
         carry += tot;
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kWG) void k_scan_apply(T *data, int64_t n, const T *part) {
-    __shared__ T lds[kWG / 64 + 1];
-    int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPT;
-    T v[kScanPT];
-    T s = 0;
+__global__ __launch_bounds__(kWG) void k_scan_apply(ScanJobs jobs, const uint64_t *part, int64_t stride) {
+    __shared__ uint64_t lds[kWG / 64 + 1];
+    const ScanJob j = jobs.job[blockIdx.y];
+    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPT;
+    uint64_t v[kScanPT], s = 0, tot;
 #pragma unroll
     for (int i = 0; i < kScanPT; ++i) {
-        v[i] = base + i < n ? data[base + i] : 0;
+        v[i] = j.at(base + i);
         s += v[i];
     }
-    T tot;
-    T run = block_exclusive<T>(s, lds, tot) + part[blockIdx.x];
+    uint64_t run = block_exclusive<kWG>(s, lds, tot) + part[blockIdx.y * stride + blockIdx.x];
 #pragma unroll
     for (int i = 0; i < kScanPT; ++i)
-        if (base + i < n) { data[base + i] = run; run += v[i]; }
+        if (base + i < j.n) { j.put(base + i, run); run += v[i]; }
 }
 
 int64_t scan_tmp_needed(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
-template <typename T>
-static void scan_exclusive(T *data, int64_t n, void *tmp, hipStream_t st) {
+static void scan_jobs(const ScanJobs &jobs, int n_job, void *tmp, hipStream_t st) {
+    int64_t n = 0;
+    for (int i = 0; i < n_job; ++i) n = std::max(n, jobs.job[i].n);
     if (n <= 0) return;
-    int64_t nb = (n + kScanTile - 1) / kScanTile;
-    T *part = (T *)tmp;
-    k_scan_reduce<T><<<(unsigned)nb, kWG, 0, st>>>(data, n, part);
-    k_scan_partials<T><<<1, kWG, 0, st>>>(part, nb);
-    k_scan_apply<T><<<(unsigned)nb, kWG, 0, st>>>(data, n, part);
+    if (n <= kScanOne) {
+        k_scan_one<<<dim3(1, (unsigned)n_job), kScanOneWG, 0, st>>>(jobs);
+        return;
+    }
+    const int64_t nb = (n + kScanTile - 1) / kScanTile;
+    uint64_t *part = (uint64_t *)tmp;
+    k_scan_reduce<<<dim3((unsigned)nb, (unsigned)n_job), kWG, 0, st>>>(jobs, part, nb);
+    k_scan_partials<<<dim3(1, (unsigned)n_job), kWG, 0, st>>>(part, nb, nb);
+    k_scan_apply<<<dim3((unsigned)nb, (unsigned)n_job), kWG, 0, st>>>(jobs, part, nb);
 }
 
-void scan_exclusive_i64(int64_t *data, int64_t n, int64_t *, void *tmp, hipStream_t st) {
-    scan_exclusive<int64_t>(data, n, tmp, st);
+void scan_exclusive(int64_t *data, int64_t n, int64_t *total, void *tmp, hipStream_t st) {
+    scan_jobs(ScanJobs{{{(uint64_t *)data, n, total, nullptr, false}, {}}}, 1, tmp, st);
 }
-void scan_exclusive_u64(uint64_t *data, int64_t n, void *tmp, hipStream_t st) {
-    scan_exclusive<unsigned long long>((unsigned long long *)data, n, tmp, st);
+void scan_exclusive2(int64_t *a, int64_t *b, int64_t n, int64_t *total_a, int64_t *total_b, void *tmp, hipStream_t st) {
+    scan_jobs(ScanJobs{{{(uint64_t *)a, n, total_a, nullptr, false}, {(uint64_t *)b, n, total_b, nullptr, false}}}, 2, tmp,
+              st);
 }
 
 // ================================================================================================= quench / drift
@@ -321,22 +370,6 @@ __global__ __launch_bounds__(kWG) void k_quench_drift(DevParams P, SegArrays S, 
     add_report(report, e, 1, valid ? (double)g.q_a : 0.0, valid);
 }
 
-// Mark active pixels (count > 0) in the high bits so one scan yields pair offsets and slot indices.
-__global__ void k_mark_active(uint64_t *pix_cnt, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        uint64_t v = pix_cnt[i];
-        pix_cnt[i] = v | (v ? (1ull << 40) : 0ull);
-    }
-}
-
-__global__ void k_totals(const uint64_t *pix_off, int64_t n_gp, const int64_t *cell_off, int64_t n_seg, DevHeader *H) {
-    uint64_t t = pix_off[n_gp];
-    H->n_pairs = (int64_t)(t & kMask40);
-    H->n_slots = (int64_t)(t >> 40);
-    H->n_cells = cell_off[n_seg];
-}
-
 // inclusive prefix sums along each row of a set of grids (one wavefront per row of len values)
 __global__ __launch_bounds__(kWG) void k_prefix_rows(int64_t *a, int64_t n_rows, int32_t len) {
     const int lane = threadIdx.x & 63;
@@ -356,28 +389,43 @@ __global__ __launch_bounds__(kWG) void k_prefix_rows(int64_t *a, int64_t n_rows,
     }
 }
 
-// inclusive prefix sums down each column of n_ev grids of CU rows x CV values (thread per (grid, v); eight
-// rows loaded ahead)
-__global__ void k_prefix_cols(int64_t *a, int32_t n_ev, int32_t CU, int32_t CV) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)n_ev * CV) return;
-    const int64_t ev = t / CV, v = t - ev * CV;
-    int64_t *p = a + ev * CU * CV + v, run = 0;
-    int32_t u = 0;
-    for (; u + 8 <= CU; u += 8) {
+// inclusive prefix sums down each column of n_ev grids of CU rows x CV values.  A workgroup takes 16 columns, every 16
+// lanes a sixteenth of their rows, which they add up first.  (A thread down a whole column is one long chain of loads: 88 us
+// for 1490 x 1490 columns, 21 so; 64 columns by 16 parts took 42, and workgroups of 1024 threads wait for a free CU beside
+// the charge cells on the other stream.)
+constexpr int kColsWG = 256, kColsWide = 16, kColsParts = kColsWG / kColsWide;
+__global__ __launch_bounds__(kColsWG) void k_prefix_cols(int64_t *a, int32_t n_ev, int32_t CU, int32_t CV) {
+    __shared__ int64_t lds[kColsParts][kColsWide];
+    const int32_t n_blk = (CV + kColsWide - 1) / kColsWide, ev = blockIdx.x / n_blk;
+    const int32_t col = threadIdx.x % kColsWide, part = threadIdx.x / kColsWide;
+    const int32_t v = (blockIdx.x - ev * n_blk) * kColsWide + col;
+    const int32_t per = (CU + kColsParts - 1) / kColsParts, u0 = min(part * per, CU), u1 = v < CV ? min(u0 + per, CU) : u0;
+    int64_t *p = a + (int64_t)ev * CU * CV + v;
+    int64_t sum = 0;
+    for (int32_t u = u0; u < u1; u += 8) {
         int64_t x[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = p[(int64_t)(u + i) * CV];
+        for (int i = 0; i < 8; ++i) x[i] = u + i < u1 ? p[(int64_t)(u + i) * CV] : 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sum += x[i];
+    }
+    lds[part][col] = sum;
+    __syncthreads();
+    int64_t run = 0;
+    for (int32_t i = 0; i < part; ++i) run += lds[i][col];
+    for (int32_t u = u0; u < u1; u += 8) {
+        int64_t x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = u + i < u1 ? p[(int64_t)(u + i) * CV] : 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             run += x[i];
-            p[(int64_t)(u + i) * CV] = run;
+            if (u + i < u1) p[(int64_t)(u + i) * CV] = run;
         }
     }
-    for (; u < CU; ++u) {
-        run += p[(int64_t)u * CV];
-        p[(int64_t)u * CV] = run;
-    }
+}
+static void launch_prefix_cols(int64_t *a, int32_t n_ev, int32_t CU, int32_t CV, hipStream_t st) {
+    k_prefix_cols<<<(unsigned)(n_ev * ((CV + kColsWide - 1) / kColsWide)), kColsWG, 0, st>>>(a, n_ev, CU, CV);
 }
 
 void launch_quench_drift(const DevParams &P, const SegArrays &S, const Work &w, hipStream_t st) {
@@ -388,13 +436,10 @@ void launch_quench_drift(const DevParams &P, const SegArrays &S, const Work &w, 
     if (n_gp > 0) {
         const int64_t rows = (int64_t)w.n_ev * P.ny;
         k_prefix_rows<<<(unsigned)((rows + kWG / 64 - 1) / (kWG / 64)), kWG, 0, st>>>((int64_t *)w.pix_cnt, rows, P.nx);
-        k_prefix_cols<<<(unsigned)(((int64_t)w.n_ev * P.nx + kWG - 1) / kWG), kWG, 0, st>>>((int64_t *)w.pix_cnt,
-                                                                                           w.n_ev, P.ny, P.nx);
+        launch_prefix_cols((int64_t *)w.pix_cnt, w.n_ev, P.ny, P.nx, st);
     }
-    k_mark_active<<<(unsigned)((n_gp + kWG - 1) / kWG), kWG, 0, st>>>(w.pix_cnt, n_gp);
-    scan_exclusive<unsigned long long>((unsigned long long *)w.pix_cnt, n_gp + 1, w.scan_tmp, st);
-    scan_exclusive<int64_t>(w.cell_off, w.n_seg + 1, w.scan_tmp, st);
-    k_totals<<<1, 1, 0, st>>>(w.pix_cnt, n_gp, w.cell_off, w.n_seg, w.hdr);
+    scan_jobs(ScanJobs{{{w.pix_cnt, n_gp + 1, &w.hdr->n_pairs, &w.hdr->n_slots, true},
+                        {(uint64_t *)w.cell_off, w.n_seg + 1, &w.hdr->n_cells, nullptr, false}}}, 2, w.scan_tmp, st);
 }
 
 __global__ void k_stage_qd(DevParams P, SegArrays S, int64_t n, float *out_f, int32_t *out_i) {
@@ -415,37 +460,36 @@ void launch_stage_quench_drift(const DevParams &P, const SegArrays &S, int64_t n
 }
 
 // ================================================================================================= slots / pairs
+// Also the events' first slots, and zeros in the packet counts (n_zero words).
 __global__ void k_slots(DevParams P, int64_t n_gp, const uint64_t *pix_off, int32_t *pix_slot, int32_t *slot_gp,
-                        int64_t *slot_off, int32_t *pixel_id_out, const DevHeader *H, int64_t cap_slots) {
+                        int64_t *slot_off, int32_t *pixel_id_out, int64_t *ev_pix_off, const DevHeader *H, uint32_t *zero,
+                        int64_t n_zero) {
     int64_t gp = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = gp; i < n_zero; i += (int64_t)gridDim.x * blockDim.x) zero[i] = 0u;
     if (gp > n_gp) return;
+    uint64_t v = pix_off[gp];
+    if (ev_pix_off && gp % P.npx == 0) ev_pix_off[gp / P.npx] = (int64_t)(v >> 40);
     if (gp == n_gp) {
-        int64_t ns = H->n_slots;
-        if (ns <= cap_slots) slot_off[ns] = H->n_pairs;
+        slot_off[H->n_slots] = H->n_pairs;
         return;
     }
-    uint64_t v = pix_off[gp], vn = pix_off[gp + 1];
+    uint64_t vn = pix_off[gp + 1];
     bool active = (vn >> 40) > (v >> 40);
     int64_t slot = (int64_t)(v >> 40);
     pix_slot[gp] = active ? (int32_t)slot : -1;
-    if (active && slot < cap_slots) {
+    if (active) {
         slot_gp[slot] = (int32_t)gp;
         slot_off[slot] = (int64_t)(v & kMask40);
         if (pixel_id_out) pixel_id_out[slot] = (int32_t)(gp % P.npx);
     }
 }
 
-__global__ void k_event_pixel_offsets(int32_t n_ev, int32_t npx, const uint64_t *pix_off, int64_t *ev_pix_off) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e <= n_ev) ev_pix_off[e] = (int64_t)(pix_off[(int64_t)e * npx] >> 40);
-}
-
-void launch_slots(const DevParams &P, const Work &w, int32_t *pixel_id_out, int64_t *ev_pix_off, hipStream_t st) {
+void launch_slots(const DevParams &P, const Work &w, int32_t *pixel_id_out, int64_t *ev_pix_off, void *zero,
+                  int64_t zero_bytes, hipStream_t st) {
     const int64_t n_gp = (int64_t)w.n_ev * P.npx;
-    k_slots<<<(unsigned)((n_gp + 1 + kWG - 1) / kWG), kWG, 0, st>>>(P, n_gp, w.pix_cnt, w.pix_slot, w.slot_gp,
-                                                                   w.slot_off, pixel_id_out, w.hdr, INT64_MAX);
-    if (ev_pix_off)
-        k_event_pixel_offsets<<<(w.n_ev + 1 + kWG - 1) / kWG, kWG, 0, st>>>(w.n_ev, P.npx, w.pix_cnt, ev_pix_off);
+    k_slots<<<(unsigned)((n_gp + 1 + kWG - 1) / kWG), kWG, 0, st>>>(P, n_gp, w.pix_cnt, w.pix_slot, w.slot_gp, w.slot_off,
+                                                                   pixel_id_out, ev_pix_off, w.hdr, (uint32_t *)zero,
+                                                                   zero_bytes / 4);
 }
 
 // Also stores each segment's scanned charge-cell offset in its record (the scan runs after k_quench_drift); with
@@ -471,6 +515,21 @@ __global__ __launch_bounds__(kWG) void k_fill_pairs(DevParams P, SegInfo *si, in
 __global__ void k_zero_words(uint32_t *p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0u;
+}
+
+// Several buffers at once, and the events' offsets and ids of a call with few of them (their copies would be a launch each).
+__global__ void k_start(ZeroRanges z, EventList ev, int64_t *ev_off, uint64_t *ev_ids) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+#pragma unroll
+    for (int r = 0; r < kZeroRanges; ++r)
+        for (int64_t i = t; i < z.words[r]; i += (int64_t)gridDim.x * blockDim.x) z.p[r][i] = 0u;
+    if (t <= ev.n && ev_off) ev_off[t] = ev.off[t];
+    if (t < ev.n && ev_off) ev_ids[t] = ev.id[t];
+}
+void launch_start(const ZeroRanges &z, const EventList &ev, int64_t *ev_off, uint64_t *ev_ids, hipStream_t st) {
+    int64_t most = kWG;
+    for (int r = 0; r < kZeroRanges; ++r) most = std::max(most, z.words[r]);
+    k_start<<<(unsigned)std::min<int64_t>((most + kWG - 1) / kWG, 4096), kWG, 0, st>>>(z, ev, ev_off, ev_ids);
 }
 
 __global__ void k_store_u64(uint64_t *p, uint64_t v) { *p = v; }
@@ -1690,8 +1749,7 @@ void launch_sum_ranges(const DevParams &P, const Work &w, const SumWork &sw, hip
     const int64_t rows = n_ev * sw.CU;
     if (rows > 0) {
         k_prefix_rows<<<(unsigned)((rows + kWG / 64 - 1) / (kWG / 64)), kWG, 0, st>>>(sw.col_seg_off, rows, sw.CV);
-        k_prefix_cols<<<(unsigned)((n_ev * sw.CV + kWG - 1) / kWG), kWG, 0, st>>>(sw.col_seg_off, (int32_t)n_ev, sw.CU,
-                                                                                  sw.CV);
+        launch_prefix_cols(sw.col_seg_off, (int32_t)n_ev, sw.CU, sw.CV, st);
     }
 }
 
@@ -3406,9 +3464,11 @@ void launch_induce_z(const DevParams &P, const Work &w, const Table &T, float *w
     }
     if (mode == 0) {
         if (n_slots <= 0) return;
-        if (w.order) launch_slot_order(P, w, n_slots, st);
+        // up to two workgroups a CU all pixels start at once, in any order
+        const int32_t *order = n_slots > 512 ? w.order : nullptr;
+        if (order) launch_slot_order(P, w, n_slots, st);
         k_induce_z<<<(unsigned)std::min<int64_t>(n_slots, 256 * 4), kWG, (size_t)2 * P.nticks * sizeof(float), st>>>(
-            P, Z, w.si, w.cells, w.slot_off, w.pairs, w.slot_gp, w.order, wave, w.hdr);
+            P, Z, w.si, w.cells, w.slot_off, w.pairs, w.slot_gp, order, wave, w.hdr);
     } else if (w.n_seg > 0) {
         const int64_t units = (w.n_seg + kZaSegs - 1) / kZaSegs * kZaRows;
         k_induce_z_atomic<<<(unsigned)std::min<int64_t>(units, 256 * 4), kWG, 0, st>>>(P, Z, w.si, w.n_seg, w.cells,
@@ -4004,8 +4064,18 @@ void launch_settle(const DevParams &P, const Work &w, const SumWork &sw, const T
 
 __global__ void k_compact(int32_t max_packets, int64_t n_slots, const int64_t *pk_off, const int32_t *slot_gp,
                           int32_t npx, const int32_t *pk_tick, const uint16_t *pk_adc, const uint8_t *pk_flag,
-                          int32_t *o_pixel, int32_t *o_tick, uint16_t *o_adc, uint8_t *o_flag, int64_t cap) {
+                          int32_t *o_pixel, int32_t *o_tick, uint16_t *o_adc, uint8_t *o_flag, int64_t cap,
+                          const DevHeader *H, int64_t *counts, int32_t n_ev, const int64_t *ev_pix_off,
+                          int64_t *ev_pkt_off) {
     const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (slot == 0 && counts) {
+        counts[0] = n_slots;
+        counts[1] = pk_off[n_slots];
+        counts[2] = H->dropped;
+        counts[3] = H->over;
+    }
+    if (ev_pkt_off && ev_pix_off)
+        for (int64_t e = slot; e <= n_ev; e += (int64_t)gridDim.x * blockDim.x) ev_pkt_off[e] = pk_off[ev_pix_off[e]];
     if (slot >= n_slots) return;
     const int64_t off = pk_off[slot], cnt = pk_off[slot + 1] - off;
     const int32_t pid = slot_gp[slot] % npx;
@@ -4018,28 +4088,13 @@ __global__ void k_compact(int32_t max_packets, int64_t n_slots, const int64_t *p
     }
 }
 
-__global__ void k_counts(int64_t n_slots, const int64_t *pk_off, const DevHeader *H, int64_t *counts, int64_t cap_pk,
-                         int32_t n_ev, const int64_t *ev_pix_off, int64_t *ev_pkt_off) {
-    const int64_t tot = pk_off[n_slots];
-    if (threadIdx.x == 0 && blockIdx.x == 0 && counts) {
-        counts[0] = n_slots;
-        counts[1] = tot;
-        counts[2] = H->dropped;
-        counts[3] = H->over;
-    }
-    for (int e = threadIdx.x; ev_pkt_off && ev_pix_off && e <= n_ev; e += blockDim.x) ev_pkt_off[e] = pk_off[ev_pix_off[e]];
-    (void)cap_pk;
-}
-
 void launch_compact_packets(const DevParams &P, const Work &w, int64_t n_slots, int32_t *pkt_pixel, int32_t *pkt_tick,
                             uint16_t *pkt_adc, uint8_t *pkt_flags, int64_t cap_packets, const int64_t *ev_pix_off,
                             int64_t *ev_pkt_off, int64_t *counts, hipStream_t st) {
-    scan_exclusive<int64_t>(w.pk_off, n_slots + 1, w.scan_tmp, st);
-    if (n_slots > 0)
-        k_compact<<<(unsigned)((n_slots + kWG - 1) / kWG), kWG, 0, st>>>(P.max_packets, n_slots, w.pk_off, w.slot_gp,
-                                                                         P.npx, w.pk_tick, w.pk_adc, w.pk_flag, pkt_pixel,
-                                                                         pkt_tick, pkt_adc, pkt_flags, cap_packets);
-    k_counts<<<1, kWG, 0, st>>>(n_slots, w.pk_off, w.hdr, counts, cap_packets, w.n_ev, ev_pix_off, ev_pkt_off);
+    scan_exclusive(w.pk_off, n_slots + 1, nullptr, w.scan_tmp, st);
+    k_compact<<<(unsigned)std::max<int64_t>((n_slots + kWG - 1) / kWG, 1), kWG, 0, st>>>(
+        P.max_packets, n_slots, w.pk_off, w.slot_gp, P.npx, w.pk_tick, w.pk_adc, w.pk_flag, pkt_pixel, pkt_tick, pkt_adc,
+        pkt_flags, cap_packets, w.hdr, counts, w.n_ev, ev_pix_off, ev_pkt_off);
 }
 
 // ================================================================================================= work statistics

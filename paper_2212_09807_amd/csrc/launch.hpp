@@ -140,12 +140,27 @@ void launch_induce_z(const DevParams &P, const Work &w, const Table &T, float *w
 void launch_induce_z_pairs(const DevParams &P, const Work &w, const Table &T, int64_t n_slots, float *out,
                            hipStream_t st);
 
-int64_t scan_tmp_needed(int64_t n);
-void scan_exclusive_i64(int64_t *data, int64_t n, int64_t *total_dst, void *tmp, hipStream_t st);
-void scan_exclusive_u64(uint64_t *data, int64_t n, void *tmp, hipStream_t st);
+int64_t scan_tmp_needed(int64_t n);          // 64-bit words of `tmp` per array
+// data[n - 1] is taken as 0 and receives the total, which also goes to `total` (may be null)
+void scan_exclusive(int64_t *data, int64_t n, int64_t *total, void *tmp, hipStream_t st);
+void scan_exclusive2(int64_t *a, int64_t *b, int64_t n, int64_t *total_a, int64_t *total_b, void *tmp, hipStream_t st);
+
+constexpr int kZeroRanges = 6, kListedEvents = 16;
+struct ZeroRanges {
+    uint32_t *p[kZeroRanges] = {};
+    int64_t words[kZeroRanges] = {};
+};
+struct EventList {                              // events of a call, up to kListedEvents
+    int64_t off[kListedEvents + 1] = {};
+    uint64_t id[kListedEvents] = {};
+    int32_t n = 0;
+};
+// zeros the ranges; writes the event list unless ev_off is null
+void launch_start(const ZeroRanges &z, const EventList &ev, int64_t *ev_off, uint64_t *ev_ids, hipStream_t st);
 
 void launch_quench_drift(const DevParams &P, const SegArrays &S, const Work &w, hipStream_t st);
-void launch_slots(const DevParams &P, const Work &w, int32_t *pixel_id_out, int64_t *ev_pix_off, hipStream_t st);
+void launch_slots(const DevParams &P, const Work &w, int32_t *pixel_id_out, int64_t *ev_pix_off, void *zero,
+                  int64_t zero_bytes, hipStream_t st);   // zero: a buffer to clear on the way (or null)
 void launch_zero(void *p, int64_t bytes, hipStream_t st);   // bytes: a multiple of 4
 void launch_store_u64(uint64_t *p, uint64_t v, hipStream_t st); // one value written by a kernel (capture-safe)
 void launch_fill_pairs(const DevParams &P, const Work &w, hipStream_t st);

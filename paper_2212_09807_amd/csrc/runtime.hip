@@ -424,16 +424,26 @@ lts_status run_sizing(lts_context *c, int32_t n_ev, const uint64_t *event_ids, c
     if ((r = ensure(c, c->hdr, sizeof(DevHeader)))) return r;
     if ((r = ensure(c, c->ev_off, sizeof(int64_t) * (size_t)(n_ev + 1)))) return r;
     if ((r = ensure(c, c->ev_ids, sizeof(uint64_t) * (size_t)n_ev))) return r;
-    if ((r = ensure(c, c->scan_tmp, sizeof(int64_t) * (size_t)scan_tmp_needed(scan_n)))) return r;
+    if ((r = ensure(c, c->scan_tmp, 2 * sizeof(int64_t) * (size_t)scan_tmp_needed(scan_n)))) return r;
     if ((r = ensure(c, c->ev_cnt, sizeof(int64_t) * 2 * (size_t)n_ev))) return r;
-    HIP_TRY(c, hipMemsetAsync(c->ev_cnt.p, 0, sizeof(int64_t) * 2 * (size_t)n_ev, st));
-    HIP_TRY(c, hipMemcpyAsync(c->ev_off.p, seg_offsets, sizeof(int64_t) * (size_t)(n_ev + 1), hipMemcpyHostToDevice, st));
-    HIP_TRY(c, hipMemcpyAsync(c->ev_ids.p, event_ids, sizeof(uint64_t) * (size_t)n_ev, hipMemcpyHostToDevice, st));
-    HIP_TRY(c, hipMemsetAsync(c->pix_cnt.p, 0, sizeof(uint64_t) * (size_t)(n_gp + 1), st));
-    HIP_TRY(c, hipMemsetAsync(c->cursor.p, 0, sizeof(int32_t) * (size_t)n_gp, st));
-    HIP_TRY(c, hipMemsetAsync(c->hdr.p, 0, sizeof(DevHeader), st));
-    HIP_TRY(c, hipMemsetAsync(as<int64_t>(c->cell_off) + n_seg, 0, sizeof(int64_t), st));
-    HIP_TRY(c, hipMemsetAsync(report, 0, sizeof(double) * 5 * (size_t)n_ev, st));
+    auto words = [](DevBuf &b) { return (uint32_t *)b.p; };
+    ZeroRanges z;
+    z.p[0] = words(c->ev_cnt), z.words[0] = 4 * (int64_t)n_ev;
+    z.p[1] = words(c->pix_cnt), z.words[1] = 2 * (n_gp + 1);
+    z.p[2] = words(c->cursor), z.words[2] = n_gp;
+    z.p[3] = words(c->hdr), z.words[3] = (int64_t)sizeof(DevHeader) / 4;
+    z.p[4] = (uint32_t *)report, z.words[4] = 10 * (int64_t)n_ev;
+    EventList ev;
+    const bool listed = n_ev <= kListedEvents;
+    if (listed) {
+        ev.n = n_ev;
+        std::copy(seg_offsets, seg_offsets + n_ev + 1, ev.off);
+        std::copy(event_ids, event_ids + n_ev, ev.id);
+    } else {
+        HIP_TRY(c, hipMemcpyAsync(c->ev_off.p, seg_offsets, sizeof(int64_t) * (size_t)(n_ev + 1), hipMemcpyHostToDevice, st));
+        HIP_TRY(c, hipMemcpyAsync(c->ev_ids.p, event_ids, sizeof(uint64_t) * (size_t)n_ev, hipMemcpyHostToDevice, st));
+    }
+    launch_start(z, ev, listed ? as<int64_t>(c->ev_off) : nullptr, as<uint64_t>(c->ev_ids), st);
     w = Work{};
     w.n_seg = n_seg;
     w.n_ev = n_ev;
@@ -495,7 +505,7 @@ void summed_needs(lts_context *c, const DevHeader &h, int64_t n_slots, int32_t n
     needs.push_back({&c->list_off, sizeof(int64_t) * (size_t)(n_slots + 1)});
     needs.push_back({&c->mlist_off, sizeof(int64_t) * (size_t)(n_slots + 1)});
     needs.push_back({&c->m_off, sizeof(int64_t) * (size_t)(n_slots + 1)});
-    needs.push_back({&c->scan_tmp, sizeof(int64_t) * (size_t)scan_tmp_needed(std::max(nc1, n_slots + 1))});
+    needs.push_back({&c->scan_tmp, 2 * sizeof(int64_t) * (size_t)scan_tmp_needed(std::max(nc1, n_slots + 1))});
 }
 
 // Whether the call's currents are summed on the FP16 matrix cores (the automatic kernels).
@@ -530,24 +540,22 @@ lts_status run_summed(lts_context *c, const Work &w, const DevHeader &h, int64_t
     sw.align_res = summed_align_res(P, c->ticks_per_thread, c->lane_exchange != 0);
     sw.piece_lists = !((c->ticks_per_thread == 0 || c->ticks_per_thread == 8) && c->lane_exchange == 0);
     void *tmp = c->scan_tmp.p;
-    HIP_TRY(c, hipMemsetAsync(sw.col_seg_off, 0, sizeof(int64_t) * (size_t)nc1, st));
-    HIP_TRY(c, hipMemsetAsync(sw.col_cursor, 0, sizeof(int32_t) * (size_t)sw.n_cols, st));
-    HIP_TRY(c, hipMemsetAsync(sw.piece_off + sw.n_cols, 0, sizeof(int64_t), st));
-    HIP_TRY(c, hipMemsetAsync(sw.s_off + sw.n_cols, 0, sizeof(int64_t), st));
-    HIP_TRY(c, hipMemsetAsync(sw.list_off + n_slots, 0, sizeof(int64_t), st));
-    HIP_TRY(c, hipMemsetAsync(sw.mlist_off + n_slots, 0, sizeof(int64_t), st));
-    HIP_TRY(c, hipMemsetAsync(sw.m_off + n_slots, 0, sizeof(int64_t), st));
+    ZeroRanges z;
+    z.p[0] = (uint32_t *)sw.col_seg_off, z.words[0] = 2 * nc1;
+    z.p[1] = (uint32_t *)sw.col_cursor, z.words[1] = sw.n_cols;
+    launch_start(z, EventList{}, nullptr, nullptr, st);
     launch_sum_ranges(P, w, sw, st);
-    scan_exclusive_i64(sw.col_seg_off, nc1, nullptr, tmp, st);
+    scan_exclusive(sw.col_seg_off, nc1, nullptr, tmp, st);
     launch_sum_fill(P, w, sw, st);
-    scan_exclusive_i64(sw.piece_off, nc1, nullptr, tmp, st);
-    scan_exclusive_i64(sw.s_off, nc1, nullptr, tmp, st);
+    int64_t *sizes = w.hdr->sum_sizes;
+    scan_exclusive2(sw.piece_off, sw.s_off, nc1, sizes, sizes + 1, tmp, st);
     // exact sizes of the piece records and the summed charges (a column's merged tick intervals are only known
     // after its segments are sorted)
     int64_t tot[3] = {0, 0, 0};
-    HIP_TRY(c, hipMemcpyAsync(&tot[1], sw.piece_off + sw.n_cols, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipMemcpyAsync(&tot[2], sw.s_off + sw.n_cols, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(c, hipMemcpyAsync(c->hdr_host->sum_sizes, sizes, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
+    tot[1] = c->hdr_host->sum_sizes[0];
+    tot[2] = c->hdr_host->sum_sizes[1];
     if (tot[2] / kAC >= (int64_t)UINT32_MAX)          // piece records hold the charge offset in units of kAC floats
         return fail(c, LTS_ERR_CAPACITY, "summed induction: too many summed charge values for one call");
     if ((r = grow(c, h, {{&c->pdesc, sizeof(PieceRef) * (size_t)std::max<int64_t>(tot[1], 1)},
@@ -562,9 +570,10 @@ lts_status run_summed(lts_context *c, const Work &w, const DevHeader &h, int64_t
     if (cells_ready) HIP_TRY(c, hipStreamWaitEvent(st, cells_ready, 0));
     launch_sum_pieces(P, w, sw, st);
     launch_sum_lists_count(P, w, sw, n_slots, st);
-    scan_exclusive_i64(sw.list_off, n_slots + 1, nullptr, tmp, st);
-    HIP_TRY(c, hipMemcpyAsync(&tot[0], sw.list_off + n_slots, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    scan_exclusive(sw.list_off, n_slots + 1, nullptr, tmp, st);
+    HIP_TRY(c, hipMemcpyAsync(c->hdr_host->sum_sizes, sw.list_off + n_slots, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
+    tot[0] = c->hdr_host->sum_sizes[0];
     if ((r = grow(c, h, {{&c->rec, sizeof(PieceRef) * (size_t)std::max<int64_t>(tot[0], 1)}}))) return r;
     if (sw.piece_lists) {
         if ((r = grow(c, h, {{&c->list, sizeof(int32_t) * (size_t)std::max<int64_t>(tot[0], 1)}}))) return r;
@@ -575,12 +584,10 @@ lts_status run_summed(lts_context *c, const Work &w, const DevHeader &h, int64_t
     // mirror merge: sizes of the merged records and charges, then the records
     sw.nS8 = (uint32_t)(tot[2] / kAC);
     launch_sum_merge(sw, n_slots, -1, st);
-    scan_exclusive_i64(sw.mlist_off, n_slots + 1, nullptr, tmp, st);
-    scan_exclusive_i64(sw.m_off, n_slots + 1, nullptr, tmp, st);
-    int64_t mt[2] = {0, 0};
-    HIP_TRY(c, hipMemcpyAsync(&mt[0], sw.mlist_off + n_slots, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipMemcpyAsync(&mt[1], sw.m_off + n_slots, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    scan_exclusive2(sw.mlist_off, sw.m_off, n_slots + 1, sizes, sizes + 1, tmp, st);
+    HIP_TRY(c, hipMemcpyAsync(c->hdr_host->sum_sizes, sizes, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
+    const int64_t mt[2] = {c->hdr_host->sum_sizes[0], c->hdr_host->sum_sizes[1]};
     if (tot[2] / kAC + mt[1] / kAC >= (int64_t)UINT32_MAX)
         return fail(c, LTS_ERR_CAPACITY, "summed induction: too many summed charge values for one call");
     if ((r = grow(c, h, {{&c->mrec, sizeof(PieceRef) * (size_t)mt[0] + sizeof(int64_t) * (size_t)(mt[0] + 1)},
@@ -745,10 +752,10 @@ lts_status run_pipeline(lts_context *c, int32_t n_ev, const uint64_t *event_ids,
     const bool graph = c->use_graph && c->reduce_mode != LTS_REDUCE_SUMMED;
     SumWork sw;
     auto launch_all = [&](hipStream_t s) -> lts_status {
-        launch_zero(w.pk_off, (int64_t)sizeof(int64_t) * (n_slots + 1) + (int64_t)sizeof(uint32_t) * n_token, s);
         {
             StageTimer t(c, s, LTS_STAGE_RASTERIZE);
-            launch_slots(P, w, out->pixel_id, out->event_pixel_offsets, s);
+            launch_slots(P, w, out->pixel_id, out->event_pixel_offsets, w.pk_off,
+                         (int64_t)sizeof(int64_t) * (n_slots + 1) + (int64_t)sizeof(uint32_t) * n_token, s);
             launch_fill_pairs(P, w, s);
             if (c->reduce_mode == LTS_REDUCE_SORTED || (settle && !summed)) launch_sort_pairs(w, n_slots, s);
         }
@@ -1318,7 +1325,7 @@ static lts_status stage_front(lts_context *c, uint64_t event_id, const lts_segme
     w.pairs_unsorted = as<int32_t>(c->pairs_u);
     w.pairs = as<int32_t>(c->pairs);
     w.cells = with_cells ? as<float>(c->cells) : nullptr;
-    launch_slots(c->P, w, nullptr, nullptr, st);
+    launch_slots(c->P, w, nullptr, nullptr, nullptr, 0, st);
     launch_fill_pairs(c->P, w, st);
     launch_sort_pairs(w, n_slots, st);
     if (with_cells) launch_cells(c->P, w, st);
@@ -1390,7 +1397,7 @@ lts_status lts_stage_reduce(lts_context *c, const int32_t *pair_pixel, const flo
     int64_t *head = as<int64_t>(c->red_head), *start = as<int64_t>(c->red_start);
     HIP_TRY(c, hipMemsetAsync(c->hdr.p, 0, sizeof(DevHeader), st));
     launch_run_heads(pair_pixel, n_pairs, head, as<DevHeader>(c->hdr), st);
-    scan_exclusive_i64(head, n_pairs + 1, nullptr, c->scan_tmp.p, st);
+    scan_exclusive(head, n_pairs + 1, nullptr, c->scan_tmp.p, st);
     launch_run_starts(pair_pixel, n_pairs, head, start, pixel_id, cap_pixels, st);
     HIP_TRY(c, hipGetLastError());
     int64_t n_runs = 0;

@@ -680,6 +680,32 @@ def test_draw_counts_in_any_width(lt, orc, torch, n, draws):
     check_event(lt, orc, w, mode=0)
 
 
+@pytest.mark.parametrize("n_x,n_y,mode", [(127, 129, 0), (128, 128, 2), (8, 1024, 0), (130, 127, 2)])
+def test_pixel_scans_at_their_limits(lt, orc, torch, n_x, n_y, mode):
+    """Pixel grids whose counts are scanned by one workgroup in one or two passes (8192 and 16,384 elements) or by tiles."""
+    w = _edge_workload(255, 37, 5, 3, 10)
+    w.readout = dataclasses.replace(w.readout, n_x=n_x, n_y=n_y)
+    check_event(lt, orc, w, mode=mode)
+
+
+@pytest.mark.parametrize("n_ev", [16, 17])
+def test_events_listed_in_the_launch_or_copied(lt, torch, n_ev):
+    w = W.make_workload(1, n_events=1)
+    e = w.events[0]
+    part = dataclasses.replace(e, **{f.name: getattr(e, f.name)[:9] for f in dataclasses.fields(e)
+                                     if isinstance(getattr(e, f.name), np.ndarray)})
+    ids = [(1 << 40) + 7 * i for i in range(n_ev)]
+    ctx = lt.Context.from_workload(w)
+    b = ctx.simulate_batch(lt.to_device(W.Segments.concat([part] * n_ev)), np.arange(n_ev + 1) * part.n, ids).host()
+    po, ko = b["event_pixel_offsets"], b["event_packet_offsets"]
+    for i in (0, n_ev - 1):
+        s = ctx.simulate(lt.to_device(part), event_id=ids[i]).host()
+        assert np.array_equal(b["pixel_id"][po[i]:po[i + 1]], s["pixel_id"])
+        assert np.array_equal(b["current"][po[i]:po[i + 1]], s["current"])
+        assert np.array_equal(b["pkt_adc"][ko[i]:ko[i + 1]], s["pkt_adc"])
+        assert np.array_equal(b["pkt_tick"][ko[i]:ko[i + 1]], s["pkt_tick"])
+
+
 def test_graph_replay_equals_direct_launches(lt, torch):
     """Calls replayed as HIP graphs (updated in place between events of different sizes, re-instantiated when the
     launch structure changes) give the same results as direct launches, with the program's own GPU work and
