@@ -2839,13 +2839,14 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
 // A workgroup stages 32 ticks x 32 octets of C at a time, and each wavefront owns a range of output ticks (it also
 // computes the two table tiles below its range), so no sum is shared between wavefronts: the result depends only on
 // the segments' order.
-//   What bounds it: the table octets of every 32 x 32 stage come through L1 from L2 (all loads of a tile pair are issued
-// before its products; without that 14.6 instead of 9.1 ms), then the products.  Staging costs one load per charge value
-// and image, so a group saves work only where its segments share columns: 16 segments and 128 ticks (64 and 256 ticks
-// measured the same).  Two workgroups of four wavefronts a CU: three spill (1.34 -> 1.21 ms on the batch of 64 tracks,
-// but 9.1 -> 9.8 on the event).  Atomic units of 8 segments (4: 4.7 ms, 8: 3.06, 16: 3.3).
-//   Measured against the vector kernels (45 x 45 x 1950 table unless said): sorted, 3000 segments 91.3 -> 9.1 ms; atomic,
-// 800 segments 50 -> 3.06 ms; one track of 512 segments on 20 x 31 x 1001 1.106 -> 0.122 ms, 64 such tracks 9.2 -> 1.34.
+//   What bounds it: dense events the table, which every stage streams from beyond L2 (7 TB/s; 6.5 of 8.6 ms are products
+// and their loads), so all loads of a tile pair are issued before its products (without that 14.6 ms); sparse ones the
+// latency of staging (584 of 1180 us for 64 tracks), so an octet's images are loaded eight at a time (four: 1218 us).  A
+// group saves work only where its segments share columns: 16 segments and 128 ticks (64 and 256 ticks measured the same).
+// Two workgroups of four wavefronts a CU: three spill (event 9.1 -> 9.8 ms).  64 ticks a stage halve the table reads but
+// leave one workgroup a CU (8.3 ms, tracks 1.67).  Atomic units of 8 segments (4: 4.7 ms, 8: 3.06, 16: 3.3).
+//   Measured against the vector kernels (45 x 45 x 1950 table unless said): sorted, 3000 segments 91.3 -> 8.6 ms; atomic,
+// 800 segments 50 -> 2.8 ms; one track on 20 x 31 x 1001 1.106 -> 0.072 ms, 64 such tracks 9.2 -> 1.18.
 // Error against 64 bits (relative to the largest current): 1.4e-6 -> 1.3e-7, 2.2e-6 -> 1.7e-7 atomic.
 constexpr int32_t kZgSegs = 16;                         // segments of a group
 constexpr int32_t kZgSpan = 128;                        // ticks of a group's charge (unless one segment has more)
@@ -2987,7 +2988,7 @@ __device__ __forceinline__ void z_dispatch(int32_t nk, const ZStage &st, __amdgp
 // Adds the current of the group st.seg[0 .. n_seg) on the pixel with centre bins (uc, vc) through emit(n, value), n in
 // [0, n_ticks), called by 32 lanes at a time, never for the same n by two wavefronts between barriers.  `bound`: an upper
 // bound of the group's charge.  All threads of the workgroup call it; it starts and ends with a barrier.
-template <class Emit>
+template <int WG, class Emit>
 __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZStage &st, int32_t n_seg, int32_t A0,
                                         int32_t A1, float bound, int32_t uc, int32_t vc,
                                         const float *__restrict__ cells, Emit emit) {
@@ -3049,13 +3050,13 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
         const float down = ldexpf(1.0f, -N);
         // this wavefront's output tiles of 16 ticks
         const int32_t m_first = max(-n0, 0) / 16, m_last = min(TR + alast - 1, NT - 1 - n0) / 16;
-        const int32_t per = (m_last - m_first + kWG / 64) / (kWG / 64);
+        const int32_t per = (m_last - m_first + WG / 64) / (WG / 64);
         const int32_t m_lo = m_first + wv * per, m_hi = min(m_lo + per, m_last + 1);
         __syncthreads();                                // the images are in place
         for (int32_t o0 = 0; o0 < n_oct; o0 += kZgOct) {
             const int32_t no = min(kZgOct, n_oct - o0), nk = (no + 3) / 4, nq = nk <= 2 ? 8 : nk <= 4 ? 16 : nk <= 6 ? 24 : 32;
-            // stage: thread (tick, octet) sums its eight bins over the images, in order, four images' loads at a time
-            for (int32_t q = tid >> 5; q < nq; q += kWG / 32) {
+            // stage: thread (tick, octet) sums its eight bins over the images, in order
+            for (int32_t q = tid >> 5; q < nq; q += WG / 32) {
                 const int32_t a = tid & 31, o = o0 + min(q, no - 1), ii = o / nj;
                 const int32_t i = i0 + ii, jo = jo0 + o - ii * nj, jb0 = jo * 8;
                 if (a == 0) st.at[q] = (uint32_t)((i * Z.njo + jo) * Z.trq) * 16u;
@@ -3072,11 +3073,15 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
                         near |= iw >= g.i0 && iw <= g.i1 && jw + 7 >= g.j0 && jw <= g.j1;
                     }
                 }
-                uint64_t mask = __ballot(near);
-                while (mask) {
-                    uint32_t x[4][8];
+                int32_t ex[8];
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) {
+                for (int k = 0; k < 8; ++k) ex[k] = Z.exps[i * P.by + min(jb0 + k, P.by - 1)];
+                uint64_t mask = __ballot(near);
+                // adds the next kImg images (in order) to c, all their loads in flight at once
+                auto add = [&](auto kImg) {
+                    uint32_t x[kImg.value][8];
+#pragma unroll
+                    for (int w = 0; w < kImg.value; ++w) {
                         const bool any = mask != 0;
                         const ZJob &g = st.job[any ? __builtin_ctzll(mask) : 0];
                         mask &= mask - 1ull;
@@ -3095,15 +3100,18 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
                                 rc, (uint32_t)(at + k * sj) | (uint32_t)((int32_t)(out << (31 - k)) >> 31), 0, 0);
                     }
 #pragma unroll
-                    for (int w = 0; w < 4; ++w)
+                    for (int w = 0; w < kImg.value; ++w)
 #pragma unroll
                         for (int k = 0; k < 8; ++k) c[k] += __builtin_bit_cast(float, x[w][k]);
+                };
+                while (mask) {
+                    if (__builtin_popcountll(mask) > 4) add(std::integral_constant<int, 8>());
+                    else add(std::integral_constant<int, 4>());
                 }
                 half8 h, l;
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    const int32_t e = jb0 + k < P.by ? Z.exps[i * P.by + jb0 + k] : 0;
-                    const float y = ldexpf(c[k], N - e);
+                    const float y = ldexpf(c[k], N - ex[k]);
                     h[k] = (_Float16)y;
                     l[k] = (_Float16)(y - (float)h[k]);
                 }
@@ -3199,7 +3207,8 @@ __device__ __forceinline__ int32_t z_load_group(const DevParams &P, const SegInf
 
 // Sorted variant (automatic choice): one workgroup per active pixel, its segments in ascending id, group by group; the
 // groups' currents go into the pixel's waveform in LDS with Kahan compensation.
-__global__ __launch_bounds__(kWG, 2) void k_induce_z(DevParams P, ZTable Z, const SegInfo *__restrict__ si,
+template <int WG>
+__global__ __launch_bounds__(WG, 512 / WG) void k_induce_z(DevParams P, ZTable Z, const SegInfo *__restrict__ si,
                                                   const float *__restrict__ cells, const int64_t *__restrict__ slot_off,
                                                   const int32_t *__restrict__ pairs, const int32_t *__restrict__ slot_gp,
                                                   const int32_t *__restrict__ order, float *__restrict__ wave,
@@ -3216,7 +3225,7 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z(DevParams P, ZTable Z, cons
         const int32_t got = __builtin_amdgcn_readfirstlane(s_slot);
         if (got >= n_slots) break;
         const int64_t slot = order ? order[got] : got;
-        for (int n = tid; n < NT; n += kWG) { s_sum[n] = 0.0f; s_cmp[n] = 0.0f; }
+        for (int n = tid; n < NT; n += WG) { s_sum[n] = 0.0f; s_cmp[n] = 0.0f; }
         const int32_t p = slot_gp[slot] % P.npx;
         const int32_t uc = (p % P.nx) * P.nsub + P.nsub / 2, vc = (p / P.nx) * P.nsub + P.nsub / 2;
         const int64_t pe = slot_off[slot + 1];
@@ -3224,7 +3233,7 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z(DevParams P, ZTable Z, cons
             int32_t A0, A1;
             float bound;
             const int32_t n = z_load_group(P, si, q, pe, uc, vc, [&](int64_t k) { return pairs[k]; }, st, A0, A1, bound);
-            z_group(P, Z, st, n, A0, A1, bound, uc, vc, cells, [&](int32_t t, float x) {
+            z_group<WG>(P, Z, st, n, A0, A1, bound, uc, vc, cells, [&](int32_t t, float x) {
                 const float y = x - s_cmp[t], z = s_sum[t] + y;
                 s_cmp[t] = (z - s_sum[t]) - y;
                 s_sum[t] = z;
@@ -3233,7 +3242,7 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z(DevParams P, ZTable Z, cons
             q += n;
         }
         float *wrow = wave + slot * NT;
-        for (int n = tid; n < NT; n += kWG) wrow[n] = s_sum[n] - s_cmp[n];
+        for (int n = tid; n < NT; n += WG) wrow[n] = s_sum[n] - s_cmp[n];
         __syncthreads();
     }
 }
@@ -3305,7 +3314,7 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_atomic(DevParams P, ZTable 
                     const int32_t slot = __builtin_amdgcn_readfirstlane(pix_slot[(int64_t)e * P.npx + iy * P.nx + ix]);
                     if (slot < 0) continue;
                     float *wrow = wave + (int64_t)slot * NT;
-                    z_group(P, Z, st, n, A0, A1, bound, ix * P.nsub + P.nsub / 2, iy * P.nsub + P.nsub / 2, cells,
+                    z_group<kWG>(P, Z, st, n, A0, A1, bound, ix * P.nsub + P.nsub / 2, iy * P.nsub + P.nsub / 2, cells,
                             [&](int32_t t, float x) {
                                 if (x != 0.0f) atomicAdd(&wrow[t], x);
                             });
@@ -3333,7 +3342,7 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_pairs(DevParams P, ZTable Z
             int32_t A0, A1;
             float bound;
             z_load_group(P, si, q, q + 1, uc, vc, [&](int64_t k) { return pairs[k]; }, st, A0, A1, bound);
-            z_group(P, Z, st, 1, A0, A1, bound, uc, vc, cells, [&](int32_t t, float x) { sm[t] += x; });
+            z_group<kWG>(P, Z, st, 1, A0, A1, bound, uc, vc, cells, [&](int32_t t, float x) { sm[t] += x; });
             __syncthreads();
             float *row = out + q * NT;
             for (int n = tid; n < NT; n += kWG) {
@@ -3449,12 +3458,19 @@ static ZTable z_table(const Table &T) {
 // The grid's dynamic LDS may exceed 64 KB with the static stage: the limit is raised once per device.
 hipError_t allow_z_lds() {
     const int most = 2 * 8000 * (int)sizeof(float);
-    hipError_t e = hipFuncSetAttribute((const void *)k_induce_z, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    hipError_t e = hipFuncSetAttribute((const void *)k_induce_z<kWG>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)k_induce_z<512>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)k_induce_z_pairs, hipFuncAttributeMaxDynamicSharedMemorySize, most / 2);
     return e;
 }
 
+// Up to 8 pixels a CU the pixels with the most groups keep the kernel running, and a workgroup of 512 threads takes them
+// faster than two of 256 take two (200 segments, 276 pixels 74 -> 62 us; 1000, 1415 pixels 3.05 -> 2.15 ms; 2500, 2437
+// pixels 10.3 -> 8.2 ms); with more the two overlap staging and products (3500, 3328 pixels 11.6 ms against 12.5; 64
+// tracks, 12,400 pixels 1.18 against 1.68).
+constexpr int64_t kZgWide = 2048;
 void launch_induce_z(const DevParams &P, const Work &w, const Table &T, float *wave, int mode, int64_t n_slots,
                      hipStream_t st) {
     const ZTable Z = z_table(T);
@@ -3467,7 +3483,9 @@ void launch_induce_z(const DevParams &P, const Work &w, const Table &T, float *w
         // up to two workgroups a CU all pixels start at once, in any order
         const int32_t *order = n_slots > 512 ? w.order : nullptr;
         if (order) launch_slot_order(P, w, n_slots, st);
-        k_induce_z<<<(unsigned)std::min<int64_t>(n_slots, 256 * 4), kWG, (size_t)2 * P.nticks * sizeof(float), st>>>(
+        const bool wide = n_slots <= kZgWide;
+        auto *k = wide ? k_induce_z<512> : k_induce_z<kWG>;
+        k<<<(unsigned)std::min<int64_t>(n_slots, 256 * 4), wide ? 512 : kWG, (size_t)2 * P.nticks * sizeof(float), st>>>(
             P, Z, w.si, w.cells, w.slot_off, w.pairs, w.slot_gp, order, wave, w.hdr);
     } else if (w.n_seg > 0) {
         const int64_t units = (w.n_seg + kZaSegs - 1) / kZaSegs * kZaRows;
