@@ -3050,7 +3050,8 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
         const float down = ldexpf(1.0f, -N);
         // this wavefront's output tiles of 16 ticks
         const int32_t m_first = max(-n0, 0) / 16, m_last = min(TR + alast - 1, NT - 1 - n0) / 16;
-        const int32_t per = (m_last - m_first + WG / 64) / (WG / 64);
+        // (an even number: which tiles pair up, and so the order of the sums, must not depend on the wavefronts)
+        const int32_t per = ((m_last - m_first + WG / 64) / (WG / 64) + 1) & ~1;
         const int32_t m_lo = m_first + wv * per, m_hi = min(m_lo + per, m_last + 1);
         __syncthreads();                                // the images are in place
         for (int32_t o0 = 0; o0 < n_oct; o0 += kZgOct) {

@@ -706,6 +706,24 @@ def test_events_listed_in_the_launch_or_copied(lt, torch, n_ev):
         assert np.array_equal(b["pkt_tick"][ko[i]:ko[i + 1]], s["pkt_tick"])
 
 
+def test_pixel_products_are_the_same_in_any_workgroup(lt, torch):
+    """An event whose pixels take 512 threads each gives, in a batch with more than 2048 pixels (256 threads each), the
+    same currents bit for bit; dense segments, so that a pixel has several groups and stages."""
+    w = W.make_workload(2)
+    e = w.events[0]
+    part = dataclasses.replace(e, **{f.name: getattr(e, f.name)[:300] for f in dataclasses.fields(e)
+                                     if isinstance(getattr(e, f.name), np.ndarray)})
+    ctx = lt.Context.from_workload(w)
+    one = ctx.simulate(lt.to_device(part), event_id=5).host()
+    assert len(one["pixel_id"]) <= 2048
+    k = 2048 // len(one["pixel_id"]) + 1
+    b = ctx.simulate_batch(lt.to_device(W.Segments.concat([part] * k)), np.arange(k + 1) * part.n, [5] * k).host()
+    po = b["event_pixel_offsets"]
+    for i in (0, k - 1):
+        assert np.array_equal(b["pixel_id"][po[i]:po[i + 1]], one["pixel_id"])
+        assert np.array_equal(b["current"][po[i]:po[i + 1]], one["current"])
+
+
 def test_graph_replay_equals_direct_launches(lt, torch):
     """Calls replayed as HIP graphs (updated in place between events of different sizes, re-instantiated when the
     launch structure changes) give the same results as direct launches, with the program's own GPU work and
