@@ -270,51 +270,108 @@ __global__ void k_light_noise_coef(const float *__restrict__ amp, int32_t F, int
     coef[i] = make_float2((float)(amp[f - 1] * cos(phi)), (float)(amp[f - 1] * sin(phi)));
 }
 
-// Noise by FFT (power-of-two windows, T >= 4, whose complex spectrum and a quarter-period cosine table fit in LDS):
-// noise[t] is the real part of y[t] = sum_{f=1}^{F} A_f e^{i phi_f} e^{2 pi i f t / T}, an unnormalised inverse DFT of
-// the one-sided spectrum, computed in place by iterative radix-2 decimation in time (bit-reversed load, log2 T
-// butterfly stages).  The twiddles e^{2 pi i m / T}, m < T/2, come from cos(2 pi m / T) for m <= T/4 staged in LDS:
-// sin(2 pi m / T) = cos(2 pi (T/4 - m) / T), and past a quarter period cos and sin follow from the quarter shift.
-// One workgroup per detector.
-inline size_t noise_fft_lds(size_t T) { return sizeof(float2) * T + sizeof(float) * (T / 4 + 1); }
+// Noise by FFT (power-of-two windows, T >= 16, whose half-length complex spectrum and a quarter-period cosine table fit in
+// LDS): noise[t] = Re sum_{f=1}^{F} c_f e^{2 pi i f t / T}, c_f = A_f e^{i phi_f}, is the real inverse DFT of X[f] = c_f / 2 and
+// its mirror, so pairs of ticks z[n] = noise[2n] + i noise[2n + 1] are the inverse DFT of length M = T / 2 of
+//   Z[k] = (X[k] + X[k + M]) + i e^{2 pi i k / T} (X[k] - X[k + M]),  X[k + M] = conj(X[M - k]).
+// Decimation in time, three radix-2 stages at a time in registers: the first three on a thread's eight gathered inputs (the
+// bit reversal is in the gather), the last ones write the result.  Twiddles e^{2 pi i m / T}, m < T/2, come from
+// cos(2 pi m / T) for m <= T/4 staged in LDS: sin(2 pi m / T) = cos(2 pi (T/4 - m) / T), and past a quarter period cos and sin
+// follow from the quarter shift.  One workgroup per detector; what bounds it is its passes through LDS and the barriers
+// between them (64 detectors x 16,384 ticks: 21 us; radix-2 stages over the full
+// complex length took 67).
+inline size_t noise_fft_lds(size_t T) { return sizeof(float2) * (T / 2 + T / 32) + sizeof(float) * (T / 4 + 1); }
+
+struct NoiseFft {
+    float2 *xs;                     // [M], one float2 of padding every 16
+    const float *qc;
+    int32_t T;
+    __device__ __forceinline__ float2 &at(int32_t i) const { return xs[i + (i >> 4)]; }
+    __device__ __forceinline__ float2 root(int32_t m) const {                 // e^{2 pi i m / T}, 0 <= m < T / 2
+        const int32_t Q = T >> 2;
+        return m <= Q ? make_float2(qc[m], qc[Q - m]) : make_float2(-qc[T / 2 - m], qc[m - Q]);
+    }
+};
+// a + w b and a - w b, each product fused into the sum
+__device__ __forceinline__ void butterfly(float2 &a, float2 &b, float2 w) {
+    const float2 p = make_float2(fmaf(w.x, b.x, fmaf(-w.y, b.y, a.x)), fmaf(w.x, b.y, fmaf(w.y, b.x, a.y)));
+    b = make_float2(fmaf(-w.x, b.x, fmaf(w.y, b.y, a.x)), fmaf(-w.x, b.y, fmaf(-w.y, b.x, a.y)));
+    a = p;
+}
+// NS stages, the first of half-length h, on points j + h e.  Entry r of stage s has the factor of entry 0 times
+// e^{2 pi i r / 2^(s + 1)}: its quarter turns are exact, the eighth turn is looked up.
+template <int NS>
+__device__ __forceinline__ void fft_stages(const NoiseFft &f, int32_t j, int32_t h, float2 (&p)[8]) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int32_t m = j * (f.T / (2 * (h << s)));
+        const float2 w0 = f.root(m), w1 = s == 2 ? f.root(m + (f.T >> 3)) : w0;
+#pragma unroll
+        for (int r = 0; r < (1 << s); ++r) {
+            const float2 v = s == 2 && (r & 1) ? w1 : w0;
+            const float2 w = r > 0 && 2 * r >= (1 << s) ? make_float2(-v.y, v.x) : v;
+#pragma unroll
+            for (int e = r; e < (1 << NS); e += 2 << s) butterfly(p[e], p[e + (1 << s)], w);
+        }
+    }
+}
+template <int NS>
+__device__ __forceinline__ void fft_pass(const NoiseFft &f, int32_t h, float2 *out) {
+    const int32_t M = f.T >> 1;
+    for (int32_t b = threadIdx.x; b < M >> NS; b += blockDim.x) {
+        const int32_t j = b & (h - 1), i0 = ((b - j) << NS) + j;
+        float2 p[8];
+#pragma unroll
+        for (int e = 0; e < 1 << NS; ++e) p[e] = f.at(i0 + h * e);
+        fft_stages<NS>(f, j, h, p);
+#pragma unroll
+        for (int e = 0; e < 1 << NS; ++e) {
+            if (out) out[i0 + h * e] = p[e];
+            else f.at(i0 + h * e) = p[e];
+        }
+    }
+    __syncthreads();
+}
 
 __global__ __launch_bounds__(1024) void k_light_noise_fft(const float2 *__restrict__ coef, int32_t F, int32_t T,
                                                           int32_t log2T, const float *__restrict__ Ct,
                                                           float *__restrict__ nz) {
     extern __shared__ float2 xs[];
-    float *qc = (float *)(xs + T);
-    const int32_t d = blockIdx.x;
-    const int32_t Q = T >> 2;
-    const float2 *cf = coef + (int64_t)d * F;
-    for (int32_t i = threadIdx.x; i < T; i += blockDim.x) {
-        const float2 y = (i >= 1 && i <= F) ? cf[i - 1] : make_float2(0.0f, 0.0f);
-        xs[__builtin_bitreverse32((uint32_t)i) >> (32 - log2T)] = y;
-    }
-    for (int32_t m = threadIdx.x; m <= Q; m += blockDim.x) qc[m] = Ct[m];
+    const int32_t M = T >> 1, log2M = log2T - 1;
+    float *qc = (float *)(xs + M + M / 16);
+    const NoiseFft f{xs, qc, T};
+    const float2 *cf = coef + (int64_t)blockIdx.x * F;
+    for (int32_t m = threadIdx.x; m <= T >> 2; m += blockDim.x) qc[m] = Ct[m];
     __syncthreads();
-    for (int32_t half = 1; half < T; half <<= 1) {
-        const int32_t stride = T / (2 * half);                    // twiddle index step for this stage
-        for (int32_t k = threadIdx.x; k < T / 2; k += blockDim.x) {
-            const int32_t j = k & (half - 1);
-            const int32_t i0 = ((k - j) << 1) + j, i1 = i0 + half;
-            const int32_t m = j * stride;                         // < T / 2
-            float wr, wi;
-            if (m <= Q) {
-                wr = qc[m];
-                wi = qc[Q - m];
-            } else {
-                wr = -qc[T / 2 - m];
-                wi = qc[m - Q];
-            }
-            const float2 a = xs[i0], b = xs[i1];
-            const float tr = wr * b.x - wi * b.y, ti = fmaf(wr, b.y, wi * b.x);
-            xs[i0] = make_float2(a.x + tr, a.y + ti);
-            xs[i1] = make_float2(a.x - tr, a.y - ti);
+    for (int32_t b = threadIdx.x; b < M >> 3; b += blockDim.x) {
+        const int32_t k0 = (int32_t)(__builtin_bitreverse32((uint32_t)b) >> 1 >> (34 - log2M));
+        float2 p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int32_t k = k0 + (M >> 3) * ((e & 1) << 2 | (e & 2) | e >> 2);
+            float2 u = make_float2(0.0f, 0.0f), v = u;                        // 2 X[k], 2 X[k + M]
+            if (k >= 1 && k <= F) u = cf[k - 1];
+            if (k >= 1 && M - k <= F) v = cf[M - k - 1];
+            v.y = -v.y;
+            const float2 w = f.root(k), t = make_float2(u.x - v.x, u.y - v.y);
+            p[e] = make_float2(0.5f * fmaf(-w.x, t.y, fmaf(-w.y, t.x, u.x + v.x)),
+                               0.5f * fmaf(w.x, t.x, fmaf(-w.y, t.y, u.y + v.y)));
         }
-        __syncthreads();
+        fft_stages<3>(f, 0, 1, p);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f.at(8 * b + e) = p[e];
     }
-    float *o = nz + (int64_t)d * T;
-    for (int32_t i = threadIdx.x; i < T; i += blockDim.x) o[i] = xs[i].x;
+    __syncthreads();
+    float2 *out = (float2 *)(nz + (int64_t)blockIdx.x * T);
+    int32_t done = 3;
+    for (; log2M - done > 3; done += 3) fft_pass<3>(f, 1 << done, nullptr);
+    switch (log2M - done) {
+        case 3: fft_pass<3>(f, 1 << done, out); break;
+        case 2: fft_pass<2>(f, 1 << done, out); break;
+        case 1: fft_pass<1>(f, 1 << done, out); break;
+        default:
+            for (int32_t i = threadIdx.x; i < M; i += blockDim.x) out[i] = f.at(i);
+    }
 }
 
 // V for 8 consecutive ticks per thread: the response sum (pef row with Rp zeros in front, r padded to nrb * 8 taps)
@@ -509,7 +566,8 @@ void launch_light(lts_light *L, uint64_t event_id, const float *ipe, double *mu_
     }
     const float *nzpre = nullptr;
     if (L->F > 0 && L->fft_log2 > 0) {
-        k_light_noise_fft<<<(unsigned)nd, 1024, noise_fft_lds((size_t)T), st>>>(L->coef.p, L->F, T, L->fft_log2,
+        k_light_noise_fft<<<(unsigned)nd, (unsigned)std::min(1024, std::max(64, T / 16)), noise_fft_lds((size_t)T),
+                            st>>>(L->coef.p, L->F, T, L->fft_log2,
                                                                               L->Ct.p, L->nz.p);
         nzpre = L->nz.p;
     }
@@ -681,8 +739,8 @@ lts_status lts_light_create(int device, const lts_light_params *p, const float *
         ok(hipMemcpy(L->St.p, S.data(), sizeof(float) * T, hipMemcpyHostToDevice)) &&
         ok(hipMemset(L->xp.p, 0, sizeof(float) * std::max<size_t>(n_xp, 1))) &&
         ok(hipMemset(L->pef.p, 0, sizeof(float) * (nd * (L->Rp + T) + 8))) && ok(hipDeviceSynchronize());
-    // power-of-two windows up to 16384 ticks take the FFT noise path if the device grants the LDS it needs
-    if (st == LTS_OK && n_freq > 0 && T >= 4 && (T & (T - 1)) == 0 && noise_fft_lds(T) <= 160 * 1024) {
+    // power-of-two windows of 16 to 16384 ticks take the FFT noise path if the device grants the LDS it needs
+    if (st == LTS_OK && n_freq > 0 && T >= 16 && T <= 16384 && (T & (T - 1)) == 0) {
         if (hipFuncSetAttribute((const void *)k_light_noise_fft, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)noise_fft_lds(T)) == hipSuccess &&
             ok(L->nz.alloc(nd * T))) {

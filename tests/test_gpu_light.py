@@ -104,6 +104,15 @@ def test_light_decay_blocks(lt, OL, torch, taps, n_ticks):
     sim.close()
 
 
+@pytest.mark.parametrize("n_ticks,n_freq", [(8, 3), (16, 7), (32, 3), (64, 31), (128, 40), (256, 127), (2048, 1023), (16384, 8191)])
+def test_light_noise_transform_lengths(lt, OL, torch, n_ticks, n_freq):
+    """The noise transform with every number of last stages, spectra that fill the band, and the shortest window."""
+    lp = dataclasses.replace(W.Light(), n_det=3, n_ticks=n_ticks, group=1, max_trig=0, trunc=0.01)
+    rng = np.random.default_rng(n_ticks)
+    amp = rng.uniform(0.5, 2.0, n_freq).astype(np.float32)
+    check(lt, OL, torch, lp, np.zeros((3, n_ticks), np.float32), W.light_response(n_resp=5), amp, 11)
+
+
 def test_light_invalid_parameters(lt, torch):
     lp = W.Light()
     r, a = W.light_response(), W.light_noise_amplitudes()
