@@ -2331,38 +2331,40 @@ __global__ __launch_bounds__(kWG) void k_sum_merge(int64_t n_slots, SumWork sw) 
 // longest lists kept it running).  A 20,000-segment event has 13.5 million records of some 30 ticks, whose charges (1.6 GB)
 // are what bounds it: the pass and this kernel take 245 + 636 us instead of 1424, for a 500-segment event 37 + 18 instead of
 // 345 (16 lanes x 4 ticks a record: 848, 4 x 8: 740).
-constexpr int32_t kMergeLanes = 8, kMergeTicks = 8;   // ticks a lane at a time
+constexpr int32_t kMergeLanes = 8, kMergeTicks = 8;     // ticks a lane at a time
+constexpr int64_t kMergeBlocks = 1 << 17;               // (a large batch has more records than one launch has threads for)
 __global__ __launch_bounds__(kWG) void k_sum_merged(int64_t n_rec, SumWork sw) {
     const int lane = threadIdx.x % kMergeLanes;
-    const int64_t g = (int64_t)blockIdx.x * (kWG / kMergeLanes) + threadIdx.x / kMergeLanes;
-    if (g >= n_rec) return;
-    const PieceRef m = sw.mrec[g];
-    if (m.cell8 < sw.nS8) return;                       // a single piece
-    const PieceRef *rec = sw.rec + sw.mstart[g];
-    const int32_t n_mem = (int32_t)(sw.mstart[g + 1] - sw.mstart[g]), lp = (m.na + kAC - 1) / kAC * kAC;
-    float *out = sw.Sm + (int64_t)(m.cell8 - sw.nS8) * kAC;
-    for (int32_t t0 = lane; t0 < lp; t0 += kMergeLanes * kMergeTicks) {
-        float v[kMergeTicks];
+    const int64_t step = (int64_t)gridDim.x * (kWG / kMergeLanes);
+    for (int64_t g = (int64_t)blockIdx.x * (kWG / kMergeLanes) + threadIdx.x / kMergeLanes; g < n_rec; g += step) {
+        const PieceRef m = sw.mrec[g];
+        if (m.cell8 < sw.nS8) continue;                 // a single piece
+        const PieceRef *rec = sw.rec + sw.mstart[g];
+        const int32_t n_mem = (int32_t)(sw.mstart[g + 1] - sw.mstart[g]), lp = (m.na + kAC - 1) / kAC * kAC;
+        float *out = sw.Sm + (int64_t)(m.cell8 - sw.nS8) * kAC;
+        for (int32_t t0 = lane; t0 < lp; t0 += kMergeLanes * kMergeTicks) {
+            float v[kMergeTicks];
 #pragma unroll
-        for (int i = 0; i < kMergeTicks; ++i) v[i] = 0.0f;
-        for (int32_t k = 0; k < n_mem; k += 2) {         // two members' loads in flight
-            const PieceRef r0 = rec[k], r1 = rec[min(k + 1, n_mem - 1)];
-            const uint32_t o0 = (uint32_t)(m.a0 + t0 - r0.a0), n0 = (uint32_t)r0.na;
-            const uint32_t o1 = (uint32_t)(m.a0 + t0 - r1.a0), n1 = k + 1 < n_mem ? (uint32_t)r1.na : 0u;
-            const float *c0 = sw.S + (int64_t)r0.cell8 * kAC, *c1 = sw.S + (int64_t)r1.cell8 * kAC;
-            float x0[kMergeTicks], x1[kMergeTicks];
+            for (int i = 0; i < kMergeTicks; ++i) v[i] = 0.0f;
+            for (int32_t k = 0; k < n_mem; k += 2) {     // two members' loads in flight
+                const PieceRef r0 = rec[k], r1 = rec[min(k + 1, n_mem - 1)];
+                const uint32_t o0 = (uint32_t)(m.a0 + t0 - r0.a0), n0 = (uint32_t)r0.na;
+                const uint32_t o1 = (uint32_t)(m.a0 + t0 - r1.a0), n1 = k + 1 < n_mem ? (uint32_t)r1.na : 0u;
+                const float *c0 = sw.S + (int64_t)r0.cell8 * kAC, *c1 = sw.S + (int64_t)r1.cell8 * kAC;
+                float x0[kMergeTicks], x1[kMergeTicks];
 #pragma unroll
-            for (int i = 0; i < kMergeTicks; ++i) {
-                const uint32_t d = (uint32_t)(kMergeLanes * i);
-                x0[i] = o0 + d < n0 ? c0[o0 + d] : 0.0f;
-                x1[i] = o1 + d < n1 ? c1[o1 + d] : 0.0f;
+                for (int i = 0; i < kMergeTicks; ++i) {
+                    const uint32_t d = (uint32_t)(kMergeLanes * i);
+                    x0[i] = o0 + d < n0 ? c0[o0 + d] : 0.0f;
+                    x1[i] = o1 + d < n1 ? c1[o1 + d] : 0.0f;
+                }
+#pragma unroll
+                for (int i = 0; i < kMergeTicks; ++i) v[i] = (v[i] + x0[i]) + x1[i];   // an exact zero leaves v unchanged
             }
 #pragma unroll
-            for (int i = 0; i < kMergeTicks; ++i) v[i] = (v[i] + x0[i]) + x1[i];   // an exact zero leaves v unchanged
+            for (int i = 0; i < kMergeTicks; ++i)
+                if (t0 + kMergeLanes * i < lp) out[t0 + kMergeLanes * i] = v[i];
         }
-#pragma unroll
-        for (int i = 0; i < kMergeTicks; ++i)
-            if (t0 + kMergeLanes * i < lp) out[t0 + kMergeLanes * i] = v[i];
     }
 }
 
@@ -2375,7 +2377,8 @@ void launch_sum_merge(const SumWork &sw, int64_t n_slots, int64_t n_rec, hipStre
     }
     k_sum_merge<true><<<g, kWG, 0, st>>>(n_slots, sw);
     constexpr int64_t per = kWG / kMergeLanes;
-    if (n_rec > 0) k_sum_merged<<<(unsigned)((n_rec + per - 1) / per), kWG, 0, st>>>(n_rec, sw);
+    if (n_rec > 0)
+        k_sum_merged<<<(unsigned)std::min<int64_t>((n_rec + per - 1) / per, kMergeBlocks), kWG, 0, st>>>(n_rec, sw);
 }
 
 // Summed induction, one wavefront per work unit (active pixel, tile of kTileTicks ticks): lane t owns ticks

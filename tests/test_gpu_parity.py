@@ -724,6 +724,23 @@ def test_pixel_products_are_the_same_in_any_workgroup(lt, torch):
         assert np.array_equal(b["current"][po[i]:po[i + 1]], one["current"])
 
 
+def test_more_records_than_threads_of_a_launch(lt, torch):
+    """A batch of 64 spill-mix events has over 2^32 / 8 merged records: its last events are those of single calls."""
+    w = W.make_workload(3, n_events=64)
+    ctx = lt.Context.from_workload(w, reduce_mode=2)
+    offs = np.r_[0, np.cumsum([e.n for e in w.events])]
+    dev = {i: lt.to_device(w.events[i]) for i in (40, 63)}
+    cap = sum(ctx.plan(lt.to_device(e))["pixels"] for e in w.events)
+    out = ctx._alloc(cap, cap * w.electronics.max_packets // 4 + 4096, 64, True)
+    b = ctx.simulate_batch(lt.to_device(W.Segments.concat(w.events)), offs, w.event_ids, out=out)
+    po = b.event_pixel_offsets.cpu().numpy()
+    for i, d in dev.items():
+        one = ctx.simulate(d, event_id=w.event_ids[i])
+        n = int(po[i + 1] - po[i])
+        assert torch.equal(b.pixel_id[po[i]:po[i + 1]], one.pixel_id[:n])
+        assert torch.equal(b.current[po[i]:po[i + 1]], one.current[:n])
+
+
 def test_graph_replay_equals_direct_launches(lt, torch):
     """Calls replayed as HIP graphs (updated in place between events of different sizes, re-instantiated when the
     launch structure changes) give the same results as direct launches, with the program's own GPU work and
