@@ -34,7 +34,6 @@ PEAK_FP32_NONPACKED_TFLOPS = 256 * 4 * 16 * 2.4e9 * 2 / 1e12
 # The induction kernels run on the FP16 matrix cores (256 CUs x 4 SIMD x 512 multiply-adds x 2.4 GHz = 2516.6 TFLOP/s),
 # three half products for one FP32 product.
 PEAK_HALF_PAIR_TFLOPS = 256 * 4 * 512 * 2.4e9 * 2 / 1e12 / 3
-PEAK_FP64_TFLOPS = 78.6
 HBM_PEAK_GBS = 8000.0
 
 INDUCE_KERNEL = {"sorted": "k_induce_z", "atomic": "k_induce_z_atomic", "summed": "k_induce_summed_mma"}
@@ -427,7 +426,7 @@ def light_leg(ltsim, W, reps=10):
     ach = 2.0 * fma / (ms / 1e3) / 1e12
     return {"workload": f"light spill: {lp.n_det} detectors x {T} ticks of {lp.tick} ns, {K}-tap scintillation kernel",
             "ms_per_event": ms, "detector_ticks_per_s": lp.n_det * T / (ms / 1e3),
-            "scint_fp64_tflops_whole_call": ach, "frac_of_fp64_peak": ach / PEAK_FP64_TFLOPS}
+            "direct_sum_equivalent_fp64_tflops": ach}         # (the recursions execute a few products a tick)
 
 
 # ----------------------------------------------------------------------------------------------- oracle leg
