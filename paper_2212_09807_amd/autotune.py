@@ -5,10 +5,10 @@ call's mean segments per event, in lts_simulate, lts_simulate_batch and every ba
 
 * reduce mode, which fixes the unit of work: per-pair pixel-major with Kahan sums (one workgroup per active pixel,
   its pairs in segment order), per-pair segment-major with FP32 atomics (one workgroup per segment, its pairs in
-  pixel order), or sum-then-convolve (one wavefront per (active pixel, 512-tick tile) unit over the pixel's column
+  pixel order), or sum-then-convolve (one wavefront per (active pixel, tick range) unit over the pixel's column
   pieces);
-* tick tile (ticks per thread: 0 = automatic, 1, 2, 4, 8): the per-pair kernels' output ticks per thread; in the
-  summed mode 0 runs the 256-tick LDS-staged wavefront kernel, 8 the 512-tick register one, and 1, 2 or 4 the
+* tick tile (ticks per thread: 0 = automatic, the matrix-core kernels; 1, 2, 4, 8 the vector ones): the per-pair
+  kernels' output ticks per thread; in the summed mode 8 runs the 512-tick register kernel, and 1, 2 or 4 the
   pixel-per-workgroup kernel over the pieces;
 * induce slices (sorted mode: workgroups per pixel, one table slice each) and lane exchange (table windows shared
   across lanes).

@@ -1794,7 +1794,7 @@ __device__ __forceinline__ uint64_t lane_u64(uint64_t v, int j) {
 // per column: sort its segment list by key (first tick, segment index) into col_seg, then count the pieces and the
 // padded summed-charge length of its merged tick intervals.  For the 512-tick summed induction kernel every
 // interval's first tick is moved down to the residue it chooses (it makes every lane's table offsets aligned there);
-// the 256-tick kernel takes intervals as they are (align_res < 0).  The order depends only on the segments' charge
+// the matrix kernel takes intervals as they are (align_res < 0).  The order depends only on the segments' charge
 // boxes and their order within the event, so the sums are the same in a batch and alone.  The columns with segments
 // are listed first (k_sum_active); persistent wavefronts take them one at a time.  Sort by ranks (a key's place is
 // the number of smaller keys; keys are unique): lane i holds key i of a 64-key chunk and compares it with every key
