@@ -3311,6 +3311,8 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_atomic(DevParams P, ZTable 
             const int32_t gy0 = __builtin_amdgcn_readlane(y0, n - 1), gy1 = __builtin_amdgcn_readlane(y1, n - 1);
             const int32_t e = __builtin_amdgcn_readlane(ev, 0);
             const float bound = lane_value(qa, n - 1) * (float)kZaSegs;
+            q += n;
+            if (gx0 > gx1 || gy0 > gy1) continue;       // segments that reach no pixel: no rectangle to walk
             __syncthreads();                            // the previous group's segments are no longer read
             if (tid < n) st.seg[tid] = z;
             for (int32_t iy = gy0 + row; iy <= gy1; iy += kZaRows)
@@ -3323,7 +3325,6 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_atomic(DevParams P, ZTable 
                                 if (x != 0.0f) atomicAdd(&wrow[t], x);
                             });
                 }
-            q += n;
         }
     }
 }

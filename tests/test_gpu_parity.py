@@ -10,6 +10,7 @@ Bars (per output):
 import dataclasses
 import json
 import os
+import time
 
 import numpy as np
 import pytest
@@ -480,6 +481,31 @@ def test_sorted_and_atomic_agree(lt, torch):
 
 
 # ----------------------------------------------------------------------------------------------- edge cases
+
+@pytest.mark.parametrize("off", [(0,), (3,), (7,), (0, 1, 4, 7), tuple(range(8))])
+def test_atomic_segments_off_the_readout(lt, orc, torch, off):
+    """Atomic mode with segments that reach no pixel at the start, in the middle and at the end of a block of eight, in
+    neighbouring pairs and as whole blocks: the currents of the others, and no work for them (the call takes milliseconds;
+    a walk over a rectangle that they do not have would take seconds)."""
+    w = W.make_workload(1)
+    segs = w.events[0].subset(np.arange(0, 48))
+    away = (np.arange(48) // 8 % 2 == 0) & np.isin(np.arange(48) % 8, off)      # (every other block)
+    for c in ("x0", "x1"):
+        getattr(segs, c)[away] += np.float32(500.0)
+    w.events = [segs]
+    h, r, e, _ = check_event(lt, orc, w, mode=1)
+    assert len(r["pixels"]) > 50
+    ctx = lt.Context.from_workload(w, reduce_mode=1)
+    d = lt.to_device(segs)
+    out = ctx.simulate(d, event_id=w.event_ids[0])
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    ctx.simulate(d, event_id=w.event_ids[0], out=out)
+    torch.cuda.synchronize()
+    t = time.perf_counter() - t
+    print(f"off {off}: {len(r['pixels'])} pixels, max e_p {e.max():.2e}, {t * 1e3:.2f} ms")
+    assert t < 0.2
+
 
 def test_empty_event(lt, torch):
     w = W.make_workload(1)
