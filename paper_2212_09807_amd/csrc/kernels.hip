@@ -2588,6 +2588,7 @@ __global__ __launch_bounds__(kWG) void k_induce_summed(DevParams P, const SegInf
 // the time.  3 tiles per unit run 4 wavefronts per SIMD; 4 tiles (3 wavefronts) took 2 to 3 % longer, 2 tiles 10 % and
 // 1 tile 40 %: the charge is staged for fewer products.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
 constexpr int32_t kMmaSub = 256;                        // ticks of one tile
@@ -2605,6 +2606,9 @@ struct alignas(16) MmaStage {                           // LDS of one wavefront
     uint32_t s[2][8][kMmaCopy / 2];                     // [plane][shift] of the reversed charge: copy k holds position m + k at m
 };
 
+// Scale of a table column of zeros: its charge never sets a common scale and becomes zero under any.
+constexpr int32_t kZeroColumn = 1 << 20;
+
 // Planes of the response table: half pairs of column b scaled by 2^exps[b], in the layout of the FP32 columns.
 __global__ __launch_bounds__(kWG) void k_table_halves(const float *__restrict__ Rpad, int32_t col_len,
                                                       _Float16 *__restrict__ hi, _Float16 *__restrict__ lo,
@@ -2618,7 +2622,7 @@ __global__ __launch_bounds__(kWG) void k_table_halves(const float *__restrict__ 
     if (lane_id() == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     for (int i = 0; i < kWG / 64; ++i) m = fmaxf(m, red[i]);
-    const int32_t e = m > 0.0f ? 14 - ilogbf(m) : 0;
+    const int32_t e = m > 0.0f ? 14 - ilogbf(m) : kZeroColumn;
     if (threadIdx.x == 0) exps[blockIdx.x] = e;
     for (int32_t k = threadIdx.x; k < col_len; k += kWG) {
         const float x = ldexpf(Rpad[base + k], e);
@@ -2834,9 +2838,11 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
 // (the columns' mirror images folded onto them) and tick: C[bin][a].  With the bins as the contraction,
 // Z[a][tau] = sum_bin C[bin][a] R[bin][tau] is a matrix product with no padding but the rounding of ticks to 16, of
 // table ticks to 16 and of the bins to whole octets (8 consecutive j of one i), and the current is the sum along Z's
-// anti-diagonals, I[n] = sum_a Z[a][n - a + T_R - 1].  Both factors are half pairs as above; the table octets are laid
-// out so that 16 table ticks of an octet are 256 consecutive bytes (a 16x16x32 operand of four octets is four such
-// runs).  Anti-diagonals: lane (tau, g) holds rows a = 4g .. 4g + 3 of a tile, so row a moves up by a lanes within its 16
+// anti-diagonals, I[n] = sum_a Z[a][n - a + T_R - 1].  Both factors are half pairs as above.  The charge's scale is one
+// per staged tick (a row of Z), the largest that its own values bear, each times its column's scale: a tick of little
+// charge keeps its bits beside a bright one, and the scales are taken off before ticks meet in a sum.  The table octets
+// are laid out so that 16 table ticks of an octet are 256 consecutive bytes (a 16x16x32 operand of four octets is four
+// such runs).  Anti-diagonals: lane (tau, g) holds rows a = 4g .. 4g + 3 of a tile, so row a moves up by a lanes within its 16
 // (DPP row shifts; what leaves the 16 belongs to the next tile), and the four groups are added by lane swaps once per
 // 16 output ticks.
 // A workgroup stages 32 ticks x 32 octets of C at a time, and each wavefront owns a range of output ticks (it also
@@ -2850,16 +2856,18 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
 // leave one workgroup a CU (8.3 ms, tracks 1.67).  Atomic units of 8 segments (4: 4.7 ms, 8: 3.06, 16: 3.3).
 //   Measured against the vector kernels (45 x 45 x 1950 table unless said): sorted, 3000 segments 91.3 -> 8.6 ms; atomic,
 // 800 segments 50 -> 2.8 ms; one track on 20 x 31 x 1001 1.106 -> 0.072 ms, 64 such tracks 9.2 -> 1.18.
-// Error against 64 bits (relative to the largest current): 1.4e-6 -> 1.3e-7, 2.2e-6 -> 1.7e-7 atomic.
+// Error against 64 bits, relative to all currents 1.7e-6 -> 1.5e-7, 9.5e-7 -> 1.4e-7 atomic; of a pixel relative to itself,
+// median and largest, 2.3e-6 and 1.0e-5 -> 1.2e-7 and 1.3e-6, a track's 4e-7 and 2.1e-6 -> 1.3e-7 and 7.8e-7.  (With one
+// scale for a group, 1 % less time, pixels that only the clouds' tails reach were off by up to 3e-3.)
 constexpr int32_t kZgSegs = 16;                         // segments of a group
 constexpr int32_t kZgSpan = 128;                        // ticks of a group's charge (unless one segment has more)
 constexpr int32_t kZgTicks = 32;                        // ticks and octets staged at a time
 constexpr int32_t kZgOct = 32;
+constexpr int32_t kZgTop = 127 + 14;                    // biased exponent of a tick's largest scaled charge: below 2^15
 
 struct ZTable {                                         // half planes of the table by octets of bins
     const u32x4 *hi, *lo;                               // [bx * njo][trq]: 8 halves
     const int32_t *exps;                                // [bx * by] scale of a bin
-    const int32_t *emin;                                // [bx * njo] smallest scale at or beyond an octet in both indices
     int32_t njo, trq;
 };
 
@@ -2876,7 +2884,9 @@ struct ZJob {
 };
 
 struct alignas(16) ZStage {
-    u32x4 c[2][2][kZgOct][16];                          // [plane][16 ticks][octet][tick]: 8 halves
+    u32x4 c[2][2][kZgOct][16];                          // [plane][16 ticks][octet][tick]: 8 halves (first 8 values, 4 a plane)
+    i32x4 ex[kZgOct][2];                                // scales of an octet's bins
+    int32_t top[2][kZgTicks];                           // [stage & 1][tick]: largest exponent of charge x column scale
     ZSeg seg[kZgSegs];
     ZJob job[4 * kZgSegs];
     uint32_t at[kZgOct];                                // byte offset of an octet's table column
@@ -2904,31 +2914,10 @@ __global__ __launch_bounds__(kWG) void k_table_octets(const float *__restrict__ 
     }
 }
 
-// emin[i][jo] = min over i' >= i, jo' >= jo of the bins' scales (one workgroup; the table has at most 256 x 32 octets).
-__global__ __launch_bounds__(kWG) void k_table_emin(const int32_t *__restrict__ exps, int32_t bx, int32_t by,
-                                                    int32_t njo, int32_t *emin) {
-    for (int32_t i = threadIdx.x; i < bx; i += kWG) {     // along j
-        int32_t m = INT32_MAX;
-        for (int32_t jo = njo - 1; jo >= 0; --jo) {
-            for (int32_t j = 8 * jo; j < min(8 * jo + 8, by); ++j) m = min(m, exps[i * by + j]);
-            emin[i * njo + jo] = m;
-        }
-    }
-    __syncthreads();
-    for (int32_t jo = threadIdx.x; jo < njo; jo += kWG) { // along i
-        int32_t m = INT32_MAX;
-        for (int32_t i = bx - 1; i >= 0; --i) {
-            m = min(m, emin[i * njo + jo]);
-            emin[i * njo + jo] = m;
-        }
-    }
-}
-
 void launch_table_octets(const float *Rpad, int32_t bx, int32_t by, int32_t t_r, int32_t col_len, int32_t trq,
-                         const int32_t *exps, void *hi, void *lo, int32_t *emin, hipStream_t st) {
+                         const int32_t *exps, void *hi, void *lo, hipStream_t st) {
     const int32_t njo = (by + 7) / 8;
     k_table_octets<<<(unsigned)(bx * njo), kWG, 0, st>>>(Rpad, col_len, t_r, by, njo, trq, exps, (u32x4 *)hi, (u32x4 *)lo);
-    k_table_emin<<<1, kWG, 0, st>>>(exps, bx, by, njo, emin);
 }
 
 template <int R>
@@ -2989,19 +2978,20 @@ __device__ __forceinline__ void z_dispatch(int32_t nk, const ZStage &st, __amdgp
 }
 
 // Adds the current of the group st.seg[0 .. n_seg) on the pixel with centre bins (uc, vc) through emit(n, value), n in
-// [0, n_ticks), called by 32 lanes at a time, never for the same n by two wavefronts between barriers.  `bound`: an upper
-// bound of the group's charge.  All threads of the workgroup call it; it starts and ends with a barrier.
+// [0, n_ticks), called by 32 lanes at a time, never for the same n by two wavefronts between barriers.  All threads of the
+// workgroup call it; it starts and ends with a barrier.
 template <int WG, class Emit>
 __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZStage &st, int32_t n_seg, int32_t A0,
-                                        int32_t A1, float bound, int32_t uc, int32_t vc,
-                                        const float *__restrict__ cells, Emit emit) {
+                                        int32_t A1, int32_t uc, int32_t vc, const float *__restrict__ cells, Emit emit) {
     const int tid = threadIdx.x, lane = tid & 63, lj = lane & 15, lg = lane >> 4;
     const int32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t TR = P.t_r, NT = P.nticks, n_tau = Z.trq / 16;
-    const int32_t ebound = __builtin_bit_cast(int32_t, bound) >> 23;
     const int32_t plane = P.bx * Z.njo * Z.trq * 16;    // bytes (at most 2^30)
     const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc((void *)Z.hi, (short)0, plane, kBufferWord3);
     const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc((void *)Z.lo, (short)0, plane, kBufferWord3);
+    constexpr int32_t kNone = -(1 << 24);               // exponent of a tick without charge
+    int32_t par = 0;                                    // the stage's half of st.top
+    if (tid < 2 * kZgTicks) (&st.top[0][0])[tid] = kNone;
     __syncthreads();                                    // the group's segments are in place
     for (int32_t ac = A0; ac <= A1; ac += kZgTicks) {
         const int32_t n0 = ac - TR + 1;                 // tick of output 0
@@ -3049,24 +3039,28 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
         if (wv == 0 && has) st.job[__builtin_popcountll(jobs & ((1ull << lane) - 1ull))] = jb;
         const int32_t jo0 = j0 / 8, nj = j1 / 8 - jo0 + 1, n_oct = (i1 - i0 + 1) * nj;
         const bool two = alast >= 16;
-        const int32_t N = min(max(min(141 - ebound, 126) + Z.emin[i0 * Z.njo + jo0], -126), 126);
-        const float down = ldexpf(1.0f, -N);
         // this wavefront's output tiles of 16 ticks
         const int32_t m_first = max(-n0, 0) / 16, m_last = min(TR + alast - 1, NT - 1 - n0) / 16;
         // (an even number: which tiles pair up, and so the order of the sums, must not depend on the wavefronts)
         const int32_t per = ((m_last - m_first + WG / 64) / (WG / 64) + 1) & ~1;
         const int32_t m_lo = m_first + wv * per, m_hi = min(m_lo + per, m_last + 1);
         __syncthreads();                                // the images are in place
-        for (int32_t o0 = 0; o0 < n_oct; o0 += kZgOct) {
+        for (int32_t o0 = 0; o0 < n_oct; o0 += kZgOct, par ^= 1) {
             const int32_t no = min(kZgOct, n_oct - o0), nk = (no + 3) / 4, nq = nk <= 2 ? 8 : nk <= 4 ? 16 : nk <= 6 ? 24 : 32;
             // stage: thread (tick, octet) sums its eight bins over the images, in order
+            const int32_t a = tid & 31;
+            int32_t most = kNone;
             for (int32_t q = tid >> 5; q < nq; q += WG / 32) {
-                const int32_t a = tid & 31, o = o0 + min(q, no - 1), ii = o / nj;
+                const int32_t o = o0 + min(q, no - 1), ii = o / nj;
                 const int32_t i = i0 + ii, jo = jo0 + o - ii * nj, jb0 = jo * 8;
                 if (a == 0) st.at[q] = (uint32_t)((i * Z.njo + jo) * Z.trq) * 16u;
                 float c[8];
+                int32_t ex[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) c[k] = 0.0f;
+                for (int k = 0; k < 8; ++k) {
+                    c[k] = 0.0f;
+                    ex[k] = Z.exps[i * P.by + min(jb0 + k, P.by - 1)];
+                }
                 // the images with a bin in one of the wavefront's two octets
                 bool near = false;
                 if (lane < n_job) {
@@ -3077,9 +3071,6 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
                         near |= iw >= g.i0 && iw <= g.i1 && jw + 7 >= g.j0 && jw <= g.j1;
                     }
                 }
-                int32_t ex[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) ex[k] = Z.exps[i * P.by + min(jb0 + k, P.by - 1)];
                 uint64_t mask = __ballot(near);
                 // adds the next kImg images (in order) to c, all their loads in flight at once
                 auto add = [&](auto kImg) {
@@ -3112,10 +3103,30 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
                     if (__builtin_popcountll(mask) > 4) add(std::integral_constant<int, 8>());
                     else add(std::integral_constant<int, 4>());
                 }
+                st.c[0][a >> 4][q][a & 15] = __builtin_bit_cast(u32x4, (floatx4){c[0], c[1], c[2], c[3]});
+                st.c[1][a >> 4][q][a & 15] = __builtin_bit_cast(u32x4, (floatx4){c[4], c[5], c[6], c[7]});
+                if (a == 0) {
+                    st.ex[q][0] = (i32x4){ex[0], ex[1], ex[2], ex[3]};
+                    st.ex[q][1] = (i32x4){ex[4], ex[5], ex[6], ex[7]};
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    most = max(most, c[k] == 0.0f ? kNone : (__builtin_bit_cast(int32_t, fabsf(c[k])) >> 23) - ex[k]);
+            }
+            most = max(most, __shfl_xor(most, 32));
+            if (lane < 32) atomicMax(&st.top[par][a], most);
+            __syncthreads();                            // the ticks' exponents are complete
+            if (tid < kZgTicks) st.top[par ^ 1][tid] = kNone;
+            // the halves, in place
+            const int32_t N = kZgTop - st.top[par][a];
+            for (int32_t q = tid >> 5; q < nq; q += WG / 32) {
+                const i32x4 e0 = st.ex[q][0], e1 = st.ex[q][1];
+                const floatx4 c0 = __builtin_bit_cast(floatx4, st.c[0][a >> 4][q][a & 15]);
+                const floatx4 c1 = __builtin_bit_cast(floatx4, st.c[1][a >> 4][q][a & 15]);
                 half8 h, l;
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    const float y = ldexpf(c[k], N - ex[k]);
+                    const float y = k < 4 ? ldexpf(c0[k & 3], N - e0[k & 3]) : ldexpf(c1[k & 3], N - e1[k & 3]);
                     h[k] = (_Float16)y;
                     l[k] = (_Float16)(y - (float)h[k]);
                 }
@@ -3124,6 +3135,11 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
             }
             __syncthreads();
             if (m_lo < m_hi) {
+                int32_t dn[2][4];                       // the lane's rows' scales
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) dn[b][r] = st.top[par][16 * b + 4 * lg + r] - kZgTop;
                 float O[4] = {0.0f, 0.0f, 0.0f, 0.0f};
                 for (int32_t t = m_lo - 2; t < m_hi; t += 2) {
                     const bool v0 = t >= 0 && t < n_tau, v1 = t + 1 >= 0 && t + 1 < n_tau;
@@ -3143,7 +3159,9 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
 #pragma unroll
                             for (int y = 0; y < 2; ++y) {
                                 if ((b == 1 && !two) || !(y ? v1 : v0)) continue;
-                                const floatx4 d = D[b][y];
+                                floatx4 d;
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) d[r] = ldexpf(D[b][y][r], dn[b][r]);
                                 const float lo = d[0] + row_up<1>(d[1]) + (row_up<2>(d[2]) + row_up<3>(d[3]));
                                 const float hi = row_down<15>(d[1]) + (row_down<14>(d[2]) + row_down<13>(d[3]));
                                 // row g moves up by 4 g more
@@ -3156,7 +3174,7 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
                     }
                     const float y0 = rows_sum(O[0]), y1 = rows_sum(O[1]);
                     const int32_t m = t + (lg & 1), n = n0 + 16 * m + lj;
-                    if (lane < 32 && m >= m_lo && m < m_hi && n >= 0 && n < NT) emit(n, (lg ? y1 : y0) * down);
+                    if (lane < 32 && m >= m_lo && m < m_hi && n >= 0 && n < NT) emit(n, lg ? y1 : y0);
                     O[0] = O[2];
                     O[1] = O[3];
                     O[2] = O[3] = 0.0f;
@@ -3169,16 +3187,14 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
 
 // Loads the group that starts at list entry q of [q, end) into st.seg: the longest run of at most kZgSegs entries whose
 // ticks span at most kZgSpan (one entry at least).  id(k) is entry k's segment.  Every wavefront finds the same group;
-// the first one writes it.  Returns its length; [A0, A1] its ticks (A1 < A0: no charge), bound a bound of its charge.
+// the first one writes it.  Returns its length; [A0, A1] its ticks (A1 < A0: no charge).
 template <class Id>
 __device__ __forceinline__ int32_t z_load_group(const DevParams &P, const SegInfo *__restrict__ si, int64_t q, int64_t end,
-                                                int32_t uc, int32_t vc, Id id, ZStage &st, int32_t &A0, int32_t &A1,
-                                                float &bound) {
+                                                int32_t uc, int32_t vc, Id id, ZStage &st, int32_t &A0, int32_t &A1) {
     const int lane = lane_id();
     const int32_t cnt = (int32_t)min<int64_t>(kZgSegs, end - q);
     ZSeg z{0, 0, 0, 0, 0, INT32_MAX, 0, 0, 0};
     int32_t lo = INT32_MAX, hi = INT32_MIN;
-    float qa = 0.0f;
     if (lane < cnt) {
         const SegInfo &g = si[id(q + lane)];
         const bool any = max(g.u0, uc - P.bx) <= min(g.u0 + g.nu - 1, uc + P.bx - 1) &&
@@ -3187,24 +3203,20 @@ __device__ __forceinline__ int32_t z_load_group(const DevParams &P, const SegInf
             z = ZSeg{g.cell_off, g.u0, g.nu, g.v0, g.nv, g.a0, g.na, g.na_pad, 0};
             lo = g.a0;
             hi = g.a0 + g.na - 1;
-            qa = fabsf(g.q_a);
         }
     }
 #pragma unroll
     for (int d = 1; d < kZgSegs; d <<= 1) {              // running span over the entries
         const int32_t x = __shfl_up(lo, d), y = __shfl_up(hi, d);
-        const float b = __shfl_up(qa, d);
         if (lane >= d) {
             lo = min(lo, x);
             hi = max(hi, y);
-            qa = fmaxf(qa, b);
         }
     }
     const bool fits = lane < cnt && (lane == 0 || (int64_t)hi - lo < kZgSpan);
     const int32_t n = __builtin_ctzll(~__ballot(fits));  // the entries that fit are a prefix
     A0 = __builtin_amdgcn_readlane(lo, n - 1);
     A1 = __builtin_amdgcn_readlane(hi, n - 1);
-    bound = lane_value(qa, n - 1) * (float)kZgSegs;
     if (threadIdx.x < 64 && lane < n) st.seg[lane] = z;
     return n;
 }
@@ -3235,9 +3247,8 @@ __global__ __launch_bounds__(WG, 512 / WG) void k_induce_z(DevParams P, ZTable Z
         const int64_t pe = slot_off[slot + 1];
         for (int64_t q = slot_off[slot]; q < pe;) {
             int32_t A0, A1;
-            float bound;
-            const int32_t n = z_load_group(P, si, q, pe, uc, vc, [&](int64_t k) { return pairs[k]; }, st, A0, A1, bound);
-            z_group<WG>(P, Z, st, n, A0, A1, bound, uc, vc, cells, [&](int32_t t, float x) {
+            const int32_t n = z_load_group(P, si, q, pe, uc, vc, [&](int64_t k) { return pairs[k]; }, st, A0, A1);
+            z_group<WG>(P, Z, st, n, A0, A1, uc, vc, cells, [&](int32_t t, float x) {
                 const float y = x - s_cmp[t], z = s_sum[t] + y;
                 s_cmp[t] = (z - s_sum[t]) - y;
                 s_sum[t] = z;
@@ -3277,7 +3288,6 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_atomic(DevParams P, ZTable 
             const int32_t cnt = (int32_t)(end - q);
             ZSeg z{0, 0, 0, 0, 0, INT32_MAX, 0, 0, 0};
             int32_t lo = INT32_MAX, hi = INT32_MIN, x0 = INT32_MAX, x1 = -1, y0 = INT32_MAX, y1 = -1, area = 0, ev = -1;
-            float qa = 0.0f;
             if (lane < cnt) {
                 const SegInfo &g = si[q + lane];
                 ev = g.event;
@@ -3287,7 +3297,6 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_atomic(DevParams P, ZTable 
                     hi = g.a0 + g.na - 1;
                     x0 = g.ix0; x1 = g.ix1; y0 = g.iy0; y1 = g.iy1;
                     area = g.n_pairs;
-                    qa = fabsf(g.q_a);
                 }
             }
             const bool same = ev == __builtin_amdgcn_readlane(ev, 0);
@@ -3295,11 +3304,9 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_atomic(DevParams P, ZTable 
             for (int d = 1; d < kZaSegs; d <<= 1) {
                 const int32_t a = __shfl_up(lo, d), b = __shfl_up(hi, d), c = __shfl_up(x0, d), e = __shfl_up(x1, d);
                 const int32_t f = __shfl_up(y0, d), h = __shfl_up(y1, d), k = __shfl_up(area, d);
-                const float m = __shfl_up(qa, d);
                 if (lane >= d) {
                     lo = min(lo, a); hi = max(hi, b); x0 = min(x0, c); x1 = max(x1, e); y0 = min(y0, f); y1 = max(y1, h);
                     area = max(area, k);
-                    qa = fmaxf(qa, m);
                 }
             }
             const bool fits = lane < cnt && (lane == 0 || (same && (int64_t)hi - lo < kZgSpan &&
@@ -3310,7 +3317,6 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_atomic(DevParams P, ZTable 
             const int32_t gx0 = __builtin_amdgcn_readlane(x0, n - 1), gx1 = __builtin_amdgcn_readlane(x1, n - 1);
             const int32_t gy0 = __builtin_amdgcn_readlane(y0, n - 1), gy1 = __builtin_amdgcn_readlane(y1, n - 1);
             const int32_t e = __builtin_amdgcn_readlane(ev, 0);
-            const float bound = lane_value(qa, n - 1) * (float)kZaSegs;
             q += n;
             if (gx0 > gx1 || gy0 > gy1) continue;       // segments that reach no pixel: no rectangle to walk
             __syncthreads();                            // the previous group's segments are no longer read
@@ -3320,7 +3326,7 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_atomic(DevParams P, ZTable 
                     const int32_t slot = __builtin_amdgcn_readfirstlane(pix_slot[(int64_t)e * P.npx + iy * P.nx + ix]);
                     if (slot < 0) continue;
                     float *wrow = wave + (int64_t)slot * NT;
-                    z_group<kWG>(P, Z, st, n, A0, A1, bound, ix * P.nsub + P.nsub / 2, iy * P.nsub + P.nsub / 2, cells,
+                    z_group<kWG>(P, Z, st, n, A0, A1, ix * P.nsub + P.nsub / 2, iy * P.nsub + P.nsub / 2, cells,
                             [&](int32_t t, float x) {
                                 if (x != 0.0f) atomicAdd(&wrow[t], x);
                             });
@@ -3345,9 +3351,8 @@ __global__ __launch_bounds__(kWG, 2) void k_induce_z_pairs(DevParams P, ZTable Z
         const int32_t uc = (p % P.nx) * P.nsub + P.nsub / 2, vc = (p / P.nx) * P.nsub + P.nsub / 2;
         for (int64_t q = slot_off[slot]; q < slot_off[slot + 1]; ++q) {
             int32_t A0, A1;
-            float bound;
-            z_load_group(P, si, q, q + 1, uc, vc, [&](int64_t k) { return pairs[k]; }, st, A0, A1, bound);
-            z_group<kWG>(P, Z, st, 1, A0, A1, bound, uc, vc, cells, [&](int32_t t, float x) { sm[t] += x; });
+            z_load_group(P, si, q, q + 1, uc, vc, [&](int64_t k) { return pairs[k]; }, st, A0, A1);
+            z_group<kWG>(P, Z, st, 1, A0, A1, uc, vc, cells, [&](int32_t t, float x) { sm[t] += x; });
             __syncthreads();
             float *row = out + q * NT;
             for (int n = tid; n < NT; n += kWG) {
@@ -3457,7 +3462,7 @@ __global__ __launch_bounds__(kWG) void k_clip_columns(DevParams P, SumWork sw, c
 }
 
 static ZTable z_table(const Table &T) {
-    return ZTable{(const u32x4 *)T.zhi, (const u32x4 *)T.zlo, T.exps, T.zemin, T.njo, T.trq};
+    return ZTable{(const u32x4 *)T.zhi, (const u32x4 *)T.zlo, T.exps, T.njo, T.trq};
 }
 
 // The grid's dynamic LDS may exceed 64 KB with the static stage: the limit is raised once per device.

@@ -48,10 +48,9 @@ struct Table {
     const double *prefix = nullptr;          // [bx * by][t_r + 1] FP64 prefix sums of each column
     const void *hi = nullptr, *lo = nullptr; // [bx * by][col_len] half pairs of each column scaled by 2^exps[column]
     const int32_t *exps = nullptr;           // [bx * by]
-    // the same half pairs by octets of bins (8 consecutive j): [bx * njo][trq] of 8 halves; smallest scale at or beyond an
-    // octet in both indices; prefix sums added over the pixels that reach a column, per offset within a pixel (or null)
+    // the same half pairs by octets of bins (8 consecutive j): [bx * njo][trq] of 8 halves; prefix sums added over the
+    // pixels that reach a column, per offset within a pixel (or null)
     const void *zhi = nullptr, *zlo = nullptr;
-    const int32_t *zemin = nullptr;
     int32_t njo = 0, trq = 0;
     const double *cls = nullptr;             // [n_sub * n_sub][t_r + 1]
 };
@@ -131,7 +130,7 @@ void launch_table_halves(const float *Rpad, int32_t n_col, int32_t col_len, void
                          hipStream_t st);
 
 void launch_table_octets(const float *Rpad, int32_t bx, int32_t by, int32_t t_r, int32_t col_len, int32_t trq,
-                         const int32_t *exps, void *hi, void *lo, int32_t *emin, hipStream_t st);
+                         const int32_t *exps, void *hi, void *lo, hipStream_t st);
 void launch_clip_classes(const DevParams &P, const double *prefix, double *cls, hipStream_t st);
 hipError_t allow_z_lds();
 // the automatic per-pair induction (mode 0 sorted, 1 atomic) and its materialised form

@@ -67,7 +67,7 @@ struct lts_context {
     bool has_table = false;
     DevBuf Rpad, prefix;
     DevBuf Rhalf, Rexp;              // the table's half pairs (high plane, then low) and their column scales
-    DevBuf Roct, Remin, Rclass;      // the half pairs by octets of bins, the octets' smallest scales, the clip classes
+    DevBuf Roct, Rclass;             // the half pairs by octets of bins, the clip classes
     std::vector<float> table_host;   // kept to build server lanes
     int32_t t_r = 0, b_x = 0, b_y = 0;
     // scratch pool
@@ -246,8 +246,9 @@ constexpr lts_status kNotAdmitted = LTS_ERR_NOT_READY;
 std::vector<DevBuf *> pool_buffers(lts_context *c) {
     return {&c->ev_cnt, &c->mask, &c->col_seg_off, &c->col_cursor, &c->col_seg, &c->col_tmp, &c->piece_off,
             &c->s_off, &c->piece, &c->pdesc, &c->S, &c->list_off, &c->list, &c->rec, &c->mlist_off, &c->m_off,
-            &c->mrec, &c->Sm, &c->segc, &c->part, &c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Roct, &c->Remin, &c->Rclass,
-            &c->si, &c->cell_off, &c->pix_cnt, &c->cursor, &c->pix_slot, &c->slot_gp, &c->slot_off, &c->pairs_u, &c->pairs, &c->cells, &c->pk_tick, &c->pk_adc,
+            &c->mrec, &c->Sm, &c->segc, &c->part, &c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Roct, &c->Rclass,
+            &c->si, &c->cell_off, &c->pix_cnt, &c->cursor, &c->pix_slot, &c->slot_gp, &c->slot_off, &c->pairs_u,
+            &c->pairs, &c->cells, &c->pk_tick, &c->pk_adc,
             &c->pk_flag, &c->pk_off, &c->hdr, &c->scan_tmp, &c->ev_off, &c->ev_ids, &c->report_tmp, &c->counts_tmp,
             &c->red_head, &c->red_start, &c->order};
 }
@@ -256,7 +257,7 @@ std::vector<DevBuf *> pool_buffers(lts_context *c) {
 // persist across calls); every buffer is grown again to the exact size the next call needs.  The caller makes sure
 // no queued work still uses them.
 void release_scratch(lts_context *c) {
-    const DevBuf *kept[] = {&c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Roct, &c->Remin, &c->Rclass, &c->mask};
+    const DevBuf *kept[] = {&c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Roct, &c->Rclass, &c->mask};
     for (DevBuf *b : pool_buffers(c))
         if (std::find(std::begin(kept), std::end(kept), b) == std::end(kept)) free_buf(*b);
 }
@@ -395,7 +396,6 @@ Table table_of(lts_context *c) {
     T.trq = (c->t_r + 15) / 16 * 16;
     T.zhi = c->Roct.p;
     T.zlo = as<uint16_t>(c->Roct) + (size_t)c->b_x * T.njo * T.trq * 8;
-    T.zemin = as<int32_t>(c->Remin);
     T.cls = as<double>(c->Rclass);
     return T;
 }
@@ -1094,9 +1094,8 @@ lts_status lts_set_response(lts_context *c, const float *R, int32_t t_r, int32_t
     const int32_t njo = (b_y + 7) / 8, trq = (t_r + 15) / 16 * 16;
     const size_t oct = (size_t)b_x * njo * trq * 8;      // halves of one plane
     if ((r = ensure(c, c->Roct, 2 * sizeof(uint16_t) * oct))) return r;
-    if ((r = ensure(c, c->Remin, sizeof(int32_t) * (size_t)b_x * njo))) return r;
     launch_table_octets(as<float>(c->Rpad), b_x, b_y, t_r, col_len, trq, as<int32_t>(c->Rexp), c->Roct.p,
-                        as<uint16_t>(c->Roct) + oct, as<int32_t>(c->Remin), nullptr);
+                        as<uint16_t>(c->Roct) + oct, nullptr);
     DevParams tab = c->P;                               // (the context's own are set when nothing can fail any more)
     tab.t_r = t_r;
     tab.bx = b_x;

@@ -1160,6 +1160,72 @@ def test_group_product_edges(lt, orc, torch, mode, n_ticks, t_r, b_x, b_y, n_sub
         c.close()
 
 
+def _bright_and_faint():
+    """Two deposits a hundred thousand times weaker than their neighbours in the same pixels, 60 and 90 ticks behind them,
+    and a track; charge that only diffusion's tails bring to the outer pixels."""
+    w = W.make_workload(1)
+    p = np.array([[12.0, 13.0, 3.0], [12.0, 13.0, 3.0], [14.1, 13.4, 6.0], [14.1, 13.4, 6.0]])
+    t = [0.0, 6.0, 0.0, 9.0]
+    w.events = [W.Segments.concat([W.make_segments(p, p + [0.02, 0.01, 0.005], [2.0, 2e-5, 1.0, 1e-5], t0=t, t1=t),
+                                   w.events[0].subset(np.arange(0, 200, 9))])]
+    return w
+
+
+def _hard_table(w, kind):
+    """corner: a round reach (zeros in the table's corner); padded: zeros past the pad's third of the reach; units: the
+    corner table in other units; wide: columns whose peaks span twelve decades."""
+    t = W.response_table(w.table, w.readout, w.physics.v_drift).copy()
+    i, j = np.meshgrid(np.arange(w.table.b_x), np.arange(w.table.b_y), indexing="ij")
+    if kind in ("corner", "units"):
+        t[:, np.hypot(i, j) > 9.5] = 0.0
+    if kind == "padded":
+        t[:, j >= 6] = 0.0
+    if kind == "wide":
+        t *= np.float32(10.0) ** -((i + j) * 2 // 3)
+    return np.ascontiguousarray(t * np.float32(1e-6) if kind == "units" else t, dtype=np.float32)
+
+
+def check_faint(lt, orc, mode, rt, kind):
+    """The matrix-core currents of every pixel are as near to the oracle as the FP32 vector kernels' of the same mode, each
+    relative to its own norm (down to 1e-7 of the brightest pixel's, FP32's resolution of it), and so are the ticks that
+    only a weak deposit reaches behind a strong one in its pixel.  The cells' own error is in both; the products may add
+    TOL_EDGE, ten times what half pairs and an FP32 sum of some thousand products come to."""
+    w = _bright_and_faint()
+    table = _hard_table(w, kind)
+    (_, a), (_, b) = run_gpu(lt, w, mode=mode, table=table), run_gpu(lt, w, mode=mode, table=table, rt=rt)
+    assert np.array_equal(a["pixel_id"], b["pixel_id"])
+    o = orc.simulate(w, 0, table=table, with_packets=False)
+    row = np.searchsorted(a["pixel_id"], o["pixels"])
+    ref, ga, gb = o["wave"], a["current"][row].astype(np.float64), b["current"][row].astype(np.float64)
+    norm = np.linalg.norm(ref, axis=1)
+    k = norm > 1e-7 * norm.max()
+    ea, eb = (np.linalg.norm(g - ref, axis=1)[k] / norm[k] for g in (ga, gb))
+    late = 0.0
+    for s in (0, 2):                                     # the strong one alone: the ticks behind its last
+        alone, _ = orc.waveforms(w.physics, w.readout, table, w.events[0].subset([s]), o["pixels"])
+        both, _ = orc.waveforms(w.physics, w.readout, table, w.events[0].subset([s, s + 1]), o["pixels"])
+        if kind == "wide":                               # (some of its columns' currents are below any resolution)
+            continue
+        for q in np.flatnonzero(np.abs(both[:, :]).max(1) > 0.1 * np.abs(both).max()):
+            n = np.flatnonzero(alone[q])[-1] + 1
+            sl = np.arange(n, np.flatnonzero(both[q])[-1] + 1)
+            sl = sl[ref[q, sl] == both[q, sl]]           # (no other segment there)
+            if len(sl) >= 20:
+                m = np.linalg.norm(ref[q, sl])
+                d, dv = (np.linalg.norm(g[q, sl] - ref[q, sl]) / m for g in (ga, gb))
+                assert d <= dv + TOL_EDGE, (q, d, dv)
+                late = max(late, d)
+    print(f"faint mode={mode} {kind}: {k.sum()} pixels, max own error {ea.max():.2e} (vector {eb.max():.2e}), behind {late:.2e}")
+    assert np.all(ea <= eb + TOL_EDGE)
+    assert late > 0.0 or kind == "wide"
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("kind", ["whole", "corner", "padded", "units", "wide"])
+def test_faint_currents_of_group_products(lt, orc, torch, mode, kind):
+    check_faint(lt, orc, mode, 4, kind)
+
+
 @pytest.mark.parametrize("cfg,ev", [(1, 0), (1, 1), (3, 0)])
 def test_packets_do_not_depend_on_the_summing_units(lt, torch, cfg, ev):
     """Decisions that rounding could turn are settled in the vector kernels' summation order: the matrix-core forms give
