@@ -2566,8 +2566,8 @@ __global__ __launch_bounds__(kWG) void k_induce_summed(DevParams P, const SegInf
 // Summed induction on the FP16 matrix cores.  Every FP32 factor is a pair of halves, x 2^k = h + l with h = half(x 2^k)
 // and l = half(x 2^k - h): 22 or more significant bits of x, and h h', h l', l h' are exact in the FP32 accumulator (the
 // dropped l l' is below 2^-22 of the product).  2^k puts the largest value of a table column (fixed when the table is
-// installed) below 2^15; for the charge, k is common to the 64 records of a chunk, the largest that keeps every one's
-// product with its column scale in range, so small values lose bits only below 2^-39 of the chunk's largest product.
+// installed) below 2^15, and a record's largest charge (a bound of it; a record's exponent is stored with its bin): a
+// record keeps its bits beside brighter ones, and only ticks below 2^-17 of its own largest keep fewer.
 //
 // One wavefront per work unit (active pixel, kMmaTiles tiles of 256 ticks), taken from a counter.  A record's current on
 // a tile's ticks t0 + 16 j + i is D[i][j] = sum_w A[i][w] B[w][j] with A[i][w] = S[i - w + off] (the charge, a Toeplitz
@@ -2576,14 +2576,14 @@ __global__ __launch_bounds__(kWG) void k_induce_summed(DevParams P, const SegInf
 // 16x16x32 instruction (lane l gives A[l % 16][8 (l / 16) ..] and B[8 (l / 16) ..][l % 16]).  The table words of a
 // record's window are staged in LDS (a tile reads each about 4 times), the charge as eight copies shifted by one value,
 // so that every lane's 8 consecutive (reversed) values are one aligned 16-byte word too; A then serves all tiles.
-// Tiles outside the record's window are skipped.  The products stay in the matrix accumulators over kMmaKahanEvery
-// records and are then added to the lane's sums with Kahan compensation, in list order (deterministic and
-// batch-invariant).
+// Tiles outside the record's window are skipped.  A part's products leave the matrix accumulators in its own scale and are
+// added to the lane's sums with Kahan compensation, in list order (deterministic and batch-invariant).
 //
 // The vector-ALU form of the same sums (256-tick units, 32 multiply-adds per lane against three LDS reads) took 37.5 ms
 // on a module event of 20,000 segments (13.6 million records, 1.37e12 products) and 36.2 ms on a spill tile of 64,000;
-// this one 16.7 and 16.8 ms, at an error against FP64 that is 0.7 to 0.95 of its (1.18e-7 against 1.33e-7 of the norm; a
-// compensated addition after every 4 parts instead of 2 would save 2 % and leave 0.93 to 0.98).
+// this one 17.1 and 17.0 ms, at an error against FP64 that is 0.7 to 0.95 of its (1.20e-7 against 1.30e-7 of the norm, of
+// a pixel at most 8e-7 of itself against 1.1e-6).  One scale for 64 records, added up after every 2 parts, would save 4 %
+// (16.4 ms), a small event's serial chains 7 %, and leave a pixel of little charge beside much with 1.5e-5.
 // It runs at the card's power limit (2.07 GHz against 2.34 GHz), with the matrix cores busy 30 % and LDS about 75 % of
 // the time.  3 tiles per unit run 4 wavefronts per SIMD; 4 tiles (3 wavefronts) took 2 to 3 % longer, 2 tiles 10 % and
 // 1 tile 40 %: the charge is staged for fewer products.
@@ -2598,7 +2598,6 @@ constexpr int32_t kMmaPart = 72;                        // charge ticks taken at
 constexpr int32_t kMmaLow = 24;                         // staged charge position of a part's last tick
 constexpr int32_t kMmaCopy = 144;                       // halves of one shifted copy (288 B: the copies' banks differ by 8)
 constexpr int32_t kMmaOct = kMmaTiles * 32 + 16;        // octets (8 table values, 16 bytes) of the longest window
-constexpr int32_t kMmaKahanEvery = 2;                   // parts summed in the accumulators between compensated additions
 static_assert(kPad >= kMmaSub + kMmaPart + 16 + 96, "summed matrix induction reads");
 
 struct alignas(16) MmaStage {                           // LDS of one wavefront
@@ -2708,9 +2707,6 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
         const int32_t t0 = (int32_t)(unit - ui * n_tiles) * kMmaUnit, t1 = min(t0 + kMmaUnit, NT) - 1;
         const int64_t pb = list_off[slot], pe = list_off[slot + 1];
         float sum[4 * kMmaTiles], cmp[4 * kMmaTiles];
-        floatx4 D[kMmaTiles];
-#pragma unroll
-        for (int T = 0; T < kMmaTiles; ++T) D[T] = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int r = 0; r < 4 * kMmaTiles; ++r) { sum[r] = 0.0f; cmp[r] = 0.0f; }
         for (int64_t c0 = pb; c0 < pe; c0 += 64) {
@@ -2721,28 +2717,10 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
             const int32_t bin = pr.bin & kBinMask;
             const bool meets = in && pr.a0 + pr.na - 1 >= t0 && pr.a0 - TR + 1 <= t1;
             if (!__ballot(meets)) continue;
-            // the chunk's scale 2^N: charge x 2^(N - eb) below 2^15 for every record
+            // the record's scales: charge x 2^(N - eb) below 2^15; its products are 2^N times what they stand for
             const int32_t eb = meets ? Rexp[bin] : 0;
-            int32_t N = meets ? min(141 - (int32_t)((uint32_t)pr.bin >> kBinBits), 126) + eb : INT32_MAX;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) N = min(N, __shfl_xor(N, o));
-            N = min(max(__builtin_amdgcn_readfirstlane(N), -126), 126);
-            const float up = ldexpf(1.0f, N - eb), down = ldexpf(1.0f, -N);
-            int pending = 0;
-            auto flush = [&] {
-#pragma unroll
-                for (int T = 0; T < kMmaTiles; ++T) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float y = fmaf(D[T][r], down, -cmp[4 * T + r]);
-                        const float t = sum[4 * T + r] + y;
-                        cmp[4 * T + r] = (t - sum[4 * T + r]) - y;
-                        sum[4 * T + r] = t;
-                    }
-                    D[T] = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
-                }
-                pending = 0;
-            };
+            const int32_t N = min(max(min(141 - (int32_t)((uint32_t)pr.bin >> kBinBits), 126) + eb, -126), 126);
+            const float up = ldexpf(1.0f, N - eb);
             // records longer than kMmaPart ticks go in several rounds over the chunk
             for (int32_t done = 0;; done += kMmaPart) {
                 const int32_t L = min(pr.na - done, kMmaPart), a0 = pr.a0 + done;
@@ -2758,10 +2736,11 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
                 // a part in hand: its fields and the lane's words of it, loaded one part ahead
                 u32x4 gh[2], gl[2];
                 float x[2] = {0.0f, 0.0f}, xu = 0.0f;
-                int32_t qp = 0;
+                int32_t qp = 0, qn = 0;
                 auto fetch = [&](int i) {
                     qp = __builtin_amdgcn_readlane(pack, i);
                     xu = lane_value(up, i);
+                    qn = __builtin_amdgcn_readlane(N, i);
                     const int32_t o = __builtin_amdgcn_readlane((int)v_at, i), end = __builtin_amdgcn_readlane((int)v_end, i);
                     // loads past the ends return zeros without touching memory
                     const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc((void *)Rh, (short)0, end, kBufferWord3);
@@ -2781,6 +2760,7 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
                 while (mask) {
                     mask &= mask - 1ull;
                     const int32_t p = qp, pk = p >> 9 & 3, pT0 = p >> 11 & 3, pT1 = p >> 13 & 3;
+                    const float down = __builtin_bit_cast(float, (127 - qn) << 23);
                     // the previous part's reads of the slice are done before it is overwritten
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
@@ -2815,12 +2795,22 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
                     // A[i][8g + q] is at position 15 - i + 8g + q + (kMmaLow - (off + 16 - L))
                     const int32_t pos = pos0 - (p >> 15);
                     const u32x4 *sl = (const u32x4 *)&st.s[0][pos & 7][0] + (pos >> 3);
+                    floatx4 D[kMmaTiles];
+#pragma unroll
+                    for (int T = 0; T < kMmaTiles; ++T) D[T] = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
                     mma_dispatch(rl, sl, pk, pT0, pT1, D);
-                    if (++pending == kMmaKahanEvery) flush();
+#pragma unroll
+                    for (int T = 0; T < kMmaTiles; ++T)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float y = fmaf(D[T][r], down, -cmp[4 * T + r]);
+                            const float t = sum[4 * T + r] + y;
+                            cmp[4 * T + r] = (t - sum[4 * T + r]) - y;
+                            sum[4 * T + r] = t;
+                        }
                 }
                 if (!__ballot(meets && pr.na > done + kMmaPart)) break;
             }
-            if (pending) flush();
         }
         float *wrow = wave + slot * NT;
 #pragma unroll

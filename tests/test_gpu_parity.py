@@ -1226,6 +1226,11 @@ def test_faint_currents_of_group_products(lt, orc, torch, mode, kind):
     check_faint(lt, orc, mode, 4, kind)
 
 
+@pytest.mark.parametrize("kind", ["whole", "corner", "padded", "units", "wide"])
+def test_faint_currents_of_summed_records(lt, orc, torch, kind):
+    check_faint(lt, orc, 2, 8, kind)
+
+
 @pytest.mark.parametrize("cfg,ev", [(1, 0), (1, 1), (3, 0)])
 def test_packets_do_not_depend_on_the_summing_units(lt, torch, cfg, ev):
     """Decisions that rounding could turn are settled in the vector kernels' summation order: the matrix-core forms give
