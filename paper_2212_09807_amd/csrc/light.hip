@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <limits>
 #include <memory>
 #include <string>
 #include <vector>
@@ -106,7 +107,8 @@ __global__ __launch_bounds__(kLWG) void k_light_scint(const float *__restrict__ 
 //   sum_k x[t - k] rho^k = P[t] + rho^(t - e) H[t - K + 1],
 // P the recursion P[t] = x[t] + rho P[t - 1] started anew in each block, and H[u] = sum_{s = u}^{e} x[s] rho^(e - s) the sums
 // from the end of the block before.  Nothing is subtracted, so no error survives what caused it: zeros stay zeros, and a
-// value not finite reaches exactly the K ticks it should.  The powers come from a table (exponentials, one rounding each).
+// value not finite reaches exactly the K ticks it should (no power is zero, or infinity times it would be no number; a
+// weight of zero takes its sum out).  The powers come from a table (exponentials, one rounding each).
 //   One workgroup per (block, detector), 8 ticks a thread, both sums by wavefront scans; what bounds it is the latency of
 // its two passes of loads, scans and barriers (64 detectors x 16,384 ticks, K = 8001: 37 instead of 323 us for the direct
 // sum, which runs at the FP64 rate).
@@ -114,6 +116,7 @@ struct LightDecay {
     double a, rho;                  // weight, power per tick
     double step[6];                 // rho^(8 2^k): what a scan step of 2^k lanes spans
     double wave;                    // rho^512
+    __device__ __forceinline__ double of(double sum) const { return a != 0.0 ? sum : 0.0; }
 };
 
 // Sum over the lanes at or above this one; carry: the wavefronts above it in the workgroup and `later`.  Returns the sum over
@@ -194,7 +197,9 @@ __global__ __launch_bounds__(1024) void k_light_decay(const float *__restrict__ 
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
                 const int32_t i = i0 + r;
-                if (i < len) o[i] = i <= K - 2 ? Dp.a * (tp[i + 1] * (hp[r] + cp)) + Ds.a * (ts[i + 1] * (hs[r] + cs)) : 0.0;
+                if (i >= len) continue;
+                const double p = tp[min(i + 1, K - 1)] * (hp[r] + cp), s = ts[min(i + 1, K - 1)] * (hs[r] + cs);
+                o[i] = i <= K - 2 ? Dp.a * Dp.of(p) + Ds.a * Ds.of(s) : 0.0;
             }
         }
     }
@@ -215,7 +220,7 @@ __global__ __launch_bounds__(1024) void k_light_decay(const float *__restrict__ 
         for (int r = 0; r < 8; ++r) {
             cp *= Dp.rho;
             cs *= Ds.rho;
-            const double m = fma(Dp.a, pp[r] + cp, Ds.a * (ps[r] + cs));
+            const double m = fma(Dp.a, Dp.of(pp[r] + cp), Ds.a * Ds.of(ps[r] + cs));
             if (i0 + r < len) o[i0 + r] = b > 0 ? o[i0 + r] + m : m;
         }
     }
@@ -700,7 +705,9 @@ lts_status lts_light_create(int device, const lts_light_params *p, const float *
     std::vector<double> w(rec ? 2 * (size_t)L->K : 8 * (size_t)L->nkb, 0.0);
     for (int32_t j = 0; j < 2; ++j) {
         const double tau = j ? q.tau_s : q.tau_p, f = j ? 1.0 - q.f_prompt : q.f_prompt;
-        auto power = [&](double k) { return std::exp(-(k * q.tick) / tau); };
+        auto power = [&](double k) {                       // (the least normal number adds nothing to a finite sum)
+            return std::max(std::exp(-(k * q.tick) / tau), std::numeric_limits<double>::min());
+        };
         LightDecay &D = L->decay[j];
         D.a = q.tick * (f / tau);
         D.rho = power(1);

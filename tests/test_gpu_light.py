@@ -104,6 +104,32 @@ def test_light_decay_blocks(lt, OL, torch, taps, n_ticks):
     sim.close()
 
 
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("f_prompt", [0.0, 0.3, 1.0])
+@pytest.mark.parametrize("tick", [0, 1, 7999, 8000, 8001, 12345])
+def test_light_value_not_finite_reaches_its_taps(lt, torch, value, f_prompt, tick):
+    """A photocurrent that is no finite number, at the edges of the blocks and inside one: the means of exactly the ticks
+    within its taps are not finite, infinite with its sign wherever the tap's weight is above zero; the others are those
+    without it."""
+    lp = dataclasses.replace(W.Light(), n_det=1, n_ticks=24500, group=1, max_trig=0, f_prompt=f_prompt)
+    taps = 8001
+    ipe = np.random.default_rng(tick).uniform(0.0, 0.05, (1, lp.n_ticks)).astype(np.float32)
+    sim = lt.LightSim(lp, W.light_response(n_resp=9), np.zeros(0, np.float32))
+    run = lambda x: sim.simulate(torch.from_numpy(x).cuda(), 1, keep_mu=True)["mu"].cpu().numpy()[0]
+    with_it = ipe.copy()
+    with_it[0, tick] = value
+    without, mu = run(ipe), run(with_it)
+    sim.close()
+    t = np.arange(lp.n_ticks)
+    hit = (t >= tick) & (t < tick + taps)
+    assert np.all(np.isfinite(without)) and np.array_equal(~np.isfinite(mu), hit)
+    assert np.array_equal(mu[~hit], without[~hit])
+    k = t[hit] - tick
+    w = f_prompt / lp.tau_p * np.exp(-k / lp.tau_p) + (1.0 - f_prompt) / lp.tau_s * np.exp(-k / lp.tau_s)
+    if not np.isnan(value):
+        assert np.all(mu[hit][w > 0] == value)
+
+
 @pytest.mark.parametrize("n_ticks,n_freq", [(8, 3), (16, 7), (32, 3), (64, 31), (128, 40), (256, 127), (2048, 1023), (16384, 8191)])
 def test_light_noise_transform_lengths(lt, OL, torch, n_ticks, n_freq):
     """The noise transform with every number of last stages, spectra that fill the band, and the shortest window."""
