@@ -3615,9 +3615,9 @@ __device__ __forceinline__ float row_tree(float x) {
     return x;
 }
 
-// With `list` the pixels are the header's n_settle entries of it (a second pass over settled currents; the report's sum of
-// currents is the first pass's).  With `settle` a pixel one of whose decisions - a crossing, a code, or the margin that
-// flags them - lies within twice the margin is appended to it, and its dropped and surplus samples are left to that pass.
+// With `list` the pixels are the header's n_settle entries of it (a second pass over settled currents).  With `settle` a
+// pixel one of whose decisions - a crossing, a code, or the margin that flags them - lies within twice the margin is
+// appended to it, and its dropped and surplus samples and its current's sum are left to that pass.
 template <bool SETTLE>
 __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *__restrict__ wave,
                                                      const int32_t *__restrict__ slot_gp,
@@ -3807,7 +3807,7 @@ __global__ __launch_bounds__(kWG) void k_electronics(DevParams P, const float *_
             if (!done && s < jn) carry(lane_value(sx, jn - 1), lane_value(sa, jn - 1));
         }
         if (lane == 0) pk_cnt[slot] = off ? 0 : cnt;
-        if (!list) add_report(report, e, 2, rs, true);
+        if (!(SETTLE && close)) add_report(report, e, 2, rs, true);
         if (SETTLE && close) {
             if (lane == 0) settle[atomicAdd(&H->n_settle, 1u)] = (int32_t)slot;
             continue;

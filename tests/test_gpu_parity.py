@@ -1220,6 +1220,18 @@ def check_faint(lt, orc, mode, rt, kind):
     assert late > 0.0 or kind == "wide"
 
 
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_report_adds_up_the_currents_returned(lt, torch, mode):
+    """The report's induced charge is the FP64 sum of the currents that the call returns, also where pixels were settled
+    (codes one electron wide: many a charge lies near an edge)."""
+    w = W.make_workload(1)
+    w.electronics = dataclasses.replace(w.electronics, q_lsb=1.0, adc_bits=16)
+    _, h = run_gpu(lt, w, mode=mode)
+    assert np.count_nonzero(h["pkt_flags"]) > 5
+    cur = h["current"].astype(np.float64)
+    assert abs(h["report"][0][2] - cur.sum()) <= 1e-13 * np.abs(cur).sum()      # (a quarter million FP64 additions)
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("kind", ["whole", "corner", "padded", "units", "wide"])
 def test_faint_currents_of_group_products(lt, orc, torch, mode, kind):
