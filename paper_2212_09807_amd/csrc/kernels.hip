@@ -3835,17 +3835,19 @@ void launch_electronics(const DevParams &P, const float *wave, const int32_t *sl
 
 // ================================================================================================= settled pixels
 // A packet's tick and code are decided by comparing a charge with a threshold or an LSB edge, and a charge that lies on
-// the edge to within rounding is decided by the order of the FP32 sum.  The vector kernels' order is the one packets are
-// stated in, so that they do not depend on which units summed the currents: a pixel with such a decision (about one in a
-// hundred) gets its currents again in that order, bit for bit, and passes the front end once more.
+// the edge to within rounding is decided by the order of the FP32 sum.  So that packets do not depend on which units
+// summed the currents, they are stated in one order: a pixel with such a decision (about one in a hundred) gets its
+// currents again in that order and passes the front end once more.
 //   Order: a pair's (a record's) products column by column, cell tick by cell tick, as one FP32 chain per output tick;
 // chains of a pair (of kSumKahanEvery records that meet a 256-tick tile) added with Kahan compensation in list order.
+// Per pair that is the vector kernels' order, bit for bit, also for the atomic mode, which has none of its own; for the
+// summed mode it is this kernel's (the 512-tick vector kernel cuts intervals and tiles otherwise and agrees to rounding).
 //   A round is 16 chains of a (pixel, 256 ticks), one per wavefront (lane t: ticks 4 t .. + 3).  The few pixels of a call
 // are spread over the chip round by round: a workgroup computes a round's chains, waits until the round before has been
 // added, adds its own to the pixel's sum and compensation in memory and passes on.  Rounds are handed out in order, so a
 // round waits only on one that is already running.  Beyond the first kSettleSpread pixels there are enough to take a
 // pixel's rounds one after the other in one workgroup.  (One workgroup per pixel and 256 ticks throughout: 4.1 instead
-// of 0.65 ms for 4 pixels of 3000 dense segments, as 48 workgroups leave the chip idle; 1.1 instead of 0.74 ms for 14
+// of 0.66 ms for 4 pixels of 3000 dense segments, as 48 workgroups leave the chip idle; 1.1 instead of 0.86 ms for 14
 // pixels of a summed event of 20,000 segments, 3000 ticks.)
 constexpr int32_t kSettleWG = 1024, kSettleWaves = kSettleWG / 64, kSettleTile = 256;
 
@@ -4031,9 +4033,11 @@ __global__ __launch_bounds__(kSettleWG) void k_settle(DevParams P, Work w, SumWo
             const bool last = r + 1 == __builtin_amdgcn_readlane(mine, i) / n_tiles;
             const int32_t n_chain = settle_chains<SUMMED>(P, w, sw, Rpad, L, slot, r, t0, min(t0 + kSettleTile, NT) - 1);
             uint32_t *tk = &token[i * n_tiles + tile];
-            if (tid == 0)
+            if (tid == 0) {
                 while (__hip_atomic_load(tk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)r)
                     __builtin_amdgcn_s_sleep(1);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            }
             __syncthreads();                            // the chains are in place, too
             if (tid < kSettleTile && t0 + tid < NT) {
                 float *ps = &wave[slot * NT + t0 + tid], *pc = &comp[(int64_t)i * NT + t0 + tid];
@@ -4046,11 +4050,11 @@ __global__ __launch_bounds__(kSettleWG) void k_settle(DevParams P, Work w, SumWo
                 __hip_atomic_store(ps, last ? sum - cmp : sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(pc, cmp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            // sum and compensation are read and written past the caches, so their stores need only be complete before the
-            // token's (a release fence would write back the whole L2 in every round)
+            // the workgroup's stores are complete, then the token is released for all of them.  (A release by every writing
+            // wavefront writes the L2 back as often: 2.06 instead of 0.86 ms on a summed event of 20,000 segments.)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            if (tid == 0) __hip_atomic_store(tk, (uint32_t)r + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) __hip_atomic_store(tk, (uint32_t)r + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             const int64_t k = (int64_t)unit - n_spread_units;
             const int64_t slot = __builtin_amdgcn_readfirstlane(list[n_spread + k / n_tiles]);

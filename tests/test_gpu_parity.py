@@ -1258,3 +1258,44 @@ def test_packets_do_not_depend_on_the_summing_units(lt, torch, cfg, ev):
     _, c = run_gpu(lt, w, ev, 1, rt=0)
     assert len(c["pkt_adc"]) == len(a["pkt_adc"])
     print(f"config {cfg} event {ev}: {len(a['pkt_adc'])} packets, {len(flagged)} flagged pixels")
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_settled_pixels_are_the_same_first_and_late_in_the_list(lt, torch, mode):
+    """Settled currents are the same bits whether a pixel's rounds are spread over the chip and handed on from workgroup to
+    workgroup (the first 64 of a call) or taken one after the other (those beyond): an event alone against six copies of it
+    in one call, with codes one electron wide, so that many pixels are settled."""
+    w = W.make_workload(1)
+    wide = dataclasses.replace(w.electronics, q_lsb=1e9)            # (no code's edge is near)
+    w.electronics = dataclasses.replace(w.electronics, q_lsb=1.0, adc_bits=16)
+    n = 6
+    d, many = lt.to_device(w.events[0]), lt.to_device(W.Segments.concat([w.events[0]] * n))
+    ctx = lt.Context.from_workload(w, reduce_mode=mode)
+    ctx.set_ticks_per_thread(0)
+    one = ctx.simulate(d, event_id=5).host()
+    off = np.arange(n + 1) * w.events[0].n
+    b = ctx.simulate_batch(many, off, [5] * n).host()
+    w.electronics = wide
+    rough = lt.Context.from_workload(w, reduce_mode=mode).simulate(d, event_id=5).host()
+    settled = np.flatnonzero(np.any(one["current"] != rough["current"], axis=1))
+    po, ko = b["event_pixel_offsets"], b["event_packet_offsets"]
+    for e in range(n):
+        rows = b["current"][po[e]:po[e + 1]]
+        if mode != 1:
+            assert np.array_equal(rows, one["current"])
+        for k in ("pkt_pixel", "pkt_tick", "pkt_adc", "pkt_flags"):
+            assert np.array_equal(b[k][ko[e]:ko[e + 1]], one[k])
+    if mode != 1:                                                   # (atomic sums differ from call to call)
+        print(f"mode {mode}: {len(settled)} settled rows of {len(one['current'])}")
+        assert 12 <= len(settled) and n * len(settled) > 64
+
+
+@pytest.mark.parametrize("cfg,ev", [(1, 0), (1, 1), (3, 0)])
+def test_atomic_packets_are_the_sorted_modes(lt, torch, cfg, ev):
+    """Decisions near an edge are settled in the sorted order in the atomic mode, too: its packets are the sorted mode's,
+    codes and ticks, whatever order the atomics took."""
+    w = W.make_workload(cfg, n_events=2)
+    _, a = run_gpu(lt, w, ev, 0)
+    _, b = run_gpu(lt, w, ev, 1)
+    for k in ("pkt_pixel", "pkt_tick", "pkt_adc", "pkt_flags"):
+        assert np.array_equal(a[k], b[k]), k
