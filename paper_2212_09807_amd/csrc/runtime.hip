@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
@@ -32,6 +33,25 @@ namespace {
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
+};
+
+// A response table on the device.  A context and the server lanes made from it hold the same one; it goes with the last of
+// them (its launches included: the free waits for the device).
+struct DevTable {
+    DevBuf Rpad, prefix;             // columns with their zero padding, and their FP64 prefix sums
+    DevBuf Rhalf, Rexp;              // the columns' half pairs (high plane, then low) and their scales
+    DevBuf Roct, Rclass;             // the half pairs by octets of bins, the clip classes
+    int device = 0;
+    int32_t t_r = 0, b_x = 0, b_y = 0, col_len = 0;
+    std::array<DevBuf *, 6> buffers() { return {&Rpad, &prefix, &Rhalf, &Rexp, &Roct, &Rclass}; }
+    DevTable() = default;
+    DevTable(const DevTable &) = delete;
+    DevTable &operator=(const DevTable &) = delete;
+    ~DevTable() {
+        (void)hipSetDevice(device);
+        for (DevBuf *b : buffers())
+            if (b->p) (void)hipFree(b->p);
+    }
 };
 
 }  // namespace
@@ -64,12 +84,7 @@ struct lts_context {
     DevBuf mlist_off, m_off, mrec, Sm;          // the mirror-merged records of the summed induction
     DevBuf segc;                                // compact segment fields for the column passes
     DevParams P{};
-    bool has_table = false;
-    DevBuf Rpad, prefix;
-    DevBuf Rhalf, Rexp;              // the table's half pairs (high plane, then low) and their column scales
-    DevBuf Roct, Rclass;             // the half pairs by octets of bins, the clip classes
-    std::vector<float> table_host;   // kept to build server lanes
-    int32_t t_r = 0, b_x = 0, b_y = 0;
+    std::shared_ptr<DevTable> table;
     // scratch pool
     DevBuf si, cell_off, pix_cnt, cursor, pix_slot, slot_gp, slot_off, pairs_u, pairs, cells, pk_tick, pk_adc,
         pk_flag, pk_off, hdr, scan_tmp, ev_off, ev_ids, report_tmp, counts_tmp, red_head, red_start, order;
@@ -246,20 +261,18 @@ constexpr lts_status kNotAdmitted = LTS_ERR_NOT_READY;
 std::vector<DevBuf *> pool_buffers(lts_context *c) {
     return {&c->ev_cnt, &c->mask, &c->col_seg_off, &c->col_cursor, &c->col_seg, &c->col_tmp, &c->piece_off,
             &c->s_off, &c->piece, &c->pdesc, &c->S, &c->list_off, &c->list, &c->rec, &c->mlist_off, &c->m_off,
-            &c->mrec, &c->Sm, &c->segc, &c->part, &c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Roct, &c->Rclass,
-            &c->si, &c->cell_off, &c->pix_cnt, &c->cursor, &c->pix_slot, &c->slot_gp, &c->slot_off, &c->pairs_u,
+            &c->mrec, &c->Sm, &c->segc, &c->part, &c->si, &c->cell_off, &c->pix_cnt, &c->cursor, &c->pix_slot, &c->slot_gp, &c->slot_off, &c->pairs_u,
             &c->pairs, &c->cells, &c->pk_tick, &c->pk_adc,
             &c->pk_flag, &c->pk_off, &c->hdr, &c->scan_tmp, &c->ev_off, &c->ev_ids, &c->report_tmp, &c->counts_tmp,
             &c->red_head, &c->red_start, &c->order};
 }
 
-// Frees the context's per-call scratch (everything in the pool but the response table and the channel mask, which
-// persist across calls); every buffer is grown again to the exact size the next call needs.  The caller makes sure
+// Frees the context's per-call scratch (everything in the pool but the channel mask, which persists across calls); every
+// buffer is grown again to the exact size the next call needs.  The caller makes sure
 // no queued work still uses them.
 void release_scratch(lts_context *c) {
-    const DevBuf *kept[] = {&c->Rpad, &c->prefix, &c->Rhalf, &c->Rexp, &c->Roct, &c->Rclass, &c->mask};
     for (DevBuf *b : pool_buffers(c))
-        if (std::find(std::begin(kept), std::end(kept), b) == std::end(kept)) free_buf(*b);
+        if (b != &c->mask) free_buf(*b);
 }
 
 // One buffer and the bytes a call needs in it.
@@ -389,15 +402,57 @@ SegArrays seg_arrays(const lts_segments *s) {
 // one's end.
 size_t half_plane(int32_t b_x, int32_t b_y, int32_t col_len) { return (size_t)b_x * b_y * col_len + 2048; }
 
-Table table_of(lts_context *c) {
-    const size_t plane = half_plane(c->b_x, c->b_y, c->P.col_len);
-    Table T{as<float>(c->Rpad), as<double>(c->prefix), c->Rhalf.p, as<uint16_t>(c->Rhalf) + plane, as<int32_t>(c->Rexp)};
-    T.njo = (c->b_y + 7) / 8;
-    T.trq = (c->t_r + 15) / 16 * 16;
-    T.zhi = c->Roct.p;
-    T.zlo = as<uint16_t>(c->Roct) + (size_t)c->b_x * T.njo * T.trq * 8;
-    T.cls = as<double>(c->Rclass);
+Table table_of(const lts_context *c) {
+    DevTable &t = *c->table;
+    const size_t plane = half_plane(t.b_x, t.b_y, t.col_len);
+    Table T{as<float>(t.Rpad), as<double>(t.prefix), t.Rhalf.p, as<uint16_t>(t.Rhalf) + plane, as<int32_t>(t.Rexp)};
+    T.njo = (t.b_y + 7) / 8;
+    T.trq = (t.t_r + 15) / 16 * 16;
+    T.zhi = t.Roct.p;
+    T.zlo = as<uint16_t>(t.Roct) + (size_t)t.b_x * T.njo * T.trq * 8;
+    T.cls = as<double>(t.Rclass);
     return T;
+}
+
+// Makes the table the context's own; the one it had goes if no other context holds it.
+void take_table(lts_context *c, std::shared_ptr<DevTable> t) {
+    c->P.t_r = t->t_r;
+    c->P.bx = t->b_x;
+    c->P.by = t->b_y;
+    c->P.col_len = t->col_len;
+    c->table = std::move(t);
+}
+
+// Uploads a table's columns and prefix sums and makes its other forms from them.
+lts_status build_table(lts_context *c, DevTable &t, const std::vector<float> &pad, const std::vector<double> &pre) {
+    lts_status r;
+    const size_t ncol = (size_t)t.b_x * t.b_y, plane = half_plane(t.b_x, t.b_y, t.col_len);
+    const int32_t njo = (t.b_y + 7) / 8, trq = (t.t_r + 15) / 16 * 16;
+    const size_t oct = (size_t)t.b_x * njo * trq * 8;    // halves of one plane
+    // clip classes up to 64 MB; finer sub-pixel grids walk the pixels of every column
+    const size_t cls = (size_t)c->P.nsub * c->P.nsub * (size_t)(t.t_r + 1) * sizeof(double);
+    const bool classes = cls <= (size_t)64 << 20;
+    if ((r = ensure(c, t.Rpad, sizeof(float) * pad.size())) || (r = ensure(c, t.prefix, sizeof(double) * pre.size())) ||
+        (r = ensure(c, t.Rhalf, 2 * sizeof(uint16_t) * plane)) || (r = ensure(c, t.Rexp, sizeof(int32_t) * ncol)) ||
+        (r = ensure(c, t.Roct, 2 * sizeof(uint16_t) * oct)) || (classes && (r = ensure(c, t.Rclass, cls))))
+        return r;
+    HIP_TRY(c, hipMemcpy(t.Rpad.p, pad.data(), sizeof(float) * pad.size(), hipMemcpyHostToDevice));
+    HIP_TRY(c, hipMemcpy(t.prefix.p, pre.data(), sizeof(double) * pre.size(), hipMemcpyHostToDevice));
+    launch_table_halves(as<float>(t.Rpad), (int32_t)ncol, t.col_len, t.Rhalf.p, as<uint16_t>(t.Rhalf) + plane,
+                        as<int32_t>(t.Rexp), nullptr);
+    launch_table_octets(as<float>(t.Rpad), t.b_x, t.b_y, t.t_r, t.col_len, trq, as<int32_t>(t.Rexp), t.Roct.p,
+                        as<uint16_t>(t.Roct) + oct, nullptr);
+    if (classes) {
+        DevParams P = c->P;                             // (the context's own are set when nothing can fail any more)
+        P.t_r = t.t_r;
+        P.bx = t.b_x;
+        P.by = t.b_y;
+        launch_clip_classes(P, as<double>(t.prefix), as<double>(t.Rclass), nullptr);
+    }
+    HIP_TRY(c, allow_z_lds());
+    HIP_TRY(c, hipGetLastError());
+    HIP_TRY(c, hipStreamSynchronize(nullptr));
+    return LTS_OK;
 }
 
 // Sizing half of the pipeline: quench / drift / rasterisation counts and scans; synchronises the stream and
@@ -682,7 +737,7 @@ lts_status run_pipeline(lts_context *c, int32_t n_ev, const uint64_t *event_ids,
                         const lts_segments *segs, const lts_outputs *out, hipStream_t st) {
     if (c->sticky) return fail(c, c->sticky, "context is in a failed state: " + c->err);
     TunedKnobs tuned(c, segs ? segs->n : 0, n_ev);
-    if (!c->has_table) return fail(c, LTS_ERR_STATE, "no response table: call lts_set_response first");
+    if (!c->table) return fail(c, LTS_ERR_STATE, "no response table: call lts_set_response first");
     lts_status r;
     if ((r = check_segments(c, segs))) return r;
     if (!out || !out->counts || !out->report || !out->pixel_id || !out->current)
@@ -1080,46 +1135,25 @@ lts_status lts_set_response(lts_context *c, const float *R, int32_t t_r, int32_t
             }
         }
     HIP_TRY(c, hipSetDevice(c->device));
-    lts_status r;
-    c->has_table = false;                               // until every part of the new one is in place
-    if ((r = ensure(c, c->Rpad, sizeof(float) * pad.size()))) return r;
-    if ((r = ensure(c, c->prefix, sizeof(double) * pre.size()))) return r;
-    HIP_TRY(c, hipMemcpy(c->Rpad.p, pad.data(), sizeof(float) * pad.size(), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(c->prefix.p, pre.data(), sizeof(double) * pre.size(), hipMemcpyHostToDevice));
-    const size_t plane = half_plane(b_x, b_y, col_len);
-    if ((r = ensure(c, c->Rhalf, 2 * sizeof(uint16_t) * plane))) return r;
-    if ((r = ensure(c, c->Rexp, sizeof(int32_t) * ncol))) return r;
-    launch_table_halves(as<float>(c->Rpad), (int32_t)ncol, col_len, c->Rhalf.p, as<uint16_t>(c->Rhalf) + plane,
-                        as<int32_t>(c->Rexp), nullptr);
-    const int32_t njo = (b_y + 7) / 8, trq = (t_r + 15) / 16 * 16;
-    const size_t oct = (size_t)b_x * njo * trq * 8;      // halves of one plane
-    if ((r = ensure(c, c->Roct, 2 * sizeof(uint16_t) * oct))) return r;
-    launch_table_octets(as<float>(c->Rpad), b_x, b_y, t_r, col_len, trq, as<int32_t>(c->Rexp), c->Roct.p,
-                        as<uint16_t>(c->Roct) + oct, nullptr);
-    DevParams tab = c->P;                               // (the context's own are set when nothing can fail any more)
-    tab.t_r = t_r;
-    tab.bx = b_x;
-    tab.by = b_y;
-    // clip classes up to 64 MB; finer sub-pixel grids walk the pixels of every column
-    const size_t cls = (size_t)tab.nsub * tab.nsub * (size_t)(t_r + 1) * sizeof(double);
-    if (cls <= (size_t)64 << 20) {
-        if ((r = ensure(c, c->Rclass, cls))) return r;
-        launch_clip_classes(tab, as<double>(c->prefix), as<double>(c->Rclass), nullptr);
-    } else {
-        free_buf(c->Rclass);
+    auto make = [&] {
+        auto t = std::make_shared<DevTable>();
+        t->device = c->device;
+        t->t_r = t_r;
+        t->b_x = b_x;
+        t->b_y = b_y;
+        t->col_len = col_len;
+        return t;
+    };
+    std::shared_ptr<DevTable> t = make();
+    lts_status r = build_table(c, *t, pad, pre);
+    if (r == LTS_ERR_OOM && c->table) {                 // no room beside the old one: without it, then
+        t.reset();
+        c->table.reset();
+        t = make();
+        r = build_table(c, *t, pad, pre);
     }
-    HIP_TRY(c, allow_z_lds());
-    HIP_TRY(c, hipGetLastError());
-    HIP_TRY(c, hipStreamSynchronize(nullptr));
-    c->table_host.assign(R, R + (size_t)t_r * b_x * b_y);
-    c->t_r = t_r;
-    c->b_x = b_x;
-    c->b_y = b_y;
-    c->P.t_r = t_r;
-    c->P.bx = b_x;
-    c->P.by = b_y;
-    c->P.col_len = col_len;
-    c->has_table = true;
+    if (r) return r;
+    take_table(c, std::move(t));
     return LTS_OK;
     LTS_API_END(c)
 }
@@ -1128,7 +1162,7 @@ lts_status lts_plan(lts_context *c, const lts_segments *segs, int64_t need[4], v
     LTS_API_BEGIN
     if (!c || !need) return LTS_ERR_INVALID_ARG;
     if (c->sticky) return fail(c, c->sticky, "context is in a failed state: " + c->err);
-    if (!c->has_table) return fail(c, LTS_ERR_STATE, "no response table: call lts_set_response first");
+    if (!c->table) return fail(c, LTS_ERR_STATE, "no response table: call lts_set_response first");
     lts_status r;
     if ((r = check_segments(c, segs))) return r;
     HIP_TRY(c, hipSetDevice(c->device));
@@ -1302,7 +1336,7 @@ lts_status lts_stage_electronics_noalloc(lts_context *c, uint64_t event_id, cons
 static lts_status stage_front(lts_context *c, uint64_t event_id, const lts_segments *segs, bool with_cells,
                               hipStream_t st, Work &w, DevHeader &h) {
     if (c->sticky) return fail(c, c->sticky, "context is in a failed state: " + c->err);
-    if (!c->has_table) return fail(c, LTS_ERR_STATE, "no response table: call lts_set_response first");
+    if (!c->table) return fail(c, LTS_ERR_STATE, "no response table: call lts_set_response first");
     lts_status r;
     if ((r = check_segments(c, segs))) return r;
     HIP_TRY(c, hipSetDevice(c->device));
@@ -1833,7 +1867,7 @@ lts_status lts_server_start(lts_context *ctx, const lts_server_cfg *cfg, lts_ser
     LTS_API_BEGIN
     if (!ctx || !out) return LTS_ERR_INVALID_ARG;
     *out = nullptr;
-    if (!ctx->has_table) return fail(ctx, LTS_ERR_STATE, "no response table: call lts_set_response first");
+    if (!ctx->table) return fail(ctx, LTS_ERR_STATE, "no response table: call lts_set_response first");
     size_t free_b = 0, total_b = 0;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     HIP_TRY(ctx, hipMemGetInfo(&free_b, &total_b));
@@ -1860,7 +1894,7 @@ lts_status lts_server_start(lts_context *ctx, const lts_server_cfg *cfg, lts_ser
             Lane *L = S->lanes.back().get();
             L->srv = S;
             lts_status r = lts_context_create(ctx->device, &ctx->ph, &ctx->ro, &ctx->el, &L->ctx);
-            if (r == LTS_OK) r = lts_set_response(L->ctx, ctx->table_host.data(), ctx->t_r, ctx->b_x, ctx->b_y);
+            if (r == LTS_OK) take_table(L->ctx, ctx->table);
             if (r == LTS_OK) r = lts_set_reduce_mode(L->ctx, ctx->reduce_mode);
             if (r == LTS_OK) r = lts_set_induce_slices(L->ctx, ctx->induce_slices);
             if (r == LTS_OK) r = lts_set_ticks_per_thread(L->ctx, ctx->ticks_per_thread);

@@ -873,6 +873,35 @@ def test_server_admission_by_device_memory(lt, torch):
             assert np.array_equal(a[k], g[k]), k
 
 
+def test_server_lanes_share_the_response_table(lt, torch):
+    """Eight lanes take less device memory than one copy of the table's columns (45 x 45 x 1950: 28.6 MB of FP32 with their
+    padding, 31.6 MB of prefix sums); they keep the table they were made with when the context takes another, or goes."""
+    w = W.make_workload(3, n_events=1)
+    w.events = [w.events[0].subset(np.arange(300))]
+    table = W.response_table(w.table, w.readout, w.physics.v_drift)
+    ctx = lt.Context.from_workload(w, table=table)
+    d = lt.to_device(w.events[0])
+    alone = ctx.simulate(d, event_id=3).host()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    srv = lt.Server(ctx, n_lanes=8, max_batch_events=1, return_currents=True)
+    try:
+        used = before - torch.cuda.mem_get_info()[0]
+        print(f"eight lanes: {used / 1e6:.1f} MB")
+        assert used < 28e6
+        import ctypes as C
+        other = np.ascontiguousarray(2 * table)
+        ctx._check(lt.lib().lts_set_response(ctx._h, other.ctypes.data_as(C.c_void_p), *table.shape))
+        twice = ctx.simulate(d, event_id=3).host()
+        assert not np.array_equal(twice["current"], alone["current"])
+        for _ in range(8):
+            g = srv.wait(srv.submit(w.events[0], 3), 60.0)
+            for k in ("pixel_id", "current", "pkt_tick", "pkt_adc"):
+                assert np.array_equal(alone[k], g[k]), k
+    finally:
+        srv.stop()
+
+
 # ----------------------------------------------------------------------------------------------- autotuner
 
 def test_autotune_table_is_accurate_and_applied(lt, torch, tmp_path):
