@@ -2396,30 +2396,6 @@ __device__ __forceinline__ const float *cell_ptr(const float *S, const float *Sm
     return cell8 < nS8 ? S + (int64_t)cell8 * kAC : Sm + (int64_t)(cell8 - nS8) * kAC;
 }
 
-// Charge that a pixel's records induce outside the readout, by one wavefront, added to the event's report.
-__device__ __forceinline__ void clipped_records(const DevParams &P, const float *S, const float *Sm, uint32_t nS8,
-                                                const double *prefix, const PieceRef *rec, int64_t pb, int64_t pe,
-                                                int32_t e, double *report) {
-    const int32_t NT = P.nticks, TR = P.t_r, lane = lane_id();
-    double clip = 0.0;
-    for (int64_t k = pb + lane; k < pe; k += 64) {
-        const PieceRef g = rec[k];
-        const int32_t wlo = g.a0 - (TR - 1), whi = g.a0 + g.na - 1;
-        if (wlo >= 0 && whi < NT) continue;
-        const double *pf = prefix + (int64_t)(g.bin & kBinMask) * (TR + 1);
-        const float *cv = cell_ptr(S, Sm, nS8, g.cell8);
-        for (int32_t a = 0; a < g.na; ++a) {
-            const int32_t aa = g.a0 + a;
-            const int32_t klo = min(max(TR - 1 - aa, 0), TR), khi = min(max(NT + TR - 1 - aa, 0), TR);
-            const double dropped = klo >= khi ? pf[TR] : pf[klo] + (pf[TR] - pf[khi]);
-            clip += (double)cv[a] * dropped;
-        }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) clip += __shfl_xor(clip, o);
-    if (lane == 0 && clip != 0.0) atomicAdd(&report[(int64_t)e * 5 + 3], clip);
-}
-
 constexpr int32_t kSumKahanEvery = 4;   // pieces summed in FP32 registers between compensated additions
 
 template <bool SHIFT>
@@ -3466,10 +3442,11 @@ hipError_t allow_z_lds() {
     return e;
 }
 
-// Up to 8 pixels a CU the pixels with the most groups keep the kernel running, and a workgroup of 512 threads takes them
-// faster than two of 256 take two (200 segments, 276 pixels 74 -> 62 us; 1000, 1415 pixels 3.05 -> 2.15 ms; 2500, 2437
-// pixels 10.3 -> 8.2 ms); with more the two overlap staging and products (3500, 3328 pixels 11.6 ms against 12.5; 64
-// tracks, 12,400 pixels 1.18 against 1.68).
+// Up to 8 pixels a CU those with the most groups keep the kernel running, and a workgroup of 512 threads takes them faster
+// than two of 256 take two; with many more the two overlap staging and products.  Measured with 256 and 512 threads: 276
+// pixels of a track 74 and 62 us, 663 of 1200 segments 4.2 and 3.2 ms, 2000 pixels 5.4 and 5.4; from 2100 to 2800 it is
+// the event that decides, an even one 5.9 to 6.2 and 6.3 to 6.7, one with a crowded place 12.5 to 15.9 and 9.3 to 12.5; 3200
+// pixels 8.0 and 8.6, 64 tracks' 12,400 1.18 and 1.68.
 constexpr int64_t kZgWide = 2048;
 void launch_induce_z(const DevParams &P, const Work &w, const Table &T, float *wave, int mode, int64_t n_slots,
                      hipStream_t st) {
