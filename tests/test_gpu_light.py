@@ -139,6 +139,23 @@ def test_light_noise_transform_lengths(lt, OL, torch, n_ticks, n_freq):
     check(lt, OL, torch, lp, np.zeros((3, n_ticks), np.float32), W.light_response(n_resp=5), amp, 11)
 
 
+@pytest.mark.parametrize("n_ticks,bound", [(64, 7.0e-8), (1024, 1.05e-7), (16384, 1.26e-7)])
+def test_light_noise_error_against_64_bits(lt, torch, n_ticks, bound):
+    """The noise transform's rounding: no more than FP32 stages over the full complex length had (7.27e-8, 1.07e-7 and
+    1.273e-7 of the noise; the form with its first stages in FP64, emulated in numpy: 6.30e-8, 9.66e-8, 1.240e-7), on the
+    spectrum of the noise model; many detectors, so that the norm is the mean error."""
+    import oracle.light as light
+    lp = dataclasses.replace(W.Light(), n_det=48, n_ticks=n_ticks, group=1, max_trig=0, trunc=0.01)
+    amp = W.light_noise_amplitudes(min(2048, n_ticks // 8))
+    sim = lt.LightSim(lp, W.light_response(n_resp=5), amp)
+    V = sim.simulate(torch.zeros((lp.n_det, n_ticks), device="cuda"), 5)["V"].cpu().numpy().astype(np.float64)
+    sim.close()
+    ref = light.simulate(lp, 5, np.zeros((lp.n_det, n_ticks), np.float32), W.light_response(n_resp=5), amp)["V"]
+    e = np.linalg.norm(V - ref) / np.linalg.norm(ref)
+    print(f"noise of {n_ticks} ticks: error {e:.3e}")
+    assert e <= bound
+
+
 def test_light_invalid_parameters(lt, torch):
     lp = W.Light()
     r, a = W.light_response(), W.light_noise_amplitudes()
