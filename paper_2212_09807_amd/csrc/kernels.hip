@@ -3128,6 +3128,8 @@ __device__ __forceinline__ void z_group(const DevParams &P, const ZTable &Z, ZSt
                                 floatx4 d;
 #pragma unroll
                                 for (int r = 0; r < 4; ++r) d[r] = ldexpf(D[b][y][r], dn[b][r]);
+                                // (charge that is not finite is no number against the padding past the table's end)
+                                if (t + y == n_tau - 1 && 16 * (t + y) + lj >= TR) d = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
                                 const float lo = d[0] + row_up<1>(d[1]) + (row_up<2>(d[2]) + row_up<3>(d[3]));
                                 const float hi = row_down<15>(d[1]) + (row_down<14>(d[2]) + row_down<13>(d[3]));
                                 // row g moves up by 4 g more

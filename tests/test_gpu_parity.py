@@ -1249,6 +1249,25 @@ def check_faint(lt, orc, mode, rt, kind):
     assert late > 0.0 or kind == "wide"
 
 
+@pytest.mark.parametrize("mode,rt", [(0, 4), (1, 4), (2, 8)])
+def test_infinite_charge_stays_in_its_window(lt, torch, mode, rt):
+    """A deposit whose charge overflows FP32 leaves no finite current in its own window and changes none outside it: the
+    matrix-core currents are finite wherever the vector kernels' are, and the same to rounding there.  (A table of 200
+    ticks: its last tile of 16 has padding.)"""
+    w = W.make_workload(1)
+    p = np.array([[12.0, 13.0, 6.0]])
+    segs = w.events[0].subset(np.arange(0, 200, 3))
+    w.events = [W.Segments.concat([segs, W.make_segments(p, p + 0.01, 1e36), W.make_segments(p + 0.05, p + 0.06, 0.02)])]
+    w.electronics = dataclasses.replace(w.electronics, q_lsb=1e9)
+    (_, a), (_, b) = run_gpu(lt, w, mode=mode), run_gpu(lt, w, mode=mode, rt=rt)
+    assert np.array_equal(a["pixel_id"], b["pixel_id"])
+    fa, fb = np.isfinite(a["current"]), np.isfinite(b["current"])
+    print(f"mode {mode}: {(~fa).sum()} values not finite (vector {(~fb).sum()})")
+    assert 0 < (~fa).sum() and np.all(fa[fb])
+    x, y = np.where(fb, a["current"], 0.0).astype(np.float64), np.where(fb, b["current"], 0.0).astype(np.float64)
+    assert per_pixel_errors(x, y).max() <= TOL_EDGE
+
+
 @pytest.mark.parametrize("mode", [0, 1, 2])
 def test_report_adds_up_the_currents_returned(lt, torch, mode):
     """The report's induced charge is the FP64 sum of the currents that the call returns, also where pixels were settled
