@@ -76,7 +76,11 @@ def roofline(kernel, workload, fma, launch_ms, extra=None):
     column first and execute fewer than they are credited with."""
     ach = 2.0 * fma / (launch_ms / 1e3) / 1e12
     peak = PEAK_HALF_PAIR_TFLOPS if kernel in MATRIX_KERNELS else PEAK_FP32_TFLOPS
-    r = {"bound": "alu", "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
+    counted = ("the products of eq. (current) per (segment, pixel) pair; the kernel sums a group's charge per table column "
+               "first and executes fewer, so achieved and frac are not its execution rate"
+               if kernel in (INDUCE_KERNEL["sorted"], INDUCE_KERNEL["atomic"]) else
+               "the products of the summed columns' non-zero ticks, each executed")
+    r = {"bound": "alu", "counted": counted, "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
          "traffic": profiled_traffic(kernel, workload), "kernel": kernel, "flops_per_launch": 2.0 * fma,
          "launch_ms": launch_ms, "frac_of_nonpacked_fp32_peak": ach / PEAK_FP32_NONPACKED_TFLOPS,
          "nonpacked_fp32_peak": PEAK_FP32_NONPACKED_TFLOPS, "kernel_source": kernel_source_digest(),

@@ -21,10 +21,10 @@
  *     synchronises three times more, to size the summed columns, the pixels' piece lists and the merged records;
  *     it also runs the charge cells on a stream of the context's own, forked from the call's stream and joined back
  *     to it before anything the call leaves behind, so the call's stream still orders all of its work).  Calls on
- *     one context that use its scratch pool (lts_plan, lts_simulate, lts_simulate_batch, lts_stage_rasterize, lts_stage_induce,
- *     lts_stage_reduce, lts_stage_electronics) are ordered on the device whatever streams they are given: each one
- *     first makes its stream wait for the previous one's completion (a HIP event), so work of consecutive calls on
- *     different streams never overlaps in the shared scratch.
+ *     one context that use its scratch pool (lts_plan, lts_simulate, lts_simulate_batch, lts_stage_rasterize,
+ *     lts_stage_induce, lts_stage_reduce, lts_stage_electronics) are ordered on the device whatever streams they are
+ *     given: each one first makes its stream wait for the previous one's completion (a HIP event), so work of
+ *     consecutive calls on different streams never overlaps in the shared scratch.
  *   - No call throws across the ABI.  Every call returns an lts_status; on failure lts_last_error() gives a
  *     message.  A failed device call makes the context's status sticky (LTS_ERR_DEVICE).  A failed host-memory
  *     allocation inside a call returns LTS_ERR_OOM and leaves the context usable; any other internal C++
@@ -190,22 +190,24 @@ lts_status lts_set_channel_mask(lts_context *ctx, const uint8_t *mask, int64_t n
  * waveforms are added in a fixed order.  1 (default) = one workgroup per pixel. */
 lts_status lts_set_induce_slices(lts_context *ctx, int32_t slices);
 
-/* Induction kernel.  0 (default): the FP16 matrix cores, every FP32 factor split into a pair of halves (error against
- * FP64 no larger than the FP32 forms'): in the per-pair modes a workgroup per (pixel, group of segments), in
- * LTS_REDUCE_SUMMED one wavefront per (pixel, 768 ticks).  1, 2, 4 or 8: the FP32 vector kernels.  Per pair, each of the
- * 256 threads of a workgroup then computes that many consecutive ticks of a pair's window, with the same sums in the
- * same order for each of the four; in LTS_REDUCE_SUMMED 8 = one wavefront per (pixel, 512-tick tile) with
- * register-resident table windows, 1, 2, 4 = the per-pair workgroup kernel over the summed pieces.  All choices agree
- * to FP32 summation order.  A pixel one of whose decisions (threshold, LSB edge, the margins that flag them) lies within
- * twice the flags' margin gets its current in the vector kernels' order also with 0, so packets do not depend on the
- * choice between 0 and the vector kernels of the per-pair modes.  With more than one induce slice, 0 = the smallest vector tile that covers the table length
- * plus a typical charge extent. */
+/* Induction kernel.  0 (default): the FP16 matrix cores, every FP32 factor split into a pair of halves under a scale of
+ * its own tick (per pair) or record (summed), so that weak charge keeps its bits beside strong (error against FP64 no
+ * larger than the FP32 forms'): in the per-pair modes a workgroup per (pixel, group of segments), in LTS_REDUCE_SUMMED
+ * one wavefront per (pixel, 768 ticks).  1, 2, 4 or 8: the FP32 vector kernels.  Per pair, each of the 256 threads of a
+ * workgroup then computes that many consecutive ticks of a pair's window, with the same sums in the same order for each
+ * of the four; in LTS_REDUCE_SUMMED 8 = one wavefront per (pixel, 512-tick tile) with register-resident table windows,
+ * 1, 2, 4 = the per-pair workgroup kernel over the summed pieces.  All choices agree to FP32 summation order.  A pixel
+ * one of whose decisions (threshold, LSB edge, the margins that flag them) lies within twice the flags' margin gets its
+ * current in one stated order also with 0 (per pair the vector kernels'), so packets do not depend on the choice between
+ * 0 and the vector kernels of the per-pair modes.  With more than one induce slice, 0 = the smallest vector tile that
+ * covers the table length plus a typical charge extent. */
 lts_status lts_set_ticks_per_thread(lts_context *ctx, int32_t rt);
 
-/* Per-pair induction with explicit 8-tick tiles (lts_set_ticks_per_thread(8)): 1 = lanes share each table window by shifting it one lane per cell-tick
- * block (one coalesced load per column and lane); 0 (default, faster on gfx950) = every lane loads its own 15-value
- * window per block.
- * Both give the same sums in the same order.  A tuning option (Sec. 3.3.2 sets no kernel design). */
+/* Induction with explicit 8-tick tiles (lts_set_ticks_per_thread(8)): 1 = lanes share each table window by shifting it one
+ * lane per cell-tick block (one coalesced load per column and lane); 0 (default, faster on gfx950) = every lane loads its
+ * own 15-value window per block.  Both give the same sums in the same order.  With automatic ticks it has no effect in the
+ * per-pair modes; in LTS_REDUCE_SUMMED 1 then takes the 8-tick kernel.  A tuning option (Sec. 3.3.2 sets no kernel
+ * design). */
 lts_status lts_set_lane_exchange(lts_context *ctx, int32_t on);
 
 /* Sorted per-pair induction (Sec. 3.3.2, eq. (current)) on the FP32 matrix cores: 1 = per pair, the product of
@@ -317,9 +319,10 @@ lts_status lts_stage_electronics_noalloc(lts_context *ctx, uint64_t event_id, co
  * out[0] (segment, pixel) pairs; out[1] products c[a,u,v] * R[k,i,j] of eq. (current) that land in the tick
  * window, summed over pairs (the multiply-adds of the induction; in LTS_REDUCE_SUMMED the products of summed
  * column charges, summed over pixels, counting only ticks that hold charge); out[2] charge cells in reach summed over
- * pairs (summed columns' ticks with charge in reach summed over pixels in LTS_REDUCE_SUMMED); out[3] charge cells of all segments; out[4] (LTS_REDUCE_SUMMED
- * only, else 0) the products the summed induction kernel computes, zeros included (every 256- or 512-tick tile,
- * as the kernel choice sets, that a merged record's window meets, all its lanes, charge ticks rounded up to 8):
+ * pairs (summed columns' ticks with charge in reach summed over pixels in LTS_REDUCE_SUMMED); out[3] charge cells of
+ * all segments; out[4] (LTS_REDUCE_SUMMED only, else 0) the products the summed induction kernel computes, zeros
+ * included (every 256- or 512-tick tile, as the kernel choice sets, that a merged record's window meets, all its
+ * lanes, charge ticks in the kernel's steps of 32 or 8):
  * out[1] / out[4] is the useful fraction of its multiply-adds; out[5] the (pixel, merged record) records the
  * kernel walks in LTS_REDUCE_SUMMED, else the pairs. */
 lts_status lts_work_stats(lts_context *ctx, double out[6]);

@@ -2578,7 +2578,7 @@ static_assert(kPad >= kMmaSub + kMmaPart + 16 + 96, "summed matrix induction rea
 
 struct alignas(16) MmaStage {                           // LDS of one wavefront
     u32x4 r[2][kMmaOct];                                // [plane][octet] of the table window
-    uint32_t s[2][8][kMmaCopy / 2];                     // [plane][shift] of the reversed charge: copy k holds position m + k at m
+    uint32_t s[2][8][kMmaCopy / 2];                     // [plane][shift] of the reversed charge: copy k has m + k at m
 };
 
 // Scale of a table column of zeros: its charge never sets a common scale and becomes zero under any.
@@ -2717,10 +2717,13 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
                     qp = __builtin_amdgcn_readlane(pack, i);
                     xu = lane_value(up, i);
                     qn = __builtin_amdgcn_readlane(N, i);
-                    const int32_t o = __builtin_amdgcn_readlane((int)v_at, i), end = __builtin_amdgcn_readlane((int)v_end, i);
+                    const int32_t o = __builtin_amdgcn_readlane((int)v_at, i);
+                    const int32_t end = __builtin_amdgcn_readlane((int)v_end, i);
                     // loads past the ends return zeros without touching memory
-                    const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc((void *)Rh, (short)0, end, kBufferWord3);
-                    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)Rl, (short)0, end, kBufferWord3);
+                    const __amdgpu_buffer_rsrc_t rh =
+                        __builtin_amdgcn_make_buffer_rsrc((void *)Rh, (short)0, end, kBufferWord3);
+                    const __amdgpu_buffer_rsrc_t rw =
+                        __builtin_amdgcn_make_buffer_rsrc((void *)Rl, (short)0, end, kBufferWord3);
                     gh[0] = __builtin_amdgcn_raw_buffer_load_b128(rh, 16 * lane, o, 0);
                     gl[0] = __builtin_amdgcn_raw_buffer_load_b128(rw, 16 * lane, o, 0);
                     gh[1] = __builtin_amdgcn_raw_buffer_load_b128(rh, 16 * lane + 1024, o, 0);
@@ -2756,7 +2759,8 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
                                            (uint32_t)__builtin_bit_cast(uint16_t, l) << 16;
                         // lane + 1's values (DPP wave_shl:1, zero past lane 63: the next round writes that word again)
                         const uint32_t v = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x130, 0xf, 0xf, true);
-                        const uint32_t wh = __builtin_amdgcn_perm(v, w, 0x05040100), wl = __builtin_amdgcn_perm(v, w, 0x07060302);
+                        const uint32_t wh = __builtin_amdgcn_perm(v, w, 0x05040100);
+                        const uint32_t wl = __builtin_amdgcn_perm(v, w, 0x07060302);
                         if (r == 0 || lane < 40)            // (three steps read up to position 119)
 #pragma unroll
                             for (int k = 0; k < 4; ++k) {
@@ -2808,9 +2812,9 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
 // per staged tick (a row of Z), the largest that its own values bear, each times its column's scale: a tick of little
 // charge keeps its bits beside a bright one, and the scales are taken off before ticks meet in a sum.  The table octets
 // are laid out so that 16 table ticks of an octet are 256 consecutive bytes (a 16x16x32 operand of four octets is four
-// such runs).  Anti-diagonals: lane (tau, g) holds rows a = 4g .. 4g + 3 of a tile, so row a moves up by a lanes within its 16
-// (DPP row shifts; what leaves the 16 belongs to the next tile), and the four groups are added by lane swaps once per
-// 16 output ticks.
+// such runs).  Anti-diagonals: lane (tau, g) holds rows a = 4g .. 4g + 3 of a tile, so row a moves up by a lanes within
+// its 16 (DPP row shifts; what leaves the 16 belongs to the next tile), and the four groups are added by lane swaps once
+// per 16 output ticks.
 // A workgroup stages 32 ticks x 32 octets of C at a time, and each wavefront owns a range of output ticks (it also
 // computes the two table tiles below its range), so no sum is shared between wavefronts: the result depends only on
 // the segments' order.
@@ -2850,7 +2854,7 @@ struct ZJob {
 };
 
 struct alignas(16) ZStage {
-    u32x4 c[2][2][kZgOct][16];                          // [plane][16 ticks][octet][tick]: 8 halves (first 8 values, 4 a plane)
+    u32x4 c[2][2][kZgOct][16];                          // [plane][16 ticks][octet][tick]: 8 halves (4 FP32 values at first)
     i32x4 ex[kZgOct][2];                                // scales of an octet's bins
     int32_t top[2][kZgTicks];                           // [stage & 1][tick]: largest exponent of charge x column scale
     ZSeg seg[kZgSegs];

@@ -601,9 +601,8 @@ void launch_light(lts_light *L, uint64_t event_id, const float *ipe, double *mu_
     }
     const float *nzpre = nullptr;
     if (L->F > 0 && L->fft_log2 > 0) {
-        k_light_noise_fft<<<(unsigned)nd, (unsigned)std::min(1024, std::max(64, T / 16)), noise_fft_lds((size_t)T),
-                            st>>>(L->coef.p, L->F, T, L->fft_log2,
-                                                                              L->Ct.p, L->nz.p);
+        k_light_noise_fft<<<(unsigned)nd, (unsigned)std::min(1024, std::max(64, T / 16)), noise_fft_lds((size_t)T), st>>>(
+            L->coef.p, L->F, T, L->fft_log2, L->Ct.p, L->nz.p);
         nzpre = L->nz.p;
     }
     const dim3 gr((unsigned)((T + kLTile - 1) / kLTile), (unsigned)nd);

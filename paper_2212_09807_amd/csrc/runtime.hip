@@ -261,15 +261,14 @@ constexpr lts_status kNotAdmitted = LTS_ERR_NOT_READY;
 std::vector<DevBuf *> pool_buffers(lts_context *c) {
     return {&c->ev_cnt, &c->mask, &c->col_seg_off, &c->col_cursor, &c->col_seg, &c->col_tmp, &c->piece_off,
             &c->s_off, &c->piece, &c->pdesc, &c->S, &c->list_off, &c->list, &c->rec, &c->mlist_off, &c->m_off,
-            &c->mrec, &c->Sm, &c->segc, &c->part, &c->si, &c->cell_off, &c->pix_cnt, &c->cursor, &c->pix_slot, &c->slot_gp, &c->slot_off, &c->pairs_u,
-            &c->pairs, &c->cells, &c->pk_tick, &c->pk_adc,
+            &c->mrec, &c->Sm, &c->segc, &c->part, &c->si, &c->cell_off, &c->pix_cnt, &c->cursor, &c->pix_slot,
+            &c->slot_gp, &c->slot_off, &c->pairs_u, &c->pairs, &c->cells, &c->pk_tick, &c->pk_adc,
             &c->pk_flag, &c->pk_off, &c->hdr, &c->scan_tmp, &c->ev_off, &c->ev_ids, &c->report_tmp, &c->counts_tmp,
             &c->red_head, &c->red_start, &c->order};
 }
 
 // Frees the context's per-call scratch (everything in the pool but the channel mask, which persists across calls); every
-// buffer is grown again to the exact size the next call needs.  The caller makes sure
-// no queued work still uses them.
+// buffer is grown again to the exact size the next call needs.  The caller makes sure no queued work still uses them.
 void release_scratch(lts_context *c) {
     for (DevBuf *b : pool_buffers(c))
         if (b != &c->mask) free_buf(*b);
