@@ -2818,14 +2818,14 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
 // A workgroup stages 32 ticks x 32 octets of C at a time, and each wavefront owns a range of output ticks (it also
 // computes the two table tiles below its range), so no sum is shared between wavefronts: the result depends only on
 // the segments' order.
-//   What bounds it: dense events the table, which every stage streams from beyond L2 (7 TB/s; 6.5 of 8.6 ms are products
-// and their loads), so all loads of a tile pair are issued before its products (without that 14.6 ms); sparse ones the
-// latency of staging (584 of 1180 us for 64 tracks), so an octet's images are loaded eight at a time (four: 1218 us).  A
-// group saves work only where its segments share columns: 16 segments and 128 ticks (64 and 256 ticks measured the same).
-// Two workgroups of four wavefronts a CU: three spill (event 9.1 -> 9.8 ms).  64 ticks a stage halve the table reads but
-// leave one workgroup a CU (8.3 ms, tracks 1.67).  Atomic units of 8 segments (4: 4.7 ms, 8: 3.06, 16: 3.3).
-//   Measured against the vector kernels (45 x 45 x 1950 table unless said): sorted, 3000 segments 91.3 -> 8.6 ms; atomic,
-// 800 segments 50 -> 2.8 ms; one track on 20 x 31 x 1001 1.106 -> 0.072 ms, 64 such tracks 9.2 -> 1.18.
+//   What bounds it: dense events the table, which every stage streams from beyond L2 (59.6 GB in 8.5 ms for 3000 segments,
+// 7.0 TB/s, the matrix cores 21 % busy), so all loads of a tile pair are issued before its products (without that 14.6
+// ms); sparse ones the latency of staging, so an octet's images are loaded eight at a time (64 tracks 1.23 ms, four at a
+// time 3 % longer).  A group saves work only where its segments share columns: 16 segments and 128 ticks (64 and 256 ticks
+// measured the same).  Two workgroups of four wavefronts a CU: three spill (6 % longer).  64 ticks a stage halve the table
+// reads but leave one workgroup a CU (3 % less, tracks 40 % more).  Atomic units of 8 segments (4: 4.7 ms, 8: 3.06, 16: 3.3).
+//   Measured against the vector kernels (45 x 45 x 1950 table unless said): sorted, 3000 segments 91.3 -> 8.5 ms; atomic,
+// 800 segments 50 -> 2.8 ms; one track on 20 x 31 x 1001 1.106 -> 0.073 ms, 64 such tracks 9.2 -> 1.23.
 // Error against 64 bits, relative to all currents 1.7e-6 -> 1.5e-7, 9.5e-7 -> 1.4e-7 atomic; of a pixel relative to itself,
 // median and largest, 2.3e-6 and 1.0e-5 -> 1.2e-7 and 1.3e-6, a track's 4e-7 and 2.1e-6 -> 1.3e-7 and 7.8e-7.  (With one
 // scale for a group, 1 % less time, pixels that only the clouds' tails reach were off by up to 3e-3.)
