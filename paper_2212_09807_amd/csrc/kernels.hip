@@ -2552,14 +2552,15 @@ __global__ __launch_bounds__(kWG) void k_induce_summed(DevParams P, const SegInf
 // 16x16x32 instruction (lane l gives A[l % 16][8 (l / 16) ..] and B[8 (l / 16) ..][l % 16]).  The table words of a
 // record's window are staged in LDS (a tile reads each about 4 times), the charge as eight copies shifted by one value,
 // so that every lane's 8 consecutive (reversed) values are one aligned 16-byte word too; A then serves all tiles.
-// Tiles outside the record's window are skipped.  A part's products leave the matrix accumulators in its own scale and are
-// added to the lane's sums with Kahan compensation, in list order (deterministic and batch-invariant).
+// Tiles outside the record's window are skipped.  Every two parts the products leave the matrix accumulators and are added
+// to the lane's sums with Kahan compensation, in list order (deterministic and batch-invariant); the second part first
+// takes the accumulators to its own scale.
 //
 // The vector-ALU form of the same sums (256-tick units, 32 multiply-adds per lane against three LDS reads) took 37.5 ms
 // on a module event of 20,000 segments (13.6 million records, 1.37e12 products) and 36.2 ms on a spill tile of 64,000;
-// this one 17.1 and 17.0 ms, at an error against FP64 that is 0.7 to 0.95 of its (1.20e-7 against 1.30e-7 of the norm, of
-// a pixel at most 8e-7 of itself against 1.1e-6).  One scale for 64 records, added up after every 2 parts, would save 4 %
-// (16.4 ms), a small event's serial chains 7 %, and leave a pixel of little charge beside much with 1.5e-5.
+// this one 16.7 and 16.6 ms, at an error against FP64 that is 0.7 to 0.95 of its (1.21e-7 against 1.30e-7 of the norm, of
+// a pixel at most 8e-7 of itself against 1.1e-6).  One scale for 64 records would save 2 % (16.3 ms), a small event's serial
+// chains 8 %, and leave a pixel of little charge beside much with 1.5e-5; an addition after every part costs 2 %.
 // It runs at the card's power limit (2.07 GHz against 2.34 GHz), with the matrix cores busy 30 % and LDS about 75 % of
 // the time.  3 tiles per unit run 4 wavefronts per SIMD; 4 tiles (3 wavefronts) took 2 to 3 % longer, 2 tiles 10 % and
 // 1 tile 40 %: the charge is staged for fewer products.
@@ -2574,6 +2575,7 @@ constexpr int32_t kMmaPart = 72;                        // charge ticks taken at
 constexpr int32_t kMmaLow = 24;                         // staged charge position of a part's last tick
 constexpr int32_t kMmaCopy = 144;                       // halves of one shifted copy (288 B: the copies' banks differ by 8)
 constexpr int32_t kMmaOct = kMmaTiles * 32 + 16;        // octets (8 table values, 16 bytes) of the longest window
+constexpr int32_t kMmaKahanEvery = 2;                   // (more would scale D out of range)
 static_assert(kPad >= kMmaSub + kMmaPart + 16 + 96, "summed matrix induction reads");
 
 struct alignas(16) MmaStage {                           // LDS of one wavefront
@@ -2685,6 +2687,9 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
         float sum[4 * kMmaTiles], cmp[4 * kMmaTiles];
 #pragma unroll
         for (int r = 0; r < 4 * kMmaTiles; ++r) { sum[r] = 0.0f; cmp[r] = 0.0f; }
+        floatx4 D[kMmaTiles];
+#pragma unroll
+        for (int T = 0; T < kMmaTiles; ++T) D[T] = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
         for (int64_t c0 = pb; c0 < pe; c0 += 64) {
             // 64 records at a time: each lane prepares one
             PieceRef pr{0, 0, 0, 0};
@@ -2696,7 +2701,21 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
             // the record's scales: charge x 2^(N - eb) below 2^15; its products are 2^N times what they stand for
             const int32_t eb = meets ? Rexp[bin] : 0;
             const int32_t N = min(max(min(141 - (int32_t)((uint32_t)pr.bin >> kBinBits), 126) + eb, -126), 126);
-            const float up = ldexpf(1.0f, N - eb);
+            int pending = 0;                             // parts in D, and its scale
+            int32_t scale = 0;
+            auto flush = [&] {
+                const float down = __builtin_bit_cast(float, (127 - scale) << 23);
+#pragma unroll
+                for (int T = 0; T < kMmaTiles; ++T)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float y = fmaf(D[T][r], down, -cmp[4 * T + r]);
+                        const float t = sum[4 * T + r] + y;
+                        cmp[4 * T + r] = (t - sum[4 * T + r]) - y;
+                        sum[4 * T + r] = t;
+                    }
+                pending = 0;
+            };
             // records longer than kMmaPart ticks go in several rounds over the chunk
             for (int32_t done = 0;; done += kMmaPart) {
                 const int32_t L = min(pr.na - done, kMmaPart), a0 = pr.a0 + done;
@@ -2711,11 +2730,11 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
                 const uint64_t v_q = (uint64_t)(cell_ptr(S, Sm, nS8, pr.cell8) + done);
                 // a part in hand: its fields and the lane's words of it, loaded one part ahead
                 u32x4 gh[2], gl[2];
-                float x[2] = {0.0f, 0.0f}, xu = 0.0f;
-                int32_t qp = 0, qn = 0;
+                float x[2] = {0.0f, 0.0f};
+                int32_t qp = 0, qn = 0, qe = 0;
                 auto fetch = [&](int i) {
                     qp = __builtin_amdgcn_readlane(pack, i);
-                    xu = lane_value(up, i);
+                    qe = __builtin_amdgcn_readlane(eb, i);
                     qn = __builtin_amdgcn_readlane(N, i);
                     const int32_t o = __builtin_amdgcn_readlane((int)v_at, i);
                     const int32_t end = __builtin_amdgcn_readlane((int)v_end, i);
@@ -2735,11 +2754,22 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
                     if ((qp >> 9 & 3) > 2)
                         x[1] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rq, l4 - 4 * lane - 252, 0, 0));
                 };
-                if (mask) fetch(__builtin_ctzll(mask));
+                // the next part's scale n, the factor that takes D to it (none of D for the first of two parts; exact) and
+                // its charge's; a part weaker by 2^-64 than the one before stays in a scale that keeps that one finite
+                int32_t n = 0;
+                float by = 0.0f, xu = 0.0f;
+                auto scales = [&] {
+                    n = pending ? min(qn, scale + 64) : qn;
+                    by = __builtin_bit_cast(float, pending ? max(127 + n - scale, 0) << 23 : 0);
+                    xu = __builtin_bit_cast(float, (127 + max(n - qe, -127)) << 23);
+                };
+                if (mask) {
+                    fetch(__builtin_ctzll(mask));
+                    scales();
+                }
                 while (mask) {
                     mask &= mask - 1ull;
                     const int32_t p = qp, pk = p >> 9 & 3, pT0 = p >> 11 & 3, pT1 = p >> 13 & 3;
-                    const float down = __builtin_bit_cast(float, (127 - qn) << 23);
                     // the previous part's reads of the slice are done before it is overwritten
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
@@ -2775,22 +2805,16 @@ __global__ __launch_bounds__(kWG, 4) void k_induce_summed_mma(DevParams P, const
                     // A[i][8g + q] is at position 15 - i + 8g + q + (kMmaLow - (off + 16 - L))
                     const int32_t pos = pos0 - (p >> 15);
                     const u32x4 *sl = (const u32x4 *)&st.s[0][pos & 7][0] + (pos >> 3);
-                    floatx4 D[kMmaTiles];
 #pragma unroll
-                    for (int T = 0; T < kMmaTiles; ++T) D[T] = (floatx4){0.0f, 0.0f, 0.0f, 0.0f};
+                    for (int T = 0; T < kMmaTiles; ++T) D[T] *= by;
                     mma_dispatch(rl, sl, pk, pT0, pT1, D);
-#pragma unroll
-                    for (int T = 0; T < kMmaTiles; ++T)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const float y = fmaf(D[T][r], down, -cmp[4 * T + r]);
-                            const float t = sum[4 * T + r] + y;
-                            cmp[4 * T + r] = (t - sum[4 * T + r]) - y;
-                            sum[4 * T + r] = t;
-                        }
+                    scale = n;
+                    if (++pending == kMmaKahanEvery) flush();
+                    scales();
                 }
                 if (!__ballot(meets && pr.na > done + kMmaPart)) break;
             }
+            if (pending) flush();
         }
         float *wrow = wave + slot * NT;
 #pragma unroll
